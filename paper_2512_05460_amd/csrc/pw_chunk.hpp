@@ -1,0 +1,172 @@
+// What the walk kernels of every table form share: the probes of a
+// walk-sharing group, exact sums in LDS, the query's median, the claiming of
+// chunks by persistent launches and the watchdog's flag.
+#pragma once
+
+#include "pw_device.hpp"
+#include "pw_internal.hpp"
+
+namespace pw {
+
+// Probes [*kf, *kf + *sz) of walk-sharing group gi: groups of M probes inside
+// each block of B (the last group of a block may be smaller).
+__device__ __forceinline__ void group_probes(uint32_t gi, uint32_t B, uint32_t M, uint32_t gpb, uint32_t* kf,
+                                             uint32_t* sz)
+{
+    const uint32_t blk = gi / gpb;
+    const uint32_t j = gi - blk * gpb;
+    *kf = blk * B + j * M;
+    *sz = min(M, B - j * M);
+}
+
+__device__ __forceinline__ void lds_add_i128(unsigned long long* p, i128 v)
+{
+    const unsigned long long lo = (unsigned long long)(u128)v;
+    const unsigned long long hi = (unsigned long long)((u128)v >> 64);
+    const unsigned long long old = atomicAdd(p, lo);
+    const unsigned long long carry = (old + lo < old) ? 1ull : 0ull;
+    atomicAdd(p + 1, hi + carry);
+}
+
+// Median of the G block means (section 3.2, Algorithm 1 final loop).
+__device__ inline void finalize_query(const WalkArgs& A, const QueryDesc& d, double* ys)
+{
+    const uint32_t G = d.G;
+    const unsigned long long* bs = A.blocksum + (size_t)d.slot * A.gdim * 2;
+    for (uint32_t g = 0; g < G; ++g) {
+        const double y = (i128_to_f64(load_i128(bs + 2 * g)) * 0x1p-64) / (double)d.B;
+        ys[g] = y;
+        if (A.ybar_debug) A.ybar_debug[g] = y;
+    }
+    for (uint32_t i = 1; i < G; ++i) {
+        const double v = ys[i];
+        uint32_t j = i;
+        while (j > 0 && ys[j - 1] > v) {
+            ys[j] = ys[j - 1];
+            --j;
+        }
+        ys[j] = v;
+    }
+    const double med = (G & 1u) ? ys[G / 2] : 0.5 * (ys[G / 2 - 1] + ys[G / 2]);
+    A.beta[d.slot] = med;
+    if (A.recycle) {
+        // every chunk of this query has finished: the slot can be cleared for reuse
+        unsigned long long* w = A.blocksum + (size_t)d.slot * A.gdim * 2;
+        for (uint32_t g = 0; g < 2 * A.gdim; ++g) w[g] = 0ull;
+        A.done[d.slot] = 0u;
+    }
+    if (A.comp_ring) {
+        const uint32_t i = atomicAdd(A.comp_count, 1u);
+        Completion c;
+        c.slot = d.slot;
+        c.pad = 0u;
+        c.beta = med;
+        A.comp_ring[i % A.comp_cap] = c;
+    }
+    __threadfence();
+}
+
+// The host watchdog's abort flag (host memory, read at system scope; the
+// value is uniform over the work group once read by one thread, and a flag
+// seen late only lets one more chunk run).
+__device__ __forceinline__ bool abort_raised(const WalkArgs& A)
+{
+    return A.abort_flag != nullptr &&
+           __hip_atomic_load(A.abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0u;
+}
+
+// Part of a split group: add each probe's partial sums to its accumulator; the
+// chunk that brings a probe's replica count to R forms its Q_R. acc holds the
+// exact S1, S2 of the probes [k0, k0 + kc) over this chunk's pc replicas.
+__device__ __forceinline__ void finish_parts(const WalkArgs& A, const QueryDesc& d, uint32_t k0, uint32_t kc,
+                                             uint32_t pc, const unsigned long long* acc, double* ys)
+{
+    if (threadIdx.x == 0) {
+        for (uint32_t j = 0; j < kc; ++j) {
+            const uint32_t k = k0 + j;
+            const size_t pi = (size_t)d.psum_base + k;
+            unsigned long long* ps = A.psum + pi * 4;
+            atomic_add_i128(ps, (i128)(((u128)acc[4 * j + 1] << 64) | (u128)acc[4 * j]));
+            atomic_add_i128(ps + 2, (i128)(((u128)acc[4 * j + 3] << 64) | (u128)acc[4 * j + 2]));
+            __threadfence();
+            const uint32_t prev = atomicAdd(A.pcount + pi, pc);
+            if (prev + pc == d.R) {
+                __threadfence();
+                const i128 S1 = load_i128(ps);
+                const u128 S2 = (u128)load_i128(ps + 2);
+                const double Q = probe_q(S1, S2, d.R);
+                if (A.q_debug) A.q_debug[k] = Q;
+                atomic_add_i128(A.blocksum + ((size_t)d.slot * A.gdim + k / d.B) * 2, f64_to_i128_trunc(Q * 0x1p64));
+                // every part of this probe has been added: clear it for reuse
+                ps[0] = ps[1] = ps[2] = ps[3] = 0ull;
+                A.pcount[pi] = 0u;
+                __threadfence();
+                const uint32_t old = atomicAdd(A.done + d.slot, 1u);
+                if (old + 1u == d.K()) {
+                    __threadfence();
+                    finalize_query(A, d, ys);
+                }
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// Whole probes [k0, k0 + kc): each forms its Q_R from the exact sums in acc and
+// adds it to its block; the one that completes the query forms the median.
+__device__ __forceinline__ void finish_probes(const WalkArgs& A, const QueryDesc& d, uint32_t k0, uint32_t kc,
+                                              const unsigned long long* acc, double* ys, uint32_t threads)
+{
+    for (uint32_t j = threadIdx.x; j < kc; j += threads) {
+        const i128 S1 = (i128)(((u128)acc[4 * j + 1] << 64) | (u128)acc[4 * j]);
+        const u128 S2 = ((u128)acc[4 * j + 3] << 64) | (u128)acc[4 * j + 2];
+        const double Q = probe_q(S1, S2, d.R);
+        const uint32_t k = k0 + j;
+        if (A.q_debug) A.q_debug[k] = Q;
+        atomic_add_i128(A.blocksum + ((size_t)d.slot * A.gdim + k / d.B) * 2, f64_to_i128_trunc(Q * 0x1p64));
+    }
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t old = atomicAdd(A.done + d.slot, kc);
+        if (old + kc == d.K()) {
+            __threadfence();
+            finalize_query(A, d, ys);
+        }
+    }
+    __syncthreads();
+}
+
+// Claim chunks from the queue of this XCD first, then from the others in
+// turn. A queue seen empty stays empty (its cursor only grows), so each
+// work group makes at most nqueues failed claims and every wave exits.
+// qstate: the current queue and how many were found empty.
+__device__ __forceinline__ void first_queue(const WalkArgs& A, uint32_t* qstate)
+{
+    uint32_t xcc = 0;
+    if (A.nqueues > 1) asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
+    qstate[0] = (xcc & 15u) % A.nqueues;
+    qstate[1] = 0;
+}
+
+__device__ __forceinline__ uint32_t claim_chunk(const WalkArgs& A, uint32_t* qstate)
+{
+    uint32_t ci = 0xFFFFFFFFu;
+    uint32_t qi = qstate[0], tried = qstate[1];
+    if (abort_raised(A)) tried = A.nqueues;  // take no further chunk
+    while (tried < A.nqueues) {
+        const uint32_t beg = A.qoff[qi];
+        const uint32_t c = atomicAdd(A.cursor + qi, 1u);
+        if (c < A.qoff[qi + 1] - beg) {
+            ci = beg + c;
+            break;
+        }
+        qi = qi + 1 == A.nqueues ? 0u : qi + 1;
+        ++tried;
+    }
+    qstate[0] = qi;
+    qstate[1] = tried;
+    return ci;
+}
+
+}  // namespace pw

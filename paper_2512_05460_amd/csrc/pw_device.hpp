@@ -52,6 +52,33 @@ __device__ __forceinline__ U4 philox10(uint32_t c0, uint32_t c1, uint32_t c2, ui
     return U4{c0, c1, c2, c3};
 }
 
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
+{
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
+// philox10 as the walks call it: block, query and (where a wave walks for one
+// probe) k are the same in every lane, so the first four rounds are mostly
+// scalar and stay in plain form; from the fifth on every word differs from
+// lane to lane and one three-input instruction replaces two exclusive ors.
+__device__ __forceinline__ U4 philox10_walk(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
+                                            uint32_t k1)
+{
+#pragma unroll
+    for (int r = 0; r < 10; ++r) {
+        const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
+        const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
+        const uint32_t h0 = (uint32_t)(p0 >> 32), h1 = (uint32_t)(p1 >> 32);
+        c0 = r < 4 ? h1 ^ c1 ^ k0 : xor3(h1, c1, k0);
+        c2 = r < 4 ? h0 ^ c3 ^ k1 : xor3(h0, c3, k1);
+        c1 = (uint32_t)p1;
+        c3 = (uint32_t)p0;
+        k0 += 0x9E3779B9u;
+        k1 += 0xBB67AE85u;
+    }
+    return U4{c0, c1, c2, c3};
+}
+
 // ---------------------------------------------------------------------------
 // Probe domain (per graph) and probe keys (per query and probe index k)
 // ---------------------------------------------------------------------------
@@ -107,21 +134,26 @@ __device__ __forceinline__ uint32_t fmix(uint32_t v, uint32_t key)
     return umul24(h, 0x873593u);
 }
 
-// pi_k(x): Feistel rounds alternate L <- (L + F(R)) mod A and R <- R ^ top_rb(F(L));
-// values that land in [n, A*2^rb) are walked again until they fall in [n].
+// Feistel rounds alternate L <- (L + F(R)) mod A and R <- R ^ top_rb(F(L)).
+__device__ __forceinline__ uint32_t feistel_once(uint32_t x, const Probe& pr, const Domain& dm)
+{
+    uint32_t L = x >> dm.rb;
+    uint32_t R = x & dm.mask;
+#pragma unroll
+    for (int r = 0; r < kFeistelRounds; r += 2) {
+        const uint32_t f = umul24hi(fmix(R, pr.K[r]) >> 8, dm.A8);
+        const uint32_t t = L + f;
+        L = min(t, t - dm.A);  // (L + f) mod A, since L + f < 2A
+        R ^= (fmix(L, pr.K[r + 1]) >> dm.rsh) & dm.mask;
+    }
+    return (L << dm.rb) | R;
+}
+
+// pi_k(x): values that land in [n, A*2^rb) are walked again until they fall in [n].
 __device__ __forceinline__ uint32_t feistel_pi(uint32_t x, const Probe& pr, const Domain& dm)
 {
     do {
-        uint32_t L = x >> dm.rb;
-        uint32_t R = x & dm.mask;
-#pragma unroll
-        for (int r = 0; r < kFeistelRounds; r += 2) {
-            const uint32_t f = umul24hi(fmix(R, pr.K[r]) >> 8, dm.A8);
-            const uint32_t t = L + f;
-            L = min(t, t - dm.A);  // (L + f) mod A, since L + f < 2A
-            R ^= (fmix(L, pr.K[r + 1]) >> dm.rsh) & dm.mask;
-        }
-        x = (L << dm.rb) | R;
+        x = feistel_once(x, pr, dm);
     } while (x >= dm.n);
     return x;
 }

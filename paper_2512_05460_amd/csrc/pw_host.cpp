@@ -19,6 +19,7 @@
 
 #include "probewalk.h"
 #include "pw_internal.hpp"
+#include "pw_signtab.hpp"
 
 using namespace pw;
 
@@ -165,6 +166,11 @@ struct bd_graph {
     uint32_t run_h1 = 0, run_words = 0, run_ninv = 0;  // code 8: direct row offsets, words of runtab, d_max + 1
     uint32_t run_shift = 0;                            // code 8: log2 of the storage ids per record
     bool runs_shared = false;                          // code 8: the table fits the walk-sharing kernels
+    DevBuf sblk, sids, slds, spid;                     // tables of the sign-table kernels (none: empty)
+    SignTables signs{}, signs_lds{};                   // the two forms' arguments
+    SignShape sign_shape[3][kSignShapes];              // launch shapes for 1, 2 and 4 probes per walk
+    std::vector<uint32_t> spos, sid4;                  // storage id -> position, or 4 x id, in those tables
+    std::atomic<int> resident[6 + 6 * kSignShapes] = {};  // work groups on the device at once, by kernel (0: not asked)
     DomainParams dom{};
     int64_t device_bytes = 0;
     std::mutex mu;  // serialises calls that use the per-graph work buffers
@@ -271,6 +277,197 @@ int fetch_device_csr(int64_t n, const int64_t* row_ptr, const int32_t* col_idx, 
     col.resize((size_t)std::max<int64_t>(nnz, 1));
     if (nnz) HIP_TRY(hipMemcpyAsync(col.data(), col_idx, (size_t)nnz * 4, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
+    return BD_OK;
+}
+
+// The kernel code that runs walks of sharing class `share` on g: the graph's,
+// except that walk sharing on the degree-run table runs code 8's sharing
+// kernels, which hold a smaller copy, or code 7's (the same tables and
+// results) where it does not fit them.
+int run_kernel(const bd_graph* g, int share)
+{
+    if (runs_layout(g->kernel_layout) && share > 1) return g->runs_shared ? kLayoutHubRuns : kLayoutHubIdX2;
+    return g->kernel_layout;
+}
+
+// Kernels a query's chunks can run on: the sign-table kernels or the general
+// walk kernels, each wave-uniform (R >= kUniformMinR) or not. A batch's chunk
+// table holds its queries' chunks in this order, one launch each.
+enum KernelPart { kSignUniform = 0, kSignAny = 1, kWalkUniform = 2, kWalkAny = 3, kKernelParts = 4 };
+constexpr bool sign_part(int part) { return part < kWalkUniform; }
+
+int share_index(int share) { return share == 4 ? 2 : share - 1; }
+const SignShape& sign_shape(const bd_graph* g, int share, int shape) { return g->sign_shape[share_index(share)][shape]; }
+
+// Work groups of a kernel that the device holds at once (asked once per graph).
+int resident_wgs(const bd_graph* g, int part, int share, int shape)
+{
+    const int i = share_index(share) * 2 + (part & 1);
+    std::atomic<int>& kept = const_cast<bd_graph*>(g)->resident[sign_part(part) ? 6 + i * kSignShapes + shape : i];
+    int r = kept.load(std::memory_order_relaxed);
+    if (r > 0) return r;
+    int per_cu = 0;
+    const bool uniform = part == kSignUniform || part == kWalkUniform;
+    const int rc = sign_part(part) ? signs_occupancy(sign_shape(g, share, shape), uniform, share, &per_cu)
+                                   : walk_occupancy(run_kernel(g, share), uniform, share, &per_cu);
+    if (rc != 0 || per_cu < 1) per_cu = 1;
+    r = per_cu * (int)g->cus;
+    kept.store(r, std::memory_order_relaxed);
+    return r;
+}
+
+uint32_t storage_id(const bd_graph* g, int32_t v)
+{
+    return g->internal.empty() ? (uint32_t)v : g->internal[(size_t)v];
+}
+
+// Launch shapes of the sign-table kernels for M probes per walk: four to one
+// work groups per CU, each with as many tables as its share of the LDS holds,
+// the adjacency in LDS where it fits beside one group's tables.
+void plan_sign_shapes(const SignTables& mem, const SignTables& lds, uint32_t M, SignShape out[kSignShapes])
+{
+    const uint32_t threads[kSignShapes] = {512, 512, 1024, 1024}, per_cu[kSignShapes] = {4, 3, 2, 1};
+    const uint32_t budget[kSignShapes] = {39680, 53480, 80640, kSignLdsMost};
+    bool found = false;
+    for (int form = 1; form >= 0 && !found; --form) {
+        const SignTables& t = form ? lds : mem;
+        if (!t.tabw) continue;
+        const uint64_t fixed = form ? 4ull * (t.nblk + t.idw) : 16ull * t.nblk;
+        const uint64_t per = 4ull * t.tabw + 32;  // a table and its two sums
+        for (int i = 0; i < kSignShapes; ++i) {
+            if (fixed + std::max<uint64_t>(M * per, M * 32 + kMaxG * 8) > budget[i]) continue;
+            SignShape& s = out[i];
+            s.lds = form;
+            s.threads = threads[i];
+            s.per_cu = per_cu[i];
+            s.T = (uint32_t)std::min<uint64_t>(64, (budget[i] - fixed) / per);
+            s.bytes = (uint32_t)(fixed + std::max<uint64_t>(s.T * per, s.T * 32 + kMaxG * 8));
+            found = true;
+        }
+    }
+}
+
+// Waves per CU with walks to run when probes have R replicas: as many as the
+// tables that a work group holds give work to.
+uint32_t sign_waves(const SignShape& s, uint32_t share, uint32_t R)
+{
+    if (!s.threads) return 0;
+    const uint64_t groups = s.T / share, waves = R >= kUniformMinR ? groups * ((R + 63ull) / 64) : groups * R / 64;
+    return s.per_cu * (uint32_t)std::min<uint64_t>(s.threads / 64, waves);
+}
+
+// Tables of the sign-table kernels, for graphs whose block table and one sign
+// table fit a CU's LDS. `order`: storage id -> caller id (empty: the tables are
+// stored in the caller's order, and the descending-degree one is made here).
+int load_sign_tables(bd_graph* g, const std::vector<uint32_t>& order_in, const int64_t* row_ptr, const int32_t* col_idx,
+                     hipStream_t st)
+{
+    const size_t n = (size_t)g->n, nnz = (size_t)g->nnz;
+    if (n > (size_t(1) << 22) || nnz == 0 || 3 * nnz + 8 > UINT32_MAX) return BD_OK;
+    std::vector<uint32_t> order = order_in;
+    if (order.empty()) {
+        order.resize(n);
+        std::vector<uint32_t> first((size_t)g->d_max + 2, 0u);
+        for (size_t v = 0; v < n; ++v) ++first[(size_t)(g->d_max - g->deg[v]) + 1];
+        for (size_t d = 1; d < first.size(); ++d) first[d] += first[d - 1];
+        for (size_t v = 0; v < n; ++v) order[first[(size_t)(g->d_max - g->deg[v])]++] = (uint32_t)v;
+    }
+    std::vector<uint32_t> rp(n + 1);
+    rp[0] = 0;
+    for (size_t i = 0; i < n; ++i) rp[i + 1] = rp[i] + (uint32_t)g->deg[order[i]];
+    SignOrder so;
+    SignTables mem{}, lds{};
+    if (plan_sign_order(rp, &so)) {
+        mem.np = so.np;
+        mem.shift = so.shift;
+        mem.nblk = so.nblk;
+        mem.tabw = so.np / 16;
+    }
+    if (n <= 16384 && nnz <= 65535 && g->d_max <= 65535) {
+        lds.np = (uint32_t)n;
+        lds.nblk = (uint32_t)((n + 3) & ~(size_t)3);
+        lds.idw = (uint32_t)((nnz + 7) / 8 * 4);
+        lds.tabw = (uint32_t)n;
+    }
+    bool use[2] = {false, false};
+    for (int c = 0; c < 3; ++c) {
+        plan_sign_shapes(mem, lds, 1u << c, g->sign_shape[c]);
+        for (const SignShape& s : g->sign_shape[c])
+            if (s.threads) use[s.lds] = true;
+    }
+    int rc = BD_OK;
+    if (use[1]) {
+        // rows and adjacency in the order of the ids that probes are evaluated on
+        const bool ranked = g->layout == 5;
+        std::vector<uint32_t> rank(ranked ? n : 0), tab(lds.nblk + lds.idw, 0u);
+        for (size_t i = 0; i < rank.size(); ++i) rank[order[i]] = (uint32_t)i;
+        uint32_t at = 0;
+        for (size_t i = 0; i < n; ++i) {
+            const size_t v = ranked ? order[i] : i;
+            tab[i] = at | (uint32_t)g->deg[v] << 16;
+            for (int64_t j = row_ptr[v]; j < row_ptr[v + 1]; ++j, ++at) {
+                const uint32_t x = ranked ? rank[(size_t)col_idx[j]] : (uint32_t)col_idx[j];
+                tab[lds.nblk + at / 2] |= 4u * x << (16u * (at & 1u));
+            }
+        }
+        rc = g->slds.alloc(tab.size() * 4);
+        if (rc != BD_OK) return rc;
+        HIP_TRY(hipMemcpyAsync(g->slds.p, tab.data(), tab.size() * 4, hipMemcpyHostToDevice, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        lds.blk = g->slds.as<const uint4>();
+        g->signs_lds = lds;
+        g->sid4.resize(n);
+        for (size_t v = 0; v < n; ++v) g->sid4[storage_id(g, (int32_t)v)] = 4u * (ranked ? rank[v] : (uint32_t)v);
+    }
+    if (use[0]) {
+        std::vector<uint32_t> pos, blk;
+        build_sign_order(rp, so, &pos, &blk);
+        // positions by caller id; the table words that hold nodes, and the ids
+        // that their 16 positions' probe values are evaluated on
+        std::vector<uint32_t> at(n), word, pid;
+        for (size_t i = 0; i < n; ++i) {
+            at[order[i]] = pos[i];
+            if (word.empty() || word.back() != pos[i] / 16) {
+                word.push_back(pos[i] / 16);
+                pid.resize(pid.size() + 16, 0u);
+            }
+            pid[pid.size() - 16 + pos[i] % 16] = g->layout == 5 ? (uint32_t)i : order[i];
+        }
+        // as the kernel reads them: of 64 words, each one's first four ids, then the next four, ...
+        const size_t segs = (word.size() + 63) / 64;
+        std::vector<uint32_t> ids_by_lane(segs * 1024, 0u);
+        for (size_t w = 0; w < word.size(); ++w)
+            for (size_t i = 0; i < 16; ++i)
+                ids_by_lane[(w / 64) * 1024 + (i / 4) * 256 + (w % 64) * 4 + i % 4] = pid[16 * w + i];
+        pid.swap(ids_by_lane);
+        mem.words = (uint32_t)word.size();
+        pid.insert(pid.end(), word.begin(), word.end());
+        std::vector<uint8_t> ids(3 * nnz + 8, 0);
+        size_t e = 0;
+        for (size_t i = 0; i < n; ++i) {
+            const uint32_t v = order[i];
+            for (int64_t j = row_ptr[v]; j < row_ptr[v + 1]; ++j, e += 3) {
+                const uint32_t x = at[(size_t)col_idx[j]];
+                ids[e] = (uint8_t)x;
+                ids[e + 1] = (uint8_t)(x >> 8);
+                ids[e + 2] = (uint8_t)(x >> 16);
+            }
+        }
+        rc = g->sblk.alloc(blk.size() * 4);
+        if (rc == BD_OK) rc = g->spid.alloc(pid.size() * 4);
+        if (rc == BD_OK) rc = g->sids.alloc(ids.size());
+        if (rc != BD_OK) return rc;
+        HIP_TRY(hipMemcpyAsync(g->sblk.p, blk.data(), blk.size() * 4, hipMemcpyHostToDevice, st));
+        HIP_TRY(hipMemcpyAsync(g->spid.p, pid.data(), pid.size() * 4, hipMemcpyHostToDevice, st));
+        HIP_TRY(hipMemcpyAsync(g->sids.p, ids.data(), ids.size(), hipMemcpyHostToDevice, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        mem.blk = g->sblk.as<const uint4>();
+        mem.pid = g->spid.as<const uint32_t>();
+        mem.ids = g->sids.as<const uint32_t>();
+        g->signs = mem;
+        g->spos.resize(n);
+        for (size_t v = 0; v < n; ++v) g->spos[storage_id(g, (int32_t)v)] = at[v];
+    }
     return BD_OK;
 }
 
@@ -534,8 +731,21 @@ extern "C" int graph_load_csr(int64_t n, const int64_t* row_ptr, const int32_t* 
             g->runs_shared = ((runtab.size() + 3) & ~(size_t)3) + g->run_ninv <= kRunWordsShared;
         }
     }
+    if (!(flags & (BD_NARROW_HUBS | BD_DIRECT_HUBS | BD_WIDE_HUBS))) {
+        const int src = load_sign_tables(g, order, row_ptr, col_idx, st);
+        if (src != BD_OK) {
+            delete g;
+            return src;
+        }
+        // (the first question also allows the kernels their LDS)
+        for (const int share : {1, 2, 4})
+            for (const int part : {kSignUniform, kSignAny})
+                for (int i = 0; i < kSignShapes; ++i)
+                    if (sign_shape(g, share, i).threads) resident_wgs(g, part, share, i);
+    }
     g->device_bytes = (int64_t)(g->node.bytes + g->col.bytes + g->adj.bytes + g->rp32.bytes + g->col24.bytes +
-                                g->node8.bytes + g->runtab.bytes);
+                                g->node8.bytes + g->runtab.bytes + g->sblk.bytes + g->sids.bytes + g->slds.bytes +
+                                g->spid.bytes);
     *out = g;
     return BD_OK;
 }
@@ -666,9 +876,32 @@ extern "C" int bd_plan(const bd_graph* g, int64_t nq, const int32_t* s, const in
 // ---------------------------------------------------------------------------
 namespace {
 
-uint32_t storage_id(const bd_graph* g, int32_t v)
+// The endpoints in the tables of the sign-table kernels (0 where the graph has none).
+void set_positions(const bd_graph* g, QueryDesc& d)
 {
-    return g->internal.empty() ? (uint32_t)v : g->internal[(size_t)v];
+    bool lds = false;
+    for (const SignShape& s : g->sign_shape[share_index(share_class(d.share))]) lds |= s.lds != 0;
+    const std::vector<uint32_t>& at = lds ? g->sid4 : g->spos;
+    d.ss = at.empty() ? 0u : at[(size_t)d.s];
+    d.st = at.empty() ? 0u : at[(size_t)d.t];
+}
+
+// The sign-table kernels' arguments for sharing class `share` in a launch shape.
+SignTables sign_tables(const bd_graph* g, int share, int shape)
+{
+    const SignShape& sh = sign_shape(g, share, shape);
+    SignTables t = sh.lds ? g->signs_lds : g->signs;
+    t.T = sh.T;
+    return t;
+}
+
+// One launch over the chunks of `a` on the kernel of `part`.
+hipError_t launch_kernel(const bd_graph* g, WalkArgs& a, int part, int share, int shape, uint32_t grid, hipStream_t st)
+{
+    const int uniform = part == kSignUniform || part == kWalkUniform;
+    if (!sign_part(part)) return launch_walk(a, run_kernel(g, share), uniform, share, grid, st);
+    a.signs = sign_tables(g, share, shape);
+    return launch_signs(a, sign_shape(g, share, shape), uniform, share, grid, st);
 }
 
 GraphTables tables(const bd_graph* g)
@@ -689,23 +922,50 @@ GraphTables tables(const bd_graph* g)
     return t;
 }
 
-// The kernel code that runs walks of sharing class `share` on g: the graph's,
-// except that walk sharing on the degree-run table runs code 8's sharing
-// kernels, which hold a smaller copy, or code 7's (the same tables and
-// results) where it does not fit them.
-int run_kernel(const bd_graph* g, int share)
+// The sign-table kernels' shape for a query, or -1 where the general kernel is
+// the better one. Twelve walking waves per CU keep enough reads in flight to
+// reach the L2 request rate; of the shapes that have them, more work groups
+// overlap one's table building with the others' walks. A table costs one
+// evaluation of the probe per node position and saves one per scored step,
+// 2 (L + 1) min(R, kSplitReplicas) of them in a chunk: taken from one per
+// position on (eight against the degree-run kernel, which also reads once per
+// step and is bound by those reads), and from 4 waves per CU.
+int query_shape(const bd_graph* g, const QueryDesc& d)
 {
-    if (runs_layout(g->kernel_layout) && share > 1) return g->runs_shared ? kLayoutHubRuns : kLayoutHubIdX2;
-    return g->kernel_layout;
+    const int share = share_class(d.share);
+    const uint64_t scored = 2 * std::min<uint64_t>(d.R, kSplitReplicas) * ((uint64_t)d.L + 1);
+    int best = -1;
+    uint32_t most = 0;
+    for (int i = 0; i < kSignShapes; ++i) {
+        const SignShape& s = sign_shape(g, share, i);
+        const uint32_t waves = sign_waves(s, std::max<uint32_t>(d.share, 1u), d.R);
+        const uint32_t score = waves < 4 ? 0 : std::min<uint32_t>(waves, 12) * 4 + s.per_cu;
+        if (score <= most) continue;
+        most = score;
+        best = i;
+    }
+    if (best < 0) return -1;
+    const uint64_t positions = (sign_shape(g, share, best).lds ? g->signs_lds : g->signs).np;
+    const bool one_read = runs_layout(g->kernel_layout) && share == 1 && !sign_shape(g, share, best).lds;
+    return scored >= positions * (one_read ? 8 : 1) ? best : -1;
 }
 
-int resident_wgs(const bd_graph* g, int uniform, int share = 1)
+// The one shape that a launch over several queries takes: the one that most of
+// their walk steps ask for.
+struct ShapeVote {
+    double steps[kSignShapes] = {};
+    void add(int shape, double work) { steps[shape] += work; }
+    int best() const { return (int)(std::max_element(steps, steps + kSignShapes) - steps); }
+};
+
+// Pairs of one pass over a work group, as chunks are sized by: those that a
+// work group of the general kernel runs at once, or 1,024 on the sign-table
+// kernels where that is more (chunks are never cut finer for it, so that a batch needs
+// no more chunks and accumulators than the general kernel's).
+uint32_t query_lanes(const bd_graph* g, const QueryDesc& d, bool signs)
 {
-    int per_cu = 0;
-    if (walk_occupancy(run_kernel(g, share), uniform, share, &per_cu) != 0 || per_cu < 1) per_cu = 1;
-    hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, g->device) != hipSuccess) return per_cu * 256;
-    return per_cu * prop.multiProcessorCount;
+    const int share = share_class(d.share);
+    return std::max((uint32_t)group_pairs(g->kernel_layout, share), signs ? 1024u : 0u);
 }
 
 // How the probes of one query are cut into work-group chunks.
@@ -739,13 +999,13 @@ struct Groups {
     uint32_t size(uint32_t gi) const { return std::min(M, B - (gi % per_block) * M); }
 };
 
-ChunkPlan chunk_plan(const bd_exec& ex, const QueryDesc& d, int layout, uint32_t spread = 0)
+ChunkPlan chunk_plan(const bd_exec& ex, const QueryDesc& d, uint32_t lanes, uint32_t spread = 0)
 {
     ChunkPlan cp;
     const Groups grp(d);
     const uint32_t R = d.R;
     const uint32_t pairs = ex.chunk_pairs > 0 ? std::max<uint32_t>((uint32_t)ex.chunk_pairs, 64u)
-                           : ex.mode == BD_MODE_PLAIN ? (uint32_t)group_pairs(layout, share_class(d.share))
+                           : ex.mode == BD_MODE_PLAIN ? lanes
                                                       : kSplitReplicas;
     if (ex.mode != BD_MODE_PLAIN && R >= kUniformMinR && R > pairs) {
         const uint32_t parts = (R + pairs - 1) / pairs;
@@ -784,8 +1044,8 @@ struct ChunkCursor {
     ChunkPlan plan;
     uint32_t next_g = 0, next_p = 0;
     ChunkCursor() = default;
-    ChunkCursor(uint32_t q_, const QueryDesc& d, const bd_exec& ex, int layout, uint32_t spread = 0)
-        : q(q_), R(d.R), grp(d), plan(chunk_plan(ex, d, layout, spread))
+    ChunkCursor(uint32_t q_, const QueryDesc& d, const bd_exec& ex, uint32_t lanes, uint32_t spread = 0)
+        : q(q_), R(d.R), grp(d), plan(chunk_plan(ex, d, lanes, spread))
     {
     }
     bool done() const { return next_g >= grp.n; }
@@ -830,11 +1090,14 @@ struct Batch {
     std::vector<uint32_t> chunk_begin;  // per valid query, first chunk (chunks grouped by query)
     std::vector<int64_t> index;         // valid query -> caller's index
     uint32_t G = 0;
-    uint32_t n_uniform = 0;             // chunks [0, n_uniform) belong to queries with R >= kUniformMinR
-    // chunk queues of the persistent launches: part 0 = [0, n_uniform), part 1 =
-    // the rest; qoff[part][i] is the first chunk of queue i relative to the part
+    uint32_t part_begin[kKernelParts + 1] = {};  // chunks of each kernel part
+    std::vector<uint8_t> part;          // per valid query, its kernel part
+    std::vector<int> shapes;            // per valid query, the sign-table kernels' shape for it (-1: general kernel)
+    int shape = 0;                      // the shape of the batched sign-table launches
+    // chunk queues of the persistent launches: qoff[part][i] is the first chunk
+    // of queue i relative to the part
     uint32_t nqueues = 1;
-    uint32_t qoff[2][kMaxQueues + 1] = {};
+    uint32_t qoff[kKernelParts][kMaxQueues + 1] = {};
     int share = 1;                      // kernel instance for the walk-sharing factor
 };
 
@@ -854,10 +1117,10 @@ void work_sizes(const Batch& b, bool qdbg, bool ydbg, size_t sz[10])
     sz[2] = nv * (size_t)b.G * 16;
     sz[3] = nv * 4;
     sz[4] = nv * 8;
-    sz[5] = 2 * kMaxQueues * 4;
+    sz[5] = kKernelParts * kMaxQueues * 4;
     sz[6] = (size_t)b.split_probes * 32;
     sz[7] = (size_t)b.split_probes * 4;
-    sz[8] = qdbg ? (size_t)b.qd[0].K * 8 : 0;
+    sz[8] = qdbg ? (size_t)b.qd[0].K() * 8 : 0;
     sz[9] = ydbg ? (size_t)b.G * 8 : 0;
 }
 
@@ -949,36 +1212,39 @@ int run_batch(bd_graph* g, const Batch& b, const bd_exec& ex, hipStream_t user_s
     a.q_debug = q_dbg_host ? static_cast<double*>(w.qdbg) : nullptr;
     a.ybar_debug = y_dbg_host ? static_cast<double*>(w.ydbg) : nullptr;
     a.abort_flag = watch ? g->ws.abort_dev : nullptr;
-    const int layout = run_kernel(g, b.share);
-
     // the zeroing every launch needs
     auto zero_all = [&](hipStream_t s2) -> int {
         if (launch_zero(w.bs, nv * gdim * 16, s2) != hipSuccess) return BD_E_HIP;
         if (launch_zero(w.done, nv * 4, s2) != hipSuccess) return BD_E_HIP;
-        if (launch_zero(w.cursor, 2 * kMaxQueues * 4, s2) != hipSuccess) return BD_E_HIP;
+        if (launch_zero(w.cursor, kKernelParts * kMaxQueues * 4, s2) != hipSuccess) return BD_E_HIP;
         if (launch_zero(w.psum, (size_t)b.split_probes * 32, s2) != hipSuccess) return BD_E_HIP;
         if (launch_zero(w.pcount, (size_t)b.split_probes * 4, s2) != hipSuccess) return BD_E_HIP;
         return BD_OK;
     };
-    // the persistent launches of the batched mode: wave-uniform chunks, then the rest
-    uint32_t grids[2] = {0, 0};
-    const uint32_t parts[3] = {0u, b.n_uniform, (uint32_t)b.chunks.size()};
-    for (int part = 0; part < 2; ++part) {
-        const uint32_t nch = parts[part + 1] - parts[part];
-        uint32_t grid = ex.grid_wgs > 0 ? (uint32_t)ex.grid_wgs : (uint32_t)resident_wgs(g, part == 0, b.share);
+    // a launch of one kernel part
+    auto launch_part = [&](WalkArgs& aw, int part, int shape, uint32_t grid, hipStream_t s2) -> int {
+        return launch_kernel(g, aw, part, b.share, shape, grid, s2) == hipSuccess ? BD_OK : BD_E_HIP;
+    };
+    // the persistent launches of the batched mode, one per kernel part
+    uint32_t grids[kKernelParts] = {};
+    for (int part = 0; part < kKernelParts; ++part) {
+        const uint32_t nch = b.part_begin[part + 1] - b.part_begin[part];
+        if (nch == 0) continue;
+        uint32_t grid = ex.grid_wgs > 0 ? (uint32_t)ex.grid_wgs : (uint32_t)resident_wgs(g, part, b.share, b.shape);
         grids[part] = std::min<uint32_t>(grid, nch);
     }
     auto launch_persistent = [&](hipStream_t s2) -> int {
-        for (int part = 0; part < 2; ++part) {
+        for (int part = 0; part < kKernelParts; ++part) {
             if (grids[part] == 0) continue;
             WalkArgs ab = a;
-            ab.chunks = static_cast<const Chunk*>(w.chunks) + parts[part];
-            ab.nchunks = parts[part + 1] - parts[part];
+            ab.chunks = static_cast<const Chunk*>(w.chunks) + b.part_begin[part];
+            ab.nchunks = b.part_begin[part + 1] - b.part_begin[part];
             ab.cursor = static_cast<uint32_t*>(w.cursor) + part * kMaxQueues;
             ab.persistent = 1;
             ab.nqueues = b.nqueues;
             for (uint32_t i = 0; i <= b.nqueues; ++i) ab.qoff[i] = b.qoff[part][i];
-            if (launch_walk(ab, layout, part == 0, b.share, grids[part], s2) != hipSuccess) return BD_E_HIP;
+            const int rc = launch_part(ab, part, b.shape, grids[part], s2);
+            if (rc != BD_OK) return rc;
         }
         return BD_OK;
     };
@@ -1031,24 +1297,24 @@ int run_batch(bd_graph* g, const Batch& b, const bd_exec& ex, hipStream_t user_s
             aq.chunks = static_cast<const Chunk*>(w.chunks) + c0;
             aq.nchunks = c1 - c0;
             aq.persistent = 0;
-            const int uniform = b.qd[q].R >= kUniformMinR;
-            status = timed([&] {
-                return launch_walk(aq, layout, uniform, b.share, c1 - c0, st) == hipSuccess ? BD_OK : BD_E_HIP;
-            });
+            status = timed([&] { return launch_part(aq, b.part[q], b.shapes[q], c1 - c0, st); });
         }
     } else if (!graph_mode) {
         status = zero_all(st);
         if (status == BD_OK) status = timed([&] { return launch_persistent(st); });
     } else {
         // key: everything the captured launches depend on
-        std::vector<uint64_t> key = {nv, b.chunks.size(), b.n_uniform, b.split_probes, gdim, grids[0],
-                                     grids[1], (uint64_t)layout, (uint64_t)b.share, b.nqueues,
+        std::vector<uint64_t> key = {nv, b.chunks.size(), b.split_probes, gdim, (uint64_t)b.shape, (uint64_t)b.share,
+                                     b.nqueues,
                                      (uint64_t)(uintptr_t)w.qd, (uint64_t)(uintptr_t)w.chunks,
                                      (uint64_t)(uintptr_t)w.bs, (uint64_t)(uintptr_t)w.psum,
                                      (uint64_t)(uintptr_t)w.pcount, (uint64_t)(uintptr_t)w.done,
                                      (uint64_t)(uintptr_t)w.beta, (uint64_t)(uintptr_t)w.cursor};
-        for (int part = 0; part < 2; ++part)
+        for (int part = 0; part < kKernelParts; ++part) {
+            key.push_back(b.part_begin[part + 1]);
+            key.push_back(grids[part]);
             for (uint32_t i = 0; i <= b.nqueues; ++i) key.push_back(b.qoff[part][i]);
+        }
         key.push_back((uint64_t)(uintptr_t)a.abort_flag);
         if (!ws.gexec || ws.gkey != key) {
             if (ws.gexec) {
@@ -1082,7 +1348,7 @@ int run_batch(bd_graph* g, const Batch& b, const bd_exec& ex, hipStream_t user_s
     beta.resize(nv);
     HIP_TRY(hipMemcpyAsync(beta.data(), w.beta, nv * 8, hipMemcpyDeviceToHost, st));
     if (q_dbg_host)
-        HIP_TRY(hipMemcpyAsync(q_dbg_host, w.qdbg, (size_t)b.qd[0].K * 8, hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipMemcpyAsync(q_dbg_host, w.qdbg, (size_t)b.qd[0].K() * 8, hipMemcpyDeviceToHost, st));
     if (y_dbg_host) HIP_TRY(hipMemcpyAsync(y_dbg_host, w.ydbg, gdim * 8, hipMemcpyDeviceToHost, st));
     std::vector<uint32_t> done_count;
     if (fired) {
@@ -1094,7 +1360,7 @@ int run_batch(bd_graph* g, const Batch& b, const bd_exec& ex, hipStream_t user_s
     if (watch) __atomic_store_n(g->ws.abort_host, 0u, __ATOMIC_SEQ_CST);
     if (incomplete) {
         incomplete->assign(nv, 0);
-        for (size_t q = 0; q < done_count.size(); ++q) (*incomplete)[q] = done_count[q] != b.qd[q].K;
+        for (size_t q = 0; q < done_count.size(); ++q) (*incomplete)[q] = done_count[q] != b.qd[q].K();
     }
     if (stats) {
         stats->walk_kernel_ms += kernel_ms;
@@ -1119,42 +1385,62 @@ void build_batch(const bd_graph* g, int64_t nq, const int32_t* s, const int32_t*
         d.t = (int32_t)storage_id(g, t[i]);
         d.L = L[i];
         d.uid = uid ? uid[i] : (uint32_t)i;
-        d.K = (uint32_t)r.K;
         d.R = (uint32_t)r.R;
         d.B = (uint32_t)r.B;
-        d.G = (uint32_t)r.G;
+        d.G = (uint16_t)r.G;
         d.slot = (uint32_t)b.qd.size();
         d.seed_lo = (uint32_t)seed;
         d.seed_hi = (uint32_t)(seed >> 32);
-        d.share = share;
+        d.share = (uint16_t)share;
+        set_positions(g, d);
         b.G = std::max<uint32_t>(b.G, d.G);
         b.index.push_back(i);
         b.qd.push_back(d);
     }
     // chunk table: grouped by query; batched launches order queries by
     // descending cost so the longest work starts first
-    auto cost = [&](size_t q) { return (double)b.qd[q].K * b.qd[q].R * (double)b.qd[q].L; };
-    int64_t umin = ex.uniform_min_r == 0 ? (int64_t)kUniformMinR
-                   : ex.uniform_min_r < 0 ? INT64_MAX : (int64_t)ex.uniform_min_r;
-    if (ex.mode != BD_MODE_PLAIN && ex.uniform_min_r == 0) {
-        // automatic: the wave-uniform kernel gets a launch of its own only when
-        // its chunks can fill the device; otherwise the general kernel runs every
-        // chunk
-        uint64_t nu = 0;
-        for (const QueryDesc& d : b.qd) {
-            if ((int64_t)d.R < umin) continue;
-            const ChunkPlan cp = chunk_plan(ex, d, g->kernel_layout);
-            const uint32_t ng = Groups(d).n;
-            nu += cp.part ? (uint64_t)ng * ((d.R + cp.part - 1) / cp.part) : (ng + cp.gc - 1) / cp.gc;
-        }
-        if (nu < (uint64_t)resident_wgs(g, 1, b.share)) umin = INT64_MAX;
+    auto cost = [&](size_t q) { return (double)b.qd[q].K() * b.qd[q].R * (double)b.qd[q].L; };
+    const int64_t umin = ex.mode == BD_MODE_PLAIN || ex.uniform_min_r == 0 ? (int64_t)kUniformMinR
+                         : ex.uniform_min_r < 0 ? INT64_MAX : (int64_t)ex.uniform_min_r;
+    b.part.resize(b.qd.size());
+    ShapeVote vote;
+    std::vector<uint32_t> lanes(b.qd.size());
+    uint64_t uniform_chunks[2] = {0, 0};   // of the sign-table and the general kernels
+    bool others[2] = {false, false};       // queries below umin
+    for (size_t q = 0; q < b.qd.size(); ++q) {
+        const QueryDesc& d = b.qd[q];
+        b.shapes.push_back(query_shape(g, d));
+        const bool signs = b.shapes[q] >= 0;
+        if (signs) vote.add(b.shapes[q], cost(q));
+        lanes[q] = query_lanes(g, d, signs);
+        const bool uniform = (int64_t)d.R >= umin;
+        b.part[q] = (uint8_t)(signs ? (uniform ? kSignUniform : kSignAny) : (uniform ? kWalkUniform : kWalkAny));
+        if (!uniform) others[signs ? 0 : 1] = true;
     }
-    auto uniform = [&](size_t q) { return ex.mode != BD_MODE_PLAIN && (int64_t)b.qd[q].R >= umin; };
+    b.shape = vote.best();
+    for (size_t q = 0; q < b.qd.size(); ++q) {
+        if (b.part[q] != kSignUniform && b.part[q] != kWalkUniform) continue;
+        const ChunkPlan cp = chunk_plan(ex, b.qd[q], lanes[q]);
+        const uint32_t ng = Groups(b.qd[q]).n;
+        uniform_chunks[sign_part(b.part[q]) ? 0 : 1] +=
+            cp.part ? (uint64_t)ng * ((b.qd[q].R + cp.part - 1) / cp.part) : (ng + cp.gc - 1) / cp.gc;
+    }
+    if (ex.mode != BD_MODE_PLAIN && ex.uniform_min_r == 0) {
+        // automatic: beside queries of fewer replicas, the wave-uniform kernel
+        // gets a launch of its own only when its chunks can fill the device;
+        // otherwise the kernel that runs any query takes them all
+        for (const int part : {kSignUniform, kWalkUniform}) {
+            const int i = part == kSignUniform ? 0 : 1;
+            if (!others[i] || uniform_chunks[i] >= (uint64_t)resident_wgs(g, part, b.share, b.shape)) continue;
+            for (uint8_t& p : b.part)
+                if (p == part) p = (uint8_t)(part + 1);
+        }
+    }
     std::vector<size_t> order(b.qd.size());
     for (size_t i = 0; i < order.size(); ++i) order[i] = i;
     if (ex.mode != BD_MODE_PLAIN) {
         std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) {
-            if (uniform(x) != uniform(y)) return uniform(x);
+            if (b.part[x] != b.part[y]) return b.part[x] < b.part[y];
             return cost(x) > cost(y);
         });
     }
@@ -1162,22 +1448,25 @@ void build_batch(const bd_graph* g, int64_t nq, const int32_t* s, const int32_t*
     b.chunk_begin.assign(b.qd.size(), 0);
     auto emit = [&](size_t q) {
         QueryDesc& d = b.qd[q];
-        ChunkCursor cur((uint32_t)q, d, ex, g->kernel_layout, ex.mode == BD_MODE_PLAIN ? g->cus : 0u);
+        ChunkCursor cur((uint32_t)q, d, ex, lanes[q], ex.mode == BD_MODE_PLAIN ? g->cus : 0u);
         if (cur.plan.part) {
             d.psum_base = b.split_probes;
-            b.split_probes += d.K;
+            b.split_probes += d.K();
         }
         b.chunk_begin[q] = (uint32_t)b.chunks.size();
         while (!cur.done()) b.chunks.push_back(cur.next());
     };
-    // each part (wave-uniform queries, then the rest) is dealt into nqueues
-    // queues by longest-processing-time-first on the walk steps, so the queues
-    // carry about equal work; a query's chunks stay together in one queue
-    const size_t split = (size_t)(std::find_if(order.begin(), order.end(), [&](size_t q) { return !uniform(q); }) -
-                                  order.begin());
-    for (int part = 0; part < 2; ++part) {
-        const size_t o0 = part == 0 ? 0 : split, o1 = part == 0 ? split : order.size();
+    // each part is dealt into nqueues queues by longest-processing-time-first on
+    // the walk steps, so the queues carry about equal work; a query's chunks
+    // stay together in one queue. Plain launches take a query at a time.
+    size_t o0 = 0;
+    for (int part = 0; part < kKernelParts; ++part) {
         const uint32_t base = (uint32_t)b.chunks.size();
+        b.part_begin[part] = base;
+        size_t o1 = o0;
+        if (ex.mode == BD_MODE_PLAIN) o1 = order.size();
+        else
+            while (o1 < order.size() && b.part[order[o1]] == part) ++o1;
         std::vector<std::vector<size_t>> bins(b.nqueues);
         std::vector<double> load(b.nqueues, 0.0);
         for (size_t oi = o0; oi < o1; ++oi) {
@@ -1191,8 +1480,9 @@ void build_batch(const bd_graph* g, int64_t nq, const int32_t* s, const int32_t*
             for (size_t q : bins[i]) emit(q);
         }
         b.qoff[part][b.nqueues] = (uint32_t)b.chunks.size() - base;
-        if (part == 0) b.n_uniform = (uint32_t)b.chunks.size();
+        o0 = o1;
     }
+    b.part_begin[kKernelParts] = (uint32_t)b.chunks.size();
 }
 
 }  // namespace
@@ -1615,7 +1905,7 @@ extern "C" int bd_gather_roofline(bd_graph* g, int32_t chains_per_lane, int32_t 
         (chains_per_lane != 1 && chains_per_lane != 2 && chains_per_lane != 4 && chains_per_lane != 8))
         return BD_E_INVALID;
     hipStream_t st = (hipStream_t)stream;
-    uint32_t grid = work_groups > 0 ? (uint32_t)work_groups : 4u * (uint32_t)resident_wgs(g, 1, 1);
+    uint32_t grid = work_groups > 0 ? (uint32_t)work_groups : 4u * (uint32_t)resident_wgs(g, kWalkUniform, 1, 0);
     DevBuf sink;
     const int wg = block_threads(g->kernel_layout, 1);
     int rc = sink.alloc((size_t)grid * wg * 4);
@@ -1752,7 +2042,9 @@ struct SlotState {
     ChunkCursor cur;           // next chunk of this query
     uint32_t L = 0;
     uint64_t steps = 0;        // walk steps of the query
-    bool uniform = false;      // R >= kUniformMinR
+    uint8_t part = kWalkAny;   // kernel part of its chunks
+    uint32_t lanes = 0;        // pairs its chunks are sized by
+    int shape = -1;            // the sign-table kernels' shape for it
     uint32_t psum_base = 0, psum_n = 0;  // accumulator range of a query with split probes
 };
 
@@ -1811,7 +2103,8 @@ struct Slice {
     hipStream_t st = nullptr;
     hipEvent_t ev = nullptr;
     uint32_t n = 0;
-    uint32_t n_uniform = 0;  // chunks [0, n_uniform) have R >= kUniformMinR
+    uint32_t part_begin[kKernelParts + 1] = {};  // chunks of each kernel part
+    int shape = 0;                               // of its sign-table launches
     bool inflight = false;
     uint64_t steps = 0;
     double t_launch = 0;
@@ -1829,7 +2122,7 @@ struct bd_server {
     hipEvent_t ev_admit = nullptr;
     bool admit_recorded = false;
     uint32_t slots = 0, gdim = 0;
-    int resident[2] = {0, 0};  // resident work groups: [0] small-R kernel, [1] wave-uniform kernel
+    int resident[2] = {0, 0};  // resident work groups of the general kernels: [0] any replicas, [1] wave-uniform
     DevBuf d_qd, d_bs, d_done, d_beta, d_psum, d_pcount;
     PinnedBuf h_qd;
     uint32_t arena = 0;  // per-probe accumulators for split probes
@@ -1874,13 +2167,20 @@ namespace {
 // waits on a loaded memory system (several microseconds on the fat layout),
 // so a chunk of several passes would hold its slice, and every request that
 // arrives meanwhile, open for tens of milliseconds.
-bd_exec server_exec(const bd_server* S)
+bd_exec server_exec(const bd_server* S, uint32_t lanes)
 {
     bd_exec ex{};
     ex.mode = BD_MODE_BATCHED;
     ex.chunk_probes = S->cfg.chunk_probes;
-    ex.chunk_pairs = group_pairs(S->g->kernel_layout, share_class(policy_share(S->pol)));
+    ex.chunk_pairs = (int32_t)lanes;
     return ex;
+}
+
+// Whether the query's replicas are split over chunks (it then needs accumulators).
+bool server_splits(const bd_server* S, const QueryDesc& d)
+{
+    const uint32_t lanes = query_lanes(S->g, d, query_shape(S->g, d) >= 0);
+    return chunk_plan(server_exec(S, lanes), d, lanes).part != 0;
 }
 
 size_t comp_bytes(const bd_server* S)
@@ -1916,14 +2216,13 @@ int admit(bd_server* S)
         const uint64_t cap = S->cfg.max_steps_inflight;
         if (cap && S->inflight_steps > 0 && S->inflight_steps + r.steps > cap) break;
         // memory admission: accumulators of split probes, all or nothing
-        const bd_exec ex = server_exec(S);
         std::vector<uint32_t> base(need, 0);
         bool fits = true;
         for (size_t i = 0; i < need && fits; ++i) {
             const QueryDesc& d = r.desc[i];
-            if (chunk_plan(ex, d, S->g->kernel_layout).part && !S->psum_alloc.alloc(d.K, &base[i])) {
+            if (server_splits(S, d) && !S->psum_alloc.alloc(d.K(), &base[i])) {
                 for (size_t j = 0; j < i; ++j)
-                    if (chunk_plan(ex, r.desc[j], S->g->kernel_layout).part) S->psum_alloc.release(base[j], r.desc[j].K);
+                    if (server_splits(S, r.desc[j])) S->psum_alloc.release(base[j], r.desc[j].K());
                 fits = false;
             }
         }
@@ -1949,12 +2248,15 @@ int admit(bd_server* S)
             ss.req = id;
             r.slots.push_back(sl);
             ss.ridx = r.index[i];
-            ss.cur = ChunkCursor(sl, d, ex, S->g->kernel_layout);
+            ss.shape = query_shape(S->g, d);
+            const bool signs = ss.shape >= 0;
+            ss.lanes = query_lanes(S->g, d, signs);
+            ss.cur = ChunkCursor(sl, d, server_exec(S, ss.lanes), ss.lanes);
             ss.L = (uint32_t)d.L;
             ss.steps = (uint64_t)r.res[(size_t)ss.ridx].walk_steps;
-            ss.uniform = d.R >= kUniformMinR;
+            ss.part = d.R >= kUniformMinR ? (signs ? kSignUniform : kWalkUniform) : (signs ? kSignAny : kWalkAny);
             ss.psum_base = base[i];
-            ss.psum_n = ss.cur.plan.part ? d.K : 0;
+            ss.psum_n = ss.cur.plan.part ? d.K() : 0;
             S->inflight_steps += ss.steps;
             r.rr_slots.push_back(sl);
         }
@@ -2078,9 +2380,10 @@ void fill_slice(bd_server* S, Slice& sl)
         double cost;
         Chunk c;
     };
-    std::vector<Item> big, small;  // wave-uniform chunks, then the rest
-    const uint64_t wg = (uint64_t)group_pairs(S->g->kernel_layout, share_class(policy_share(S->pol)));
-    auto room = [&] { return big.size() + small.size() < kSliceMaxChunks; };
+    std::vector<Item> items[kKernelParts];
+    size_t taken = 0;
+    ShapeVote vote;
+    auto room = [&] { return taken < kSliceMaxChunks; };
     // one chunk of request r (its next query in turn); false when it has none left
     auto take = [&](Request& r) {
         if (r.rr_slots.empty()) return false;
@@ -2091,13 +2394,15 @@ void fill_slice(bd_server* S, Slice& sl)
         sl.steps += cs;
         r.left_steps -= std::min(r.left_steps, cs);
         const Chunk c = ss.cur.next();
-        const double cost = ((double)ss.L + 1.0) * (double)(((uint64_t)c.gc * c.pc + wg - 1) / wg);
+        const double cost = ((double)ss.L + 1.0) * (double)(((uint64_t)c.gc * c.pc + ss.lanes - 1) / ss.lanes);
         sl.sum_cost += cost;
         if (cost > sl.max_cost) {
             sl.max_cost = cost;
             target = std::max(target, 4.0 * cost * S->ms_per_lane_step * S->steps_per_ms);
         }
-        (ss.uniform ? big : small).push_back(Item{cost, c});
+        if (ss.shape >= 0) vote.add(ss.shape, (double)cs);
+        items[ss.part].push_back(Item{cost, c});
+        ++taken;
         if (!ss.cur.done()) r.rr_slots.push_back(q);
         return true;
     };
@@ -2122,7 +2427,7 @@ void fill_slice(bd_server* S, Slice& sl)
         }
     }
     while (!S->rr.empty() && room() &&
-           ((double)sl.steps < target || big.size() + small.size() < (size_t)S->resident[1])) {
+           ((double)sl.steps < target || taken < (size_t)S->resident[1])) {
         const uint64_t id = S->rr.front();
         S->rr.pop_front();
         Request& r = S->reqs[id];
@@ -2134,16 +2439,25 @@ void fill_slice(bd_server* S, Slice& sl)
         if (!r.rr_slots.empty()) S->rr.push_back(id);
         else r.in_rr = false;
     }
-    auto longest_first = [](const Item& a, const Item& b) { return a.cost > b.cost; };
-    std::stable_sort(big.begin(), big.end(), longest_first);
-    std::stable_sort(small.begin(), small.end(), longest_first);
-    for (const Item& it : big) out[sl.n++] = it.c;
-    // The wave-uniform chunks get a launch of their own only when they can fill
-    // the device; otherwise the general kernel (which runs any chunk) takes them
-    // at the head of its table, so the slice is one launch and no part of it
-    // waits for a nearly empty one.
-    sl.n_uniform = sl.n >= (uint32_t)S->resident[1] ? sl.n : 0u;
-    for (const Item& it : small) out[sl.n++] = it.c;
+    // Of each family, the wave-uniform chunks get a launch of their own only when
+    // they can fill the device or there are no others; otherwise the kernel that
+    // runs any chunk takes them at the head of its table, so the slice is one
+    // launch and no part of it waits for a nearly empty one.
+    sl.shape = vote.best();
+    const int share = share_class(policy_share(S->pol));
+    for (const int part : {kSignUniform, kWalkUniform}) {
+        std::vector<Item>&u = items[part], &any = items[part + 1];
+        if (any.empty() || u.empty() || u.size() >= (size_t)resident_wgs(S->g, part, share, sl.shape)) continue;
+        any.insert(any.begin(), u.begin(), u.end());
+        u.clear();
+    }
+    for (int part = 0; part < kKernelParts; ++part) {
+        std::stable_sort(items[part].begin(), items[part].end(),
+                         [](const Item& a, const Item& b) { return a.cost > b.cost; });
+        sl.part_begin[part] = sl.n;
+        for (const Item& it : items[part]) out[sl.n++] = it.c;
+    }
+    sl.part_begin[kKernelParts] = sl.n;
 }
 
 int launch_slice(bd_server* S, Slice& sl)
@@ -2173,20 +2487,19 @@ int launch_slice(bd_server* S, Slice& sl)
     a.comp_cap = S->slots;
     a.recycle = 1;
     a.persistent = 1;
-    const uint32_t parts[3] = {0u, sl.n_uniform, sl.n};
-    for (int part = 0; part < 2; ++part) {
+    const int share = share_class(policy_share(S->pol));
+    for (int part = 0; part < kKernelParts; ++part) {
         WalkArgs ap = a;
-        ap.chunks = sl.chunks_d.as<const Chunk>() + parts[part];
-        ap.nchunks = parts[part + 1] - parts[part];
+        ap.chunks = sl.chunks_d.as<const Chunk>() + sl.part_begin[part];
+        ap.nchunks = sl.part_begin[part + 1] - sl.part_begin[part];
         ap.cursor = sl.d_cursor.as<uint32_t>() + part;
         ap.nqueues = 1;
         ap.qoff[0] = 0;
         ap.qoff[1] = ap.nchunks;
-        const uint32_t grid = std::min<uint32_t>((uint32_t)S->resident[part == 0], ap.nchunks);
-        if (grid && launch_walk(ap, run_kernel(S->g, share_class(policy_share(S->pol))), part == 0,
-                                share_class(policy_share(S->pol)), grid, st) !=
-                        hipSuccess)
-            return BD_E_HIP;
+        if (ap.nchunks == 0) continue;
+        const uint32_t grid = std::min<uint32_t>((uint32_t)resident_wgs(S->g, part, share, sl.shape), ap.nchunks);
+        const hipError_t e = launch_kernel(S->g, ap, part, share, sl.shape, grid, st);
+        if (e != hipSuccess) return BD_E_HIP;
     }
     if (hipMemcpyAsync(sl.comp_h.p, sl.d_comp.p, comp_prefix_bytes(S), hipMemcpyDeviceToHost, st) != hipSuccess)
         return BD_E_HIP;
@@ -2302,8 +2615,8 @@ extern "C" int bd_server_create(bd_graph* g, const bd_server_cfg* cfg, bd_server
         delete S;
         return BD_E_BUDGET;
     }
-    S->resident[0] = resident_wgs(g, 0, share_class(policy_share(S->pol)));
-    S->resident[1] = resident_wgs(g, 1, share_class(policy_share(S->pol)));
+    S->resident[0] = resident_wgs(g, kWalkAny, share_class(policy_share(S->pol)), 0);
+    S->resident[1] = resident_wgs(g, kWalkUniform, share_class(policy_share(S->pol)), 0);
     int rc = S->d_qd.alloc((size_t)S->slots * sizeof(QueryDesc));
     if (rc == BD_OK) rc = S->d_bs.alloc((size_t)S->slots * S->gdim * 16);
     if (rc == BD_OK) rc = S->d_done.alloc((size_t)S->slots * 4);
@@ -2366,18 +2679,17 @@ extern "C" int bd_server_submit(bd_server* S, int64_t nq, const int32_t* s, cons
         d.t = (int32_t)storage_id(S->g, t[i]);
         d.L = L[i];
         d.uid = uid ? uid[i] : (uint32_t)i;
-        d.K = (uint32_t)pr.K;
         d.R = (uint32_t)pr.R;
         d.B = (uint32_t)pr.B;
-        d.G = (uint32_t)pr.G;
+        d.G = (uint16_t)pr.G;
         d.seed_lo = (uint32_t)seed;
         d.seed_hi = (uint32_t)(seed >> 32);
-        d.share = policy_share(S->pol);
+        d.share = (uint16_t)policy_share(S->pol);
+        set_positions(S->g, d);
         r.desc.push_back(d);
         r.index.push_back(i);
         r.steps += (uint64_t)pr.walk_steps;
-        const bd_exec ex = server_exec(S);
-        if (chunk_plan(ex, d, S->g->kernel_layout).part) r.split_probes += d.K;
+        if (server_splits(S, d)) r.split_probes += d.K();
     }
     r.remaining = (int64_t)r.desc.size();
     if (r.desc.size() > S->slots || r.split_probes > S->arena) return BD_E_FULL;

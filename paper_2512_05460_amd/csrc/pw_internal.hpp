@@ -13,13 +13,16 @@ namespace pw {
 // One query as the device sees it (Algorithm 1 inputs and parameters).
 struct QueryDesc {
     int32_t s, t;       // internal (storage) ids of the endpoints
+    uint32_t ss, st;    // the endpoints in the sign-table kernels' tables (pw_signs.hip)
     int32_t L;
     uint32_t uid;
-    uint32_t K, R, B, G;
+    uint32_t R, B;
+    uint16_t G;
+    uint16_t share;     // walk-sharing group size M (1 = every probe has its own walks)
     uint32_t slot;      // row of the block-sum / done / result tables
     uint32_t seed_lo, seed_hi;  // 64-bit Philox key of this query
     uint32_t psum_base; // first per-probe accumulator of a query whose probes are split
-    uint32_t share;     // walk-sharing group size M (1 = every probe has its own walks)
+    __host__ __device__ uint32_t K() const { return B * G; }  // probes
 };
 
 // A work-group chunk: replicas [p0, p0 + pc) of the walk-sharing groups
@@ -55,6 +58,37 @@ struct GraphTables {
     uint32_t run_shift;                    // log2 of the storage ids per run record
     DomainParams dom;
 };
+
+// Tables of the sign-table kernels (pw_signs.hip). With the adjacency in LDS
+// nodes go by the ids their probes are evaluated on; else they are in descending
+// degree, every run of equal degree padded to whole blocks of 2^shift positions.
+struct SignTables {
+    const uint4* blk;     // per block {base, d, bits of 1.0f/d, 0}: row offset of position x = base + x d;
+                          // or row offset | degree << 16 of every node, then the adjacency as 2-byte 4 x id
+    const uint32_t* ids;  // adjacency as positions, 3 bytes each (not in LDS)
+    const uint32_t* pid;  // of each table word with nodes, the ids that its 16 positions' probe values are
+                          // evaluated on (0 in the padding), 64 words by 4 ids at a time; then the words'
+                          // indices (not in LDS)
+    uint32_t words;       // such words
+    uint32_t np;          // positions
+    uint32_t nblk, shift; // blocks; words of rows (a multiple of 4) with the adjacency in LDS
+    uint32_t idw;         // words of the adjacency in LDS (a multiple of 4)
+    uint32_t tabw;        // words of one sign table: 16 positions a word, or 1 with the adjacency in LDS
+    uint32_t T;           // sign tables a work group holds
+};
+
+// A launch shape of the sign-table kernels for a graph and sharing class: one
+// to four work groups per CU.
+struct SignShape {
+    int lds = 0;           // 1: the adjacency is staged in LDS
+    uint32_t threads = 0;  // per work group; 0: the tables do not fit
+    uint32_t per_cu = 0;   // work groups a CU holds at once
+    uint32_t bytes = 0;    // dynamic LDS
+    uint32_t T = 0;        // sign tables
+};
+constexpr int kSignShapes = 4;
+// Dynamic LDS a work group can ask for: the CU's 160 KB less the kernels' static part.
+constexpr uint32_t kSignLdsMost = 160u * 1024u - 1280u;
 
 // A finished query as posted by the work group that completed it.
 struct Completion {
@@ -93,6 +127,7 @@ struct WalkArgs {
     // the host sets it): a work group reads it before each chunk and, once it
     // is nonzero, takes no further chunk.
     const uint32_t* abort_flag;
+    SignTables signs;               // sign-table kernels only
 };
 
 // Largest walk-sharing group the kernels are built for.
@@ -198,6 +233,7 @@ constexpr uint32_t kSplitReplicas = 4096;
 // uniform: every chunk of the launch has R >= kUniformMinR.
 // layout: 0 CSR, 1 fat, 2 compact.
 hipError_t launch_walk(const WalkArgs& a, int layout, int uniform, int share, uint32_t grid, hipStream_t st);
+hipError_t launch_signs(const WalkArgs& a, const SignShape& sh, int uniform, int share, uint32_t grid, hipStream_t st);
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t st);
 hipError_t launch_trace(const GraphTables& g, int layout, uint32_t count, const int32_t* start,
                         const uint32_t* uid, const uint32_t* k, const uint32_t* p,
@@ -227,6 +263,7 @@ hipError_t launch_lambda(const uint32_t* rp, const uint32_t* col, const uint32_t
                          double* scal, hipStream_t st);
 // Work groups of the walk kernel that fit on the device at once.
 int walk_occupancy(int layout, int uniform, int share, int* wgs_per_cu);
+int signs_occupancy(const SignShape& sh, int uniform, int share, int* wgs_per_cu);
 
 // Bytes of the fixed device scratch array (pw_scratch.hip).
 constexpr size_t kScratchBytes = size_t(64) << 20;

@@ -1,0 +1,74 @@
+// Node order and block table of the sign-table kernels (host side, no HIP;
+// the kernels that read them are in pw_signs.hip).
+#pragma once
+
+#include <stddef.h>
+#include <stdint.h>
+#include <string.h>
+
+#include <vector>
+
+namespace pw {
+
+constexpr uint32_t kSignShiftMin = 4, kSignShiftMax = 9;
+
+// Nodes are given in descending degree (row offsets rp[0..n]). Every run of
+// equal degree starts a new block of 2^shift positions, so that a block has one
+// degree; positions past a run's end are padding.
+struct SignOrder {
+    uint32_t shift = 0;
+    uint32_t np = 0;             // positions, a multiple of 16
+    uint32_t nblk = 0;           // blocks
+    std::vector<uint32_t> run;   // first storage id of each run, then n
+};
+
+// The block size for which the block table (16 bytes a block) and two sign
+// tables (2 bits a position each) take least; false beyond 2^24 positions,
+// which the 24-bit products of the kernels could not hold.
+inline bool plan_sign_order(const std::vector<uint32_t>& rp, SignOrder* o)
+{
+    const size_t n = rp.size() - 1;
+    o->run.clear();
+    for (size_t i = 0; i < n; ++i)
+        if (i == 0 || rp[i + 1] - rp[i] != rp[i] - rp[i - 1]) o->run.push_back((uint32_t)i);
+    o->run.push_back((uint32_t)n);
+    uint64_t best = ~uint64_t(0);
+    for (uint32_t s = kSignShiftMin; s <= kSignShiftMax; ++s) {
+        uint64_t blocks = 0;
+        for (size_t r = 0; r + 1 < o->run.size(); ++r)
+            blocks += ((uint64_t)(o->run[r + 1] - o->run[r]) + (1u << s) - 1) >> s;
+        const uint64_t np = blocks << s, bytes = 16 * blocks + np / 2;
+        if (np <= (1u << 24) && bytes < best) {
+            best = bytes;
+            o->shift = s;
+            o->np = (uint32_t)np;
+            o->nblk = (uint32_t)blocks;
+        }
+    }
+    return best != ~uint64_t(0);
+}
+
+// pos[storage id] and the block entries {base, d, bits of 1.0f/d, 0}: position
+// x of a block has row offset base + x d (32-bit arithmetic, base may wrap).
+inline void build_sign_order(const std::vector<uint32_t>& rp, const SignOrder& o, std::vector<uint32_t>* pos,
+                             std::vector<uint32_t>* blk)
+{
+    pos->resize(rp.size() - 1);
+    blk->assign((size_t)o.nblk * 4, 0u);
+    uint32_t at = 0;  // next block
+    for (size_t r = 0; r + 1 < o.run.size(); ++r) {
+        const uint32_t f = o.run[r], e = o.run[r + 1], d = rp[f + 1] - rp[f], x0 = at << o.shift;
+        for (uint32_t i = f; i < e; ++i) (*pos)[i] = x0 + (i - f);
+        const float inv = 1.0f / (float)d;
+        const uint32_t nb = (e - f + (1u << o.shift) - 1) >> o.shift, base = rp[f] - x0 * d;
+        for (uint32_t b = 0; b < nb; ++b) {
+            uint32_t* w = blk->data() + 4 * (size_t)(at + b);
+            w[0] = base;
+            w[1] = d;
+            memcpy(w + 2, &inv, 4);
+        }
+        at += nb;
+    }
+}
+
+}  // namespace pw
