@@ -166,6 +166,8 @@ struct bd_graph {
     uint32_t run_h1 = 0, run_words = 0, run_ninv = 0;  // code 8: direct row offsets, words of runtab, d_max + 1
     uint32_t run_shift = 0;                            // code 8: log2 of the storage ids per record
     bool runs_shared = false;                          // code 8: the table fits the walk-sharing kernels
+    DevBuf hubs;                                       // storage ids of the rows above kHubDegree
+    uint32_t nhubs = 0;
     DevBuf sblk, sids, slds, spid;                     // tables of the sign-table kernels (none: empty)
     SignTables signs{}, signs_lds{};                   // the two forms' arguments
     SignShape sign_shape[3][kSignShapes];              // launch shapes for 1, 2 and 4 probes per walk
@@ -731,6 +733,23 @@ extern "C" int graph_load_csr(int64_t n, const int64_t* row_ptr, const int32_t* 
             g->runs_shared = ((runtab.size() + 3) & ~(size_t)3) + g->run_ninv <= kRunWordsShared;
         }
     }
+    {
+        std::vector<uint32_t> hubs;
+        for (size_t i = 0; i < (size_t)n; ++i)
+            if (nodetab[4 * i + 1] > kHubDegree) hubs.push_back((uint32_t)i);
+        g->nhubs = (uint32_t)hubs.size();
+        const int hrc = g->hubs.alloc(hubs.size() * 4);
+        if (hrc != BD_OK) {
+            delete g;
+            return hrc;
+        }
+        if (!hubs.empty() && (hipMemcpyAsync(g->hubs.p, hubs.data(), hubs.size() * 4, hipMemcpyHostToDevice, st) !=
+                                  hipSuccess ||
+                              hipStreamSynchronize(st) != hipSuccess)) {
+            delete g;
+            return BD_E_HIP;
+        }
+    }
     if (!(flags & (BD_NARROW_HUBS | BD_DIRECT_HUBS | BD_WIDE_HUBS))) {
         const int src = load_sign_tables(g, order, row_ptr, col_idx, st);
         if (src != BD_OK) {
@@ -745,7 +764,7 @@ extern "C" int graph_load_csr(int64_t n, const int64_t* row_ptr, const int32_t* 
     }
     g->device_bytes = (int64_t)(g->node.bytes + g->col.bytes + g->adj.bytes + g->rp32.bytes + g->col24.bytes +
                                 g->node8.bytes + g->runtab.bytes + g->sblk.bytes + g->sids.bytes + g->slds.bytes +
-                                g->spid.bytes);
+                                g->spid.bytes + g->hubs.bytes);
     *out = g;
     return BD_OK;
 }
@@ -1645,6 +1664,20 @@ extern "C" int bd_query_probes(bd_graph* g, int32_t s, int32_t t, double eps, in
 // Truncated series in binary64 and the spectral quantities of Lemma 2.3 /
 // Theorem 3.8
 // ---------------------------------------------------------------------------
+namespace {
+
+// The adjacency in storage order, as 4-byte or as packed 3-byte ids (the other is null).
+const uint32_t* packed_ids(const bd_graph* g)
+{
+    return g->layout == 2 || g->layout == 3 || g->layout == 5 ? g->col24.as<const uint32_t>() : nullptr;
+}
+const uint32_t* plain_ids(const bd_graph* g)
+{
+    return packed_ids(g) ? nullptr : g->col.as<const uint32_t>();
+}
+
+}  // namespace
+
 extern "C" int bd_truncated_beta(bd_graph* g, int64_t nq, const int32_t* s, const int32_t* t, int32_t L,
                                  void* stream, double* beta_L)
 {
@@ -1655,48 +1688,60 @@ extern "C" int bd_truncated_beta(bd_graph* g, int64_t nq, const int32_t* s, cons
     std::lock_guard<std::mutex> lock(g->mu);
     hipStream_t st = (hipStream_t)stream;
     const uint32_t n = (uint32_t)g->n;
-    const uint32_t* rp = g->rp32.as<const uint32_t>();
-    const bool packed_ids = g->layout == 2 || g->layout == 3 || g->layout == 5;
-    const uint32_t* col = packed_ids ? nullptr : g->col.as<const uint32_t>();
-    const uint32_t* col24 = packed_ids ? g->col24.as<const uint32_t>() : nullptr;
-    // queries per pass: three n x Q binary64 blocks within half the free device memory
+    auto inverse_degree = [&](int32_t v) { return 1.0 / (double)g->deg[(size_t)v]; };
+    const SignTables& lt = g->signs_lds;
+    if (lt.tabw && n <= kSeriesSmallNodes && series_small_bytes(lt.nblk, lt.idw, n) <= kSignLdsMost) {
+        // a small graph: one launch, a work group per pair
+        for (int64_t q0 = 0; q0 < nq; q0 += 65536) {
+            const size_t Q = (size_t)std::min<int64_t>(65536, nq - q0);
+            std::vector<SeriesPair> pairs(Q);
+            for (size_t q = 0; q < Q; ++q) {
+                const int32_t a = s[q0 + (int64_t)q], b = t[q0 + (int64_t)q];
+                pairs[q] = SeriesPair{g->sid4[storage_id(g, a)] / 4u, g->sid4[storage_id(g, b)] / 4u, inverse_degree(a),
+                                      -inverse_degree(b)};
+            }
+            int rc = g->ws.ensure(g->ws.qd, Q * sizeof(SeriesPair));
+            if (rc == BD_OK) rc = g->ws.ensure(g->ws.beta, Q * 8);
+            if (rc != BD_OK) return rc;
+            HIP_TRY(hipMemcpyAsync(g->ws.qd.p, pairs.data(), Q * sizeof(SeriesPair), hipMemcpyHostToDevice, st));
+            HIP_TRY(launch_series_small(lt.blk, lt.nblk, lt.idw, n, (uint32_t)Q, L, g->ws.qd.as<const SeriesPair>(),
+                                        g->ws.beta.as<double>(), st));
+            HIP_TRY(hipMemcpyAsync(beta_L + q0, g->ws.beta.p, Q * 8, hipMemcpyDeviceToHost, st));
+            HIP_TRY(hipStreamSynchronize(st));
+        }
+        return BD_OK;
+    }
+    // queries per pass: two n x Q binary64 matrices within half the free device
+    // memory (whole slabs of columns)
     size_t free_b = 0, total_b = 0;
     HIP_TRY(hipMemGetInfo(&free_b, &total_b));
-    const size_t per_q = (size_t)n * 8 * 3;
-    const uint32_t Qmax = (uint32_t)std::max<size_t>(1, std::min<size_t>({64, (size_t)nq, free_b / 2 / per_q}));
-    DevBuf dv, dy, dh, dsq, dlin;
-    int rc = dv.alloc((size_t)n * Qmax * 8);
-    if (rc == BD_OK) rc = dy.alloc((size_t)n * Qmax * 8);
-    if (rc == BD_OK) rc = dh.alloc((size_t)n * Qmax * 8);
-    if (rc == BD_OK) rc = dsq.alloc(Qmax * 8);
-    if (rc == BD_OK) rc = dlin.alloc(Qmax * 8);
+    uint32_t Qmax = (uint32_t)std::min<int64_t>(64, nq);
+    auto matrix = [&](uint32_t Q) { return (size_t)n * series_columns(Q) * series_slabs(Q) * 8; };
+    while (Qmax > 1 && 2 * matrix(Qmax) > free_b / 2) Qmax = Qmax > 16 ? (Qmax - 1) / 16 * 16 : Qmax / 2;
+    DevBuf dh, dy, dpart, dbeta;
+    int rc = dh.alloc(matrix(Qmax));
+    if (rc == BD_OK) rc = dy.alloc(matrix(Qmax));
+    if (rc == BD_OK) rc = dpart.alloc((size_t)kSeriesParts * 2 * 8 * series_columns(Qmax) * series_slabs(Qmax));
+    if (rc == BD_OK) rc = dbeta.alloc(64 * 8);
     if (rc != BD_OK) return rc;
     for (int64_t q0 = 0; q0 < nq; q0 += Qmax) {
         const uint32_t Q = (uint32_t)std::min<int64_t>(Qmax, nq - q0);
-        const size_t bytes = (size_t)n * Q * 8;
         // v_0 = D^{-1} b_st in storage ids
-        uint32_t ss[64], tt[64];
-        double vs[64], vt[64];
-        for (uint32_t q = 0; q < Q; ++q) {
+        SeriesSeeds seeds{};
+        for (uint32_t q = 0; q < 64; ++q) {
+            seeds.s[q] = seeds.t[q] = n;
+            if (q >= Q) continue;
             const int32_t a = s[q0 + q], b = t[q0 + q];
-            ss[q] = storage_id(g, a);
-            tt[q] = storage_id(g, b);
-            vs[q] = 1.0 / (double)g->deg[(size_t)a];
-            vt[q] = -1.0 / (double)g->deg[(size_t)b];
+            seeds.s[q] = storage_id(g, a);
+            seeds.t[q] = storage_id(g, b);
+            seeds.vs[q] = inverse_degree(a);
+            seeds.vt[q] = -inverse_degree(b);
         }
-        HIP_TRY(launch_zero(dv.p, bytes, st));
-        HIP_TRY(launch_zero(dh.p, bytes, st));
-        HIP_TRY(launch_series_seed(ss, tt, vs, vt, Q, dv.as<double>(), dh.as<double>(), st));
-        for (int32_t i = 0; i < L; ++i) {
-            HIP_TRY(launch_spmv_step(rp, col, col24, n, Q, dv.as<double>(), dy.as<double>(), dh.as<double>(), st));
-            std::swap(dv.p, dy.p);
-        }
-        HIP_TRY(launch_colsum(dh.as<double>(), n, Q, dsq.as<double>(), dlin.as<double>(), st));
-        std::vector<double> sq(Q), lin(Q);
-        HIP_TRY(hipMemcpyAsync(sq.data(), dsq.p, Q * 8, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipMemcpyAsync(lin.data(), dlin.p, Q * 8, hipMemcpyDeviceToHost, st));
+        HIP_TRY(launch_series(g->rp32.as<const uint32_t>(), plain_ids(g), packed_ids(g), n, g->hubs.as<const uint32_t>(),
+                              g->nhubs, Q, L, seeds, dh.as<double>(), dy.as<double>(), dpart.as<double>(),
+                              dbeta.as<double>(), st));
+        HIP_TRY(hipMemcpyAsync(beta_L + q0, dbeta.p, Q * 8, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
-        for (uint32_t q = 0; q < Q; ++q) beta_L[q0 + q] = sq[q] - lin[q] * lin[q] / (double)n;
     }
     return BD_OK;
 }
@@ -1707,24 +1752,17 @@ extern "C" int bd_graph_lambda(bd_graph* g, int32_t iters, uint64_t seed, void* 
     std::lock_guard<std::mutex> lock(g->mu);
     hipStream_t st = (hipStream_t)stream;
     const uint32_t n = (uint32_t)g->n;
-    const uint32_t* rp = g->rp32.as<const uint32_t>();
-    const bool packed_ids = g->layout == 2 || g->layout == 3 || g->layout == 5;
-    const uint32_t* col = packed_ids ? nullptr : g->col.as<const uint32_t>();
-    const uint32_t* col24 = packed_ids ? g->col24.as<const uint32_t>() : nullptr;
-    DevBuf phi, x, y, z, part, scal;
-    int rc = phi.alloc((size_t)n * 8);
-    if (rc == BD_OK) rc = x.alloc((size_t)n * 8);
+    DevBuf w, y, sums;  // sums: the partial sums, then the estimate
+    int rc = w.alloc((size_t)n * 8);
     if (rc == BD_OK) rc = y.alloc((size_t)n * 8);
-    if (rc == BD_OK) rc = z.alloc((size_t)n * 8);
-    if (rc == BD_OK) rc = part.alloc(2 * 1024 * 8);
-    if (rc == BD_OK) rc = scal.alloc(2 * 8);
+    if (rc == BD_OK) rc = sums.alloc((4 * kLambdaBlocks + 1) * 8);
     if (rc != BD_OK) return rc;
-    HIP_TRY(launch_lambda(rp, col, col24, n, (uint32_t)g->nnz, iters, seed, phi.as<double>(), x.as<double>(),
-                          y.as<double>(), z.as<double>(), part.as<double>(), scal.as<double>(), st));
-    double sc[2] = {0.0, 0.0};
-    HIP_TRY(hipMemcpyAsync(sc, scal.p, sizeof(sc), hipMemcpyDeviceToHost, st));
+    double* out = sums.as<double>() + 4 * kLambdaBlocks;
+    HIP_TRY(launch_lambda(g->rp32.as<const uint32_t>(), plain_ids(g), packed_ids(g), n, (uint32_t)g->nnz,
+                          g->hubs.as<const uint32_t>(), g->nhubs, iters, seed, w.as<double>(), y.as<double>(),
+                          sums.as<double>(), out, st));
+    HIP_TRY(hipMemcpyAsync(lambda, out, 8, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
-    *lambda = sc[1];
     return BD_OK;
 }
 

@@ -247,20 +247,36 @@ hipError_t build_fat_adjacency(const uint4* node, const uint32_t* col, uint4* ad
 // Gather-roofline microbenchmark: `chains` in {1, 2, 4, 8} chains per lane.
 hipError_t launch_gather(const GraphTables& g, int layout, int chains, uint32_t grid, int32_t steps, uint32_t seed,
                          uint32_t* sink, hipStream_t st);
-// Binary64 truncated series and spectral helpers (row offsets rp[0..n], and
-// either col (32-bit ids) or col24 (packed 3-byte ids)).
-hipError_t launch_spmv_step(const uint32_t* rp, const uint32_t* col, const uint32_t* col24, uint32_t n, uint32_t Q,
-                            const double* V, double* Y, double* H, hipStream_t st);
-hipError_t launch_colsum(const double* H, uint32_t n, uint32_t Q, double* sq, double* lin, hipStream_t st);
-// v_0 = D^{-1} b_st columns (Q <= 64): entries s[q] = vs[q], t[q] = vt[q] of V and H,
-// which the caller has zeroed.
-hipError_t launch_series_seed(const uint32_t* s, const uint32_t* t, const double* vs, const double* vt, uint32_t Q,
-                              double* V, double* H, hipStream_t st);
-// Power iteration for lambda, all on the device: phi, x, y, z are n doubles,
-// part 2 * 1024 doubles, scal 2 doubles; the estimate ends in scal[1].
+// Binary64 truncated series (pw_series.hip; row offsets rp[0..n], and either col
+// (32-bit ids) or col24 (packed 3-byte ids)). v_0 = D^{-1} b_st of column q has
+// entries s[q] = vs[q] and t[q] = vt[q]; unused columns have s = t = n.
+struct SeriesSeeds {
+    uint32_t s[64], t[64];
+    double vs[64], vt[64];
+};
+struct SeriesPair {
+    uint32_t s, t;
+    double vs, vt;
+};
+constexpr uint32_t kHubDegree = 64;          // rows above it get a work group of their own
+constexpr uint32_t kSeriesParts = 512;       // partial sums per column
+constexpr uint32_t kSeriesSmallNodes = 2048; // largest graph of the one-work-group form
+uint32_t series_columns(uint32_t Q);         // columns a slab
+uint32_t series_slabs(uint32_t Q);           // slabs of Q columns
+// H and Y: n x series_columns x series_slabs doubles each; part: 2 kSeriesParts a column.
+hipError_t launch_series(const uint32_t* rp, const uint32_t* col, const uint32_t* col24, uint32_t n,
+                         const uint32_t* hubs, uint32_t nhub, uint32_t Q, int32_t L, const SeriesSeeds& seeds, double* H,
+                         double* Y, double* part, double* beta, hipStream_t st);
+// The same for graphs of at most kSeriesSmallNodes nodes whose rows and 2-byte
+// adjacency (SignTables::blk with the adjacency in LDS) fit LDS with a column.
+size_t series_small_bytes(uint32_t nrow, uint32_t idw, uint32_t n);
+hipError_t launch_series_small(const uint4* tab, uint32_t nrow, uint32_t idw, uint32_t n, uint32_t Q, int32_t L,
+                               const SeriesPair* pairs, double* beta, hipStream_t st);
+// Power iteration for lambda: W and Y are n doubles, part 4 * kLambdaBlocks.
+constexpr uint32_t kLambdaBlocks = 512;
 hipError_t launch_lambda(const uint32_t* rp, const uint32_t* col, const uint32_t* col24, uint32_t n, uint32_t nnz,
-                         int32_t iters, uint64_t seed, double* phi, double* x, double* y, double* z, double* part,
-                         double* scal, hipStream_t st);
+                         const uint32_t* hubs, uint32_t nhub, int32_t iters, uint64_t seed, double* W, double* Y,
+                         double* part, double* lambda, hipStream_t st);
 // Work groups of the walk kernel that fit on the device at once.
 int walk_occupancy(int layout, int uniform, int share, int* wgs_per_cu);
 int signs_occupancy(const SignShape& sh, int uniform, int share, int* wgs_per_cu);

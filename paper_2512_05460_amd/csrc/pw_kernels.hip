@@ -729,254 +729,3 @@ hipError_t launch_gather(const GraphTables& g, int layout, int chains, uint32_t 
 }
 
 }  // namespace pw
-
-namespace pw {
-
-// ---------------------------------------------------------------------------
-// Sparse products in binary64 for the truncated series (Lemma 2.3) and the
-// mixing factor (section 2.1). V is n x Q row-major (Q <= 64 columns).
-//
-// One wave per row. Its lanes are J = 64/Qp neighbour slots times Qp columns
-// (Qp = the power of two >= Q): lane (j, q) sums V[u][q] over the row's
-// neighbours j, j + J, j + 2J, ..., and a butterfly over the J slots (the same
-// value in every lane of a column, in a fixed order) completes the row sum. With
-// Q = 64 a lane owns one column and walks the whole row; with Q = 1 the 64
-// lanes share the row's neighbours.
-//   kMode 0 (series step):     y[x][q] = (1/d_x) sum_u v[u][q];  h[x][q] += y[x][q]
-//   kMode 1 (normalised A):    y[x]    = (1/sqrt d_x) sum_u v[u]  (v = x / sqrt d)
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t nbr_at(const uint32_t* col, const uint32_t* col24, uint32_t i)
-{
-    if (col24) {
-        const uint32_t o = i * 3u;
-        return __builtin_amdgcn_alignbit(col24[(o >> 2) + 1], col24[o >> 2], (o & 3u) * 8u) & 0xFFFFFFu;
-    }
-    return col[i];
-}
-
-template <int kMode>
-__global__ __launch_bounds__(256) void rowsum_kernel(const uint32_t* rp, const uint32_t* col, const uint32_t* col24,
-                                                     uint32_t n, uint32_t Q, uint32_t qbits, const double* V,
-                                                     double* Y, double* H)
-{
-    const uint32_t row = blockIdx.x * 4u + (threadIdx.x >> 6);
-    if (row >= n) return;  // wave-uniform: the whole wave leaves
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t Qp = 1u << qbits;
-    const uint32_t q = lane & (Qp - 1u);
-    const uint32_t j = lane >> qbits;
-    const uint32_t J = 64u >> qbits;
-    const uint32_t b = rp[row], e = rp[row + 1];
-    double acc = 0.0;
-    if (q < Q)
-        for (uint32_t i = b + j; i < e; i += J) acc = __dadd_rn(acc, V[(size_t)nbr_at(col, col24, i) * Q + q]);
-    for (uint32_t off = Qp; off < 64u; off <<= 1) acc = __dadd_rn(acc, __shfl_xor(acc, (int)off));
-    if (j != 0 || q >= Q) return;
-    const double d = (double)(e - b);
-    if (kMode == 0) {
-        const double y = __dmul_rn(acc, __ddiv_rn(1.0, d));
-        const size_t at = (size_t)row * Q + q;
-        Y[at] = y;
-        H[at] = __dadd_rn(H[at], y);
-    } else {
-        Y[row] = __ddiv_rn(acc, sqrt(d));
-    }
-}
-
-// v_0 = D^{-1} b_st for up to 64 queries: zero first, then the two entries of
-// each column (storage ids and degrees in the argument block).
-struct SeriesSeed {
-    uint32_t s[64], t[64];
-    double vs[64], vt[64];
-};
-
-__global__ void series_seed_kernel(SeriesSeed a, uint32_t Q, double* V, double* H)
-{
-    const uint32_t q = threadIdx.x;
-    if (q >= Q) return;
-    V[(size_t)a.s[q] * Q + q] = a.vs[q];
-    V[(size_t)a.t[q] * Q + q] = a.vt[q];
-    H[(size_t)a.s[q] * Q + q] = a.vs[q];
-    H[(size_t)a.t[q] * Q + q] = a.vt[q];
-}
-
-// Per-query sums ||h||^2 and 1^T h in a fixed order: one work group per query,
-// a strided partial per thread, then a fixed tree in LDS.
-__global__ __launch_bounds__(256) void colsum_kernel(const double* H, uint32_t n, uint32_t Q, double* sq,
-                                                     double* lin)
-{
-    __shared__ double a[256], c[256];
-    const uint32_t q = blockIdx.x;
-    double s2 = 0.0, s1 = 0.0;
-    for (uint32_t x = threadIdx.x; x < n; x += 256u) {
-        const double h = H[(size_t)x * Q + q];
-        s2 = __dadd_rn(s2, __dmul_rn(h, h));
-        s1 = __dadd_rn(s1, h);
-    }
-    a[threadIdx.x] = s2;
-    c[threadIdx.x] = s1;
-    __syncthreads();
-    for (uint32_t w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) {
-            a[threadIdx.x] = __dadd_rn(a[threadIdx.x], a[threadIdx.x + w]);
-            c[threadIdx.x] = __dadd_rn(c[threadIdx.x], c[threadIdx.x + w]);
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        sq[q] = a[0];
-        lin[q] = c[0];
-    }
-}
-
-static uint32_t pow2_bits(uint32_t Q)
-{
-    uint32_t b = 0;
-    while ((1u << b) < Q) ++b;
-    return b;
-}
-
-hipError_t launch_spmv_step(const uint32_t* rp, const uint32_t* col, const uint32_t* col24, uint32_t n, uint32_t Q,
-                            const double* V, double* Y, double* H, hipStream_t st)
-{
-    hipLaunchKernelGGL(rowsum_kernel<0>, dim3((n + 3) / 4), dim3(256), 0, st, rp, col, col24, n, Q, pow2_bits(Q), V,
-                       Y, H);
-    return hipGetLastError();
-}
-
-hipError_t launch_series_seed(const uint32_t* s, const uint32_t* t, const double* vs, const double* vt, uint32_t Q,
-                              double* V, double* H, hipStream_t st)
-{
-    SeriesSeed a{};
-    for (uint32_t q = 0; q < Q && q < 64; ++q) {
-        a.s[q] = s[q];
-        a.t[q] = t[q];
-        a.vs[q] = vs[q];
-        a.vt[q] = vt[q];
-    }
-    hipLaunchKernelGGL(series_seed_kernel, dim3(1), dim3(64), 0, st, a, Q, V, H);
-    return hipGetLastError();
-}
-
-hipError_t launch_colsum(const double* H, uint32_t n, uint32_t Q, double* sq, double* lin, hipStream_t st)
-{
-    hipLaunchKernelGGL(colsum_kernel, dim3(Q), dim3(256), 0, st, H, n, Q, sq, lin);
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// Spectral radius of P off the stationary direction: power iteration on the
-// symmetric N = D^{-1/2} A D^{-1/2} (same spectrum as P), whose top
-// eigenvector is phi = sqrt(d)/||sqrt(d)|| = sqrt(d / nnz). Every iteration
-// runs on the device: z = x / sqrt(d); y = N x (rowsum_kernel<1>); the two sums
-// phi.y and y.y in a fixed order (per-block partials, then one block); and
-// x = (y - (phi.y) phi) / ||y - (phi.y) phi||, whose norm
-// sqrt(y.y - (phi.y)^2) (phi is a unit vector) is the estimate of lambda.
-// ---------------------------------------------------------------------------
-constexpr uint32_t kDotBlocks = 1024;
-
-__global__ __launch_bounds__(256) void phi_kernel(const uint32_t* rp, uint32_t n, double nnz, double* phi)
-{
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-        phi[i] = sqrt(__ddiv_rn((double)(rp[i + 1] - rp[i]), nnz));
-}
-
-// a counter-based start vector: the SplitMix64 output function of seed + i
-// times the golden-ratio increment, mapped to [-1/2, 1/2)
-__global__ __launch_bounds__(256) void start_vector_kernel(uint64_t seed, uint32_t n, double* x)
-{
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        uint64_t z = seed + (uint64_t)(i + 1) * 0x9E3779B97F4A7C15ull;
-        z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-        z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-        z ^= z >> 31;
-        x[i] = (double)(z >> 11) * 0x1p-53 - 0.5;
-    }
-}
-
-__global__ __launch_bounds__(256) void scale_rsqrt_deg_kernel(const uint32_t* rp, uint32_t n, const double* x,
-                                                              double* z)
-{
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-        z[i] = __ddiv_rn(x[i], sqrt((double)(rp[i + 1] - rp[i])));
-}
-
-__device__ __forceinline__ void block_sum2(double* a, double* c)
-{
-    for (uint32_t w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) {
-            a[threadIdx.x] = __dadd_rn(a[threadIdx.x], a[threadIdx.x + w]);
-            c[threadIdx.x] = __dadd_rn(c[threadIdx.x], c[threadIdx.x + w]);
-        }
-        __syncthreads();
-    }
-}
-
-__global__ __launch_bounds__(256) void dot2_kernel(const double* phi, const double* y, uint32_t n, double* part)
-{
-    __shared__ double a[256], c[256];
-    double py = 0.0, yy = 0.0;
-    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n; i += gridDim.x * 256u) {
-        py = __dadd_rn(py, __dmul_rn(phi[i], y[i]));
-        yy = __dadd_rn(yy, __dmul_rn(y[i], y[i]));
-    }
-    a[threadIdx.x] = py;
-    c[threadIdx.x] = yy;
-    __syncthreads();
-    block_sum2(a, c);
-    if (threadIdx.x == 0) {
-        part[2 * blockIdx.x] = a[0];
-        part[2 * blockIdx.x + 1] = c[0];
-    }
-}
-
-// scal[0] = phi.y, scal[1] = sqrt(max(y.y - (phi.y)^2, 0))
-__global__ __launch_bounds__(256) void dot2_finish_kernel(const double* part, uint32_t nb, double* scal)
-{
-    __shared__ double a[256], c[256];
-    double py = 0.0, yy = 0.0;
-    for (uint32_t i = threadIdx.x; i < nb; i += 256u) {
-        py = __dadd_rn(py, part[2 * i]);
-        yy = __dadd_rn(yy, part[2 * i + 1]);
-    }
-    a[threadIdx.x] = py;
-    c[threadIdx.x] = yy;
-    __syncthreads();
-    block_sum2(a, c);
-    if (threadIdx.x == 0) {
-        scal[0] = a[0];
-        scal[1] = sqrt(fmax(__dsub_rn(c[0], __dmul_rn(a[0], a[0])), 0.0));
-    }
-}
-
-__global__ __launch_bounds__(256) void project_kernel(const double* y, const double* phi, const double* scal,
-                                                      uint32_t n, double* x)
-{
-    const double dot = scal[0], nrm = scal[1];
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x)
-        x[i] = nrm > 0.0 ? __ddiv_rn(__dsub_rn(y[i], __dmul_rn(dot, phi[i])), nrm) : 0.0;
-}
-
-hipError_t launch_lambda(const uint32_t* rp, const uint32_t* col, const uint32_t* col24, uint32_t n, uint32_t nnz,
-                         int32_t iters, uint64_t seed, double* phi, double* x, double* y, double* z, double* part,
-                         double* scal, hipStream_t st)
-{
-    const dim3 grid(std::min<uint32_t>((n + 255) / 256, 16384u)), block(256);
-    const uint32_t nb = std::min<uint32_t>(kDotBlocks, (n + 255) / 256);
-    hipLaunchKernelGGL(phi_kernel, grid, block, 0, st, rp, n, (double)nnz, phi);
-    hipLaunchKernelGGL(start_vector_kernel, grid, block, 0, st, seed, n, y);
-    hipLaunchKernelGGL(dot2_kernel, dim3(nb), block, 0, st, phi, y, n, part);
-    hipLaunchKernelGGL(dot2_finish_kernel, dim3(1), block, 0, st, part, nb, scal);
-    hipLaunchKernelGGL(project_kernel, grid, block, 0, st, y, phi, scal, n, x);
-    for (int32_t it = 0; it < iters; ++it) {
-        hipLaunchKernelGGL(scale_rsqrt_deg_kernel, grid, block, 0, st, rp, n, x, z);
-        hipLaunchKernelGGL(rowsum_kernel<1>, dim3((n + 3) / 4), block, 0, st, rp, col, col24, n, 1u, 0u, z, y,
-                           (double*)nullptr);
-        hipLaunchKernelGGL(dot2_kernel, dim3(nb), block, 0, st, phi, y, n, part);
-        hipLaunchKernelGGL(dot2_finish_kernel, dim3(1), block, 0, st, part, nb, scal);
-        hipLaunchKernelGGL(project_kernel, grid, block, 0, st, y, phi, scal, n, x);
-    }
-    return hipGetLastError();
-}
-
-}  // namespace pw
