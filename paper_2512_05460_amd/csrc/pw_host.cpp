@@ -255,10 +255,10 @@ int validate(int64_t n, const int64_t* rp, const int32_t* col, int32_t* bip)
 }
 
 // The caller's arrays when they live in device memory (BD_DEVICE_PTRS): checked
-// to be device allocations of the current device, then read once into host
-// copies for validation and layout building.
-int fetch_device_csr(int64_t n, const int64_t* row_ptr, const int32_t* col_idx, hipStream_t st,
-                     std::vector<int64_t>& rp, std::vector<int32_t>& col)
+// to be device allocations of the current device; the offsets are read into a
+// host copy, which the planner's degrees and the storage order come from.
+int fetch_device_offsets(int64_t n, const int64_t* row_ptr, const int32_t* col_idx, hipStream_t st,
+                         std::vector<int64_t>& rp)
 {
     int dev = -1;
     HIP_TRY(hipGetDevice(&dev));
@@ -276,10 +276,67 @@ int fetch_device_csr(int64_t n, const int64_t* row_ptr, const int32_t* col_idx, 
     const int64_t nnz = rp[(size_t)n];
     if (rp[0] != 0 || nnz < 0) return BD_E_GRAPH;
     if (nnz > kMaxNnz) return BD_E_RANGE;
-    col.resize((size_t)std::max<int64_t>(nnz, 1));
-    if (nnz) HIP_TRY(hipMemcpyAsync(col.data(), col_idx, (size_t)nnz * 4, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
     return BD_OK;
+}
+
+template <class T>
+int upload(DevBuf& b, const std::vector<T>& v, hipStream_t st)
+{
+    const int rc = b.alloc(v.size() * sizeof(T));
+    if (rc != BD_OK || v.empty()) return rc;
+    HIP_TRY(hipMemcpyAsync(b.p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, st));
+    return BD_OK;
+}
+
+// The caller's CSR on the device: its own arrays, or copies of host ones.
+struct LoadCsr {
+    CsrView view{};
+    DevBuf rp, col;
+    int set(int64_t n, int64_t nnz, const int64_t* row_ptr, const int32_t* col_idx, bool on_device, hipStream_t st)
+    {
+        view = CsrView{(uint32_t)n, row_ptr, col_idx};
+        if (on_device) return BD_OK;
+        int rc = rp.alloc(((size_t)n + 1) * 8);
+        if (rc == BD_OK) rc = col.alloc((size_t)nnz * 4);
+        if (rc != BD_OK) return rc;
+        HIP_TRY(hipMemcpyAsync(rp.p, row_ptr, ((size_t)n + 1) * 8, hipMemcpyHostToDevice, st));
+        HIP_TRY(hipMemcpyAsync(col.p, col_idx, (size_t)nnz * 4, hipMemcpyHostToDevice, st));
+        view.rp = rp.as<const int64_t>();
+        view.col = col.as<const int32_t>();
+        return BD_OK;
+    }
+    // ids in range; with `deep` also simple, sorted, symmetric and connected
+    int check(bool deep, int32_t* bipartite, hipStream_t st) const
+    {
+        DevBuf word, parent;
+        int rc = word.alloc(16);
+        if (rc != BD_OK) return rc;
+        HIP_TRY(launch_zero(word.p, 16, st));
+        HIP_TRY(launch_check(view, deep ? 1 : 0, word.as<uint32_t>(), st));
+        uint32_t got[2] = {0, 0};
+        HIP_TRY(hipMemcpyAsync(got, word.p, 8, hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        if (got[0]) return BD_E_GRAPH;
+        if (!deep) return BD_OK;
+        rc = parent.alloc((size_t)view.n * 8);
+        if (rc != BD_OK) return rc;
+        HIP_TRY(launch_components(view, parent.as<uint32_t>(), word.as<uint32_t>() + 1, st));
+        HIP_TRY(hipMemcpyAsync(got, word.p, 8, hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        if (got[1] & 1u) return BD_E_GRAPH;
+        *bipartite = got[1] & 2u ? 0 : 1;
+        return BD_OK;
+    }
+};
+
+// Caller ids in descending degree, ties by id.
+std::vector<uint32_t> degree_order(const std::vector<int32_t>& deg, int32_t d_max)
+{
+    std::vector<uint32_t> first((size_t)d_max + 2, 0u), order(deg.size());
+    for (const int32_t d : deg) ++first[(size_t)(d_max - d) + 1];
+    for (size_t d = 1; d < first.size(); ++d) first[d] += first[d - 1];
+    for (size_t v = 0; v < deg.size(); ++v) order[first[(size_t)(d_max - deg[v])]++] = (uint32_t)v;
+    return order;
 }
 
 // The kernel code that runs walks of sharing class `share` on g: the graph's,
@@ -361,19 +418,12 @@ uint32_t sign_waves(const SignShape& s, uint32_t share, uint32_t R)
 // Tables of the sign-table kernels, for graphs whose block table and one sign
 // table fit a CU's LDS. `order`: storage id -> caller id (empty: the tables are
 // stored in the caller's order, and the descending-degree one is made here).
-int load_sign_tables(bd_graph* g, const std::vector<uint32_t>& order_in, const int64_t* row_ptr, const int32_t* col_idx,
-                     hipStream_t st)
+int load_sign_tables(bd_graph* g, const std::vector<uint32_t>& order_in, const LoadCsr& csr, const int64_t* row_ptr,
+                     const int32_t* col_host, hipStream_t st)
 {
     const size_t n = (size_t)g->n, nnz = (size_t)g->nnz;
     if (n > (size_t(1) << 22) || nnz == 0 || 3 * nnz + 8 > UINT32_MAX) return BD_OK;
-    std::vector<uint32_t> order = order_in;
-    if (order.empty()) {
-        order.resize(n);
-        std::vector<uint32_t> first((size_t)g->d_max + 2, 0u);
-        for (size_t v = 0; v < n; ++v) ++first[(size_t)(g->d_max - g->deg[v]) + 1];
-        for (size_t d = 1; d < first.size(); ++d) first[d] += first[d - 1];
-        for (size_t v = 0; v < n; ++v) order[first[(size_t)(g->d_max - g->deg[v])]++] = (uint32_t)v;
-    }
+    const std::vector<uint32_t> order = order_in.empty() ? degree_order(g->deg, g->d_max) : order_in;
     std::vector<uint32_t> rp(n + 1);
     rp[0] = 0;
     for (size_t i = 0; i < n; ++i) rp[i + 1] = rp[i] + (uint32_t)g->deg[order[i]];
@@ -402,13 +452,20 @@ int load_sign_tables(bd_graph* g, const std::vector<uint32_t>& order_in, const i
         // rows and adjacency in the order of the ids that probes are evaluated on
         const bool ranked = g->layout == 5;
         std::vector<uint32_t> rank(ranked ? n : 0), tab(lds.nblk + lds.idw, 0u);
+        std::vector<int32_t> fetched;
+        if (!col_host) {
+            fetched.resize(nnz);
+            HIP_TRY(hipMemcpyAsync(fetched.data(), csr.view.col, nnz * 4, hipMemcpyDeviceToHost, st));
+            HIP_TRY(hipStreamSynchronize(st));
+            col_host = fetched.data();
+        }
         for (size_t i = 0; i < rank.size(); ++i) rank[order[i]] = (uint32_t)i;
         uint32_t at = 0;
         for (size_t i = 0; i < n; ++i) {
             const size_t v = ranked ? order[i] : i;
             tab[i] = at | (uint32_t)g->deg[v] << 16;
             for (int64_t j = row_ptr[v]; j < row_ptr[v + 1]; ++j, ++at) {
-                const uint32_t x = ranked ? rank[(size_t)col_idx[j]] : (uint32_t)col_idx[j];
+                const uint32_t x = ranked ? rank[(size_t)col_host[j]] : (uint32_t)col_host[j];
                 tab[lds.nblk + at / 2] |= 4u * x << (16u * (at & 1u));
             }
         }
@@ -444,24 +501,17 @@ int load_sign_tables(bd_graph* g, const std::vector<uint32_t>& order_in, const i
         pid.swap(ids_by_lane);
         mem.words = (uint32_t)word.size();
         pid.insert(pid.end(), word.begin(), word.end());
-        std::vector<uint8_t> ids(3 * nnz + 8, 0);
-        size_t e = 0;
-        for (size_t i = 0; i < n; ++i) {
-            const uint32_t v = order[i];
-            for (int64_t j = row_ptr[v]; j < row_ptr[v + 1]; ++j, e += 3) {
-                const uint32_t x = at[(size_t)col_idx[j]];
-                ids[e] = (uint8_t)x;
-                ids[e + 1] = (uint8_t)(x >> 8);
-                ids[e + 2] = (uint8_t)(x >> 16);
-            }
-        }
-        rc = g->sblk.alloc(blk.size() * 4);
-        if (rc == BD_OK) rc = g->spid.alloc(pid.size() * 4);
-        if (rc == BD_OK) rc = g->sids.alloc(ids.size());
+        DevBuf d_order, d_at, d_rp;
+        rc = upload(g->sblk, blk, st);
+        if (rc == BD_OK) rc = upload(g->spid, pid, st);
+        if (rc == BD_OK) rc = upload(d_order, order, st);
+        if (rc == BD_OK) rc = upload(d_at, at, st);
+        if (rc == BD_OK) rc = upload(d_rp, rp, st);
+        if (rc == BD_OK) rc = g->sids.alloc(3 * nnz + 8);
         if (rc != BD_OK) return rc;
-        HIP_TRY(hipMemcpyAsync(g->sblk.p, blk.data(), blk.size() * 4, hipMemcpyHostToDevice, st));
-        HIP_TRY(hipMemcpyAsync(g->spid.p, pid.data(), pid.size() * 4, hipMemcpyHostToDevice, st));
-        HIP_TRY(hipMemcpyAsync(g->sids.p, ids.data(), ids.size(), hipMemcpyHostToDevice, st));
+        HIP_TRY(launch_zero(g->sids.as<char>() + (3 * nnz & ~(size_t)3), 12, st));
+        HIP_TRY(launch_rename(csr.view, d_order.as<const uint32_t>(), d_at.as<const uint32_t>(), d_rp.as<const uint32_t>(),
+                              nullptr, g->sids.as<uint8_t>(), st));
         HIP_TRY(hipStreamSynchronize(st));
         mem.blk = g->sblk.as<const uint4>();
         mem.pid = g->spid.as<const uint32_t>();
@@ -490,13 +540,12 @@ extern "C" int graph_load_csr(int64_t n, const int64_t* row_ptr, const int32_t* 
     *out = nullptr;
     if (n < 2 || n > kMaxN) return BD_E_RANGE;
     std::vector<int64_t> rp_host;
-    std::vector<int32_t> col_host;
-    if (flags & BD_DEVICE_PTRS) {
-        const int rc = fetch_device_csr(n, row_ptr, col_idx, (hipStream_t)stream, rp_host, col_host);
+    const bool on_device = (flags & BD_DEVICE_PTRS) != 0;
+    const int64_t* row_ptr_dev = row_ptr;  // with on_device
+    if (on_device) {
+        const int rc = fetch_device_offsets(n, row_ptr, col_idx, (hipStream_t)stream, rp_host);
         if (rc != BD_OK) return rc;
         row_ptr = rp_host.data();
-        col_idx = col_host.data();
-        flags &= ~BD_DEVICE_PTRS;
     }
     if (row_ptr[0] != 0) return BD_E_GRAPH;
     const int64_t nnz = row_ptr[n];
@@ -534,19 +583,23 @@ extern "C" int graph_load_csr(int64_t n, const int64_t* row_ptr, const int32_t* 
         if (flags & BD_LAYOUT_FAT) return BD_E_INVALID;
         if (!wide && (n > (int64_t(1) << 24) || 3 * nnz + 8 > (int64_t)UINT32_MAX)) return BD_E_RANGE;
     }
-    for (int64_t i = 0; i < nnz; ++i)
-        if (col_idx[i] < 0 || col_idx[i] >= n) return BD_E_GRAPH;
+    const bool deep = !(flags & BD_SKIP_VALIDATION);
     int32_t bip = 0;
-    if (!(flags & BD_SKIP_VALIDATION)) {
-        const int rc = validate(n, row_ptr, col_idx, &bip);
-        if (rc != BD_OK) return rc;
-    }
     int dev = 0, ndev = 0;
     if (hipGetDeviceCount(&ndev) != hipSuccess || ndev < 1) {
+        // without a device the checks' verdicts come from the host
         (void)hipGetLastError();
-        return BD_E_NODEVICE;
+        for (int64_t i = 0; i < nnz; ++i)
+            if (col_idx[i] < 0 || col_idx[i] >= n) return BD_E_GRAPH;
+        const int rc = deep ? validate(n, row_ptr, col_idx, &bip) : BD_OK;
+        return rc != BD_OK ? rc : BD_E_NODEVICE;
     }
     HIP_TRY(hipGetDevice(&dev));
+    hipStream_t st = (hipStream_t)stream;
+    LoadCsr csr;
+    int rc = csr.set(n, nnz, on_device ? row_ptr_dev : row_ptr, col_idx, on_device, st);
+    if (rc == BD_OK) rc = csr.check(deep, &bip, st);
+    if (rc != BD_OK) return rc;
 
     bd_graph* g = new (std::nothrow) bd_graph();
     if (!g) return BD_E_NOMEM;
@@ -577,113 +630,39 @@ extern "C" int graph_load_csr(int64_t n, const int64_t* row_ptr, const int32_t* 
     for (int64_t v = 0; v < n; ++v) g->deg[(size_t)v] = (int32_t)(row_ptr[v + 1] - row_ptr[v]);
     // storage order: caller order, or descending degree (ties by id)
     std::vector<uint32_t> order;  // storage id -> caller id
-    std::vector<int32_t> relabelled;
-    const int32_t* col_store = col_idx;
     if (flags & BD_RELABEL_DEGREE) {
-        order.resize((size_t)n);
-        for (int64_t v = 0; v < n; ++v) order[(size_t)v] = (uint32_t)v;
-        std::stable_sort(order.begin(), order.end(),
-                         [&](uint32_t a, uint32_t b) { return g->deg[a] > g->deg[b]; });
+        order = degree_order(g->deg, dmax);
         g->internal.resize((size_t)n);
         for (int64_t i = 0; i < n; ++i) g->internal[order[(size_t)i]] = (uint32_t)i;
         if (storage_probe) g->external = order;  // walks report storage ids: map them back
-        relabelled.resize((size_t)nnz);
-        int64_t pos = 0;
-        for (int64_t i = 0; i < n; ++i) {
-            const uint32_t v = order[(size_t)i];
-            for (int64_t e = row_ptr[v]; e < row_ptr[v + 1]; ++e)
-                relabelled[(size_t)pos++] = (int32_t)g->internal[(size_t)col_idx[e]];
-        }
-        col_store = relabelled.data();
     }
-    std::vector<uint32_t> nodetab((size_t)n * 4);
-    int64_t off = 0;
-    for (int64_t i = 0; i < n; ++i) {
-        const uint32_t v = order.empty() ? (uint32_t)i : order[(size_t)i];
-        const int32_t d = g->deg[v];
-        const float inv = 1.0f / (float)d;
-        uint32_t bits;
-        std::memcpy(&bits, &inv, 4);
-        nodetab[(size_t)i * 4 + 0] = (uint32_t)off;
-        nodetab[(size_t)i * 4 + 1] = (uint32_t)d;
-        nodetab[(size_t)i * 4 + 2] = bits;
-        nodetab[(size_t)i * 4 + 3] = v;
-        off += d;
-    }
-    hipStream_t st = (hipStream_t)stream;
-    int rc = BD_OK;
-    std::vector<uint32_t> rp32, packed;
-    if (g->layout >= 2) {
-        // compact: 32-bit row offsets (storage order), 3-byte neighbour storage ids
-        // (little endian) with 8 bytes of padding -- 4-byte ids above 2^24 nodes;
-        // with hubs first also the node entries {row offset, original id}, entry
-        // n = {nnz, 0}
-        const bool packed_ids = g->layout != 4;
-        const bool hubs = g->layout == 3 || g->layout == 4;  // 8-byte node entries (layout 5 reads rp32)
-        rp32.resize((size_t)n + 1);
-        for (int64_t i = 0; i < n; ++i) rp32[(size_t)i] = nodetab[(size_t)i * 4];
-        rp32[(size_t)n] = (uint32_t)nnz;
-        if (packed_ids) {
-            const size_t bytes = (size_t)(3 * nnz + 8);
-            packed.assign((bytes + 3) / 4, 0u);
-            uint8_t* b = reinterpret_cast<uint8_t*>(packed.data());
-            for (int64_t i = 0; i < nnz; ++i) {
-                const uint32_t v = (uint32_t)col_store[i];
-                b[3 * i + 0] = (uint8_t)v;
-                b[3 * i + 1] = (uint8_t)(v >> 8);
-                b[3 * i + 2] = (uint8_t)(v >> 16);
-            }
-        }
-        std::vector<uint32_t> node8;
-        if (hubs) {
-            node8.resize(2 * ((size_t)n + 1));
-            for (int64_t i = 0; i < n; ++i) {
-                node8[2 * (size_t)i] = nodetab[(size_t)i * 4];
-                node8[2 * (size_t)i + 1] = nodetab[(size_t)i * 4 + 3];
-            }
-            node8[2 * (size_t)n] = (uint32_t)nnz;
-            node8[2 * (size_t)n + 1] = 0u;
-        }
-        rc = g->rp32.alloc(rp32.size() * 4);
-        if (rc == BD_OK && packed_ids) rc = g->col24.alloc(packed.size() * 4);
-        if (rc == BD_OK && !packed_ids) rc = g->col.alloc((size_t)std::max<int64_t>(nnz, 1) * 4);
-        if (rc == BD_OK && hubs) rc = g->node8.alloc(node8.size() * 4);
-        if (rc != BD_OK) {
-            delete g;
-            return rc;
-        }
-        if (hipMemcpyAsync(g->rp32.p, rp32.data(), rp32.size() * 4, hipMemcpyHostToDevice, st) != hipSuccess ||
-            (packed_ids && hipMemcpyAsync(g->col24.p, packed.data(), packed.size() * 4, hipMemcpyHostToDevice,
-                                          st) != hipSuccess) ||
-            (!packed_ids && hipMemcpyAsync(g->col.p, col_store, (size_t)nnz * 4, hipMemcpyHostToDevice,
-                                           st) != hipSuccess) ||
-            (hubs && hipMemcpyAsync(g->node8.p, node8.data(), node8.size() * 4, hipMemcpyHostToDevice,
-                                    st) != hipSuccess)) {
-            delete g;
-            return BD_E_HIP;
-        }
-        if (hipStreamSynchronize(st) != hipSuccess) {
-            delete g;
-            return BD_E_HIP;
-        }
-    } else {
-        rp32.resize((size_t)n + 1);
-        for (int64_t i = 0; i < n; ++i) rp32[(size_t)i] = nodetab[(size_t)i * 4];
-        rp32[(size_t)n] = (uint32_t)nnz;
-        rc = g->rp32.alloc(rp32.size() * 4);
-        if (rc == BD_OK) rc = g->node.alloc((size_t)n * 16);
-        if (rc == BD_OK) rc = g->col.alloc((size_t)std::max<int64_t>(nnz, 1) * 4);
-        if (rc == BD_OK && g->layout == 1) rc = g->adj.alloc((size_t)std::max<int64_t>(nnz, 1) * 16);
-        if (rc != BD_OK) {
-            delete g;
-            return rc;
-        }
-        if (hipMemcpyAsync(g->node.p, nodetab.data(), (size_t)n * 16, hipMemcpyHostToDevice, st) != hipSuccess ||
-            hipMemcpyAsync(g->rp32.p, rp32.data(), rp32.size() * 4, hipMemcpyHostToDevice, st) != hipSuccess ||
-            hipMemcpyAsync(g->col.p, col_store, (size_t)nnz * 4, hipMemcpyHostToDevice, st) != hipSuccess) {
-            delete g;
-            return BD_E_HIP;
-        }
+    std::vector<uint32_t> rp32((size_t)n + 1);
+    rp32[0] = 0;
+    for (size_t i = 0; i < (size_t)n; ++i) rp32[i + 1] = rp32[i] + (uint32_t)g->deg[order.empty() ? i : order[i]];
+    // compact: 32-bit row offsets (storage order), 3-byte neighbour storage ids
+    // (little endian) with 8 bytes of padding -- 4-byte ids above 2^24 nodes; with
+    // hubs first also the node entries {row offset, original id}
+    const bool packed = g->layout >= 2 && g->layout != 4;
+    DevBuf d_order, d_internal;
+    rc = upload(g->rp32, rp32, st);
+    if (rc == BD_OK && !order.empty()) rc = upload(d_order, order, st);
+    if (rc == BD_OK && !order.empty()) rc = upload(d_internal, g->internal, st);
+    if (rc == BD_OK && packed) rc = g->col24.alloc((size_t)(3 * nnz + 8));
+    if (rc == BD_OK && !packed) rc = g->col.alloc((size_t)std::max<int64_t>(nnz, 1) * 4);
+    if (rc == BD_OK && g->layout < 2) rc = g->node.alloc((size_t)n * 16);
+    if (rc == BD_OK && (g->layout == 3 || g->layout == 4)) rc = g->node8.alloc(((size_t)n + 1) * 8);
+    if (rc == BD_OK && g->layout == 1) rc = g->adj.alloc((size_t)std::max<int64_t>(nnz, 1) * 16);
+    if (rc == BD_OK &&
+        ((packed && launch_zero(g->col24.as<char>() + (3 * (size_t)nnz & ~(size_t)3), 12, st) != hipSuccess) ||
+         launch_rename(csr.view, d_order.as<const uint32_t>(), d_internal.as<const uint32_t>(),
+                       g->rp32.as<const uint32_t>(), g->col.as<uint32_t>(), g->col24.as<uint8_t>(), st) != hipSuccess ||
+         launch_nodes((uint32_t)n, d_order.as<const uint32_t>(), g->rp32.as<const uint32_t>(), g->node.as<uint4>(),
+                      g->node8.as<uint2>(), st) != hipSuccess))
+        rc = BD_E_HIP;
+    if (rc != BD_OK) {
+        (void)hipStreamSynchronize(st);  // copies into the buffers may be under way
+        delete g;
+        return rc;
     }
     if (g->layout == 1 &&
         build_fat_adjacency(g->node.as<uint4>(), g->col.as<uint32_t>(), g->adj.as<uint4>(),
@@ -736,7 +715,7 @@ extern "C" int graph_load_csr(int64_t n, const int64_t* row_ptr, const int32_t* 
     {
         std::vector<uint32_t> hubs;
         for (size_t i = 0; i < (size_t)n; ++i)
-            if (nodetab[4 * i + 1] > kHubDegree) hubs.push_back((uint32_t)i);
+            if (rp32[i + 1] - rp32[i] > kHubDegree) hubs.push_back((uint32_t)i);
         g->nhubs = (uint32_t)hubs.size();
         const int hrc = g->hubs.alloc(hubs.size() * 4);
         if (hrc != BD_OK) {
@@ -751,7 +730,7 @@ extern "C" int graph_load_csr(int64_t n, const int64_t* row_ptr, const int32_t* 
         }
     }
     if (!(flags & (BD_NARROW_HUBS | BD_DIRECT_HUBS | BD_WIDE_HUBS))) {
-        const int src = load_sign_tables(g, order, row_ptr, col_idx, st);
+        const int src = load_sign_tables(g, order, csr, row_ptr, on_device ? nullptr : col_idx, st);
         if (src != BD_OK) {
             delete g;
             return src;
