@@ -28,33 +28,57 @@ __device__ __forceinline__ void lds_add_i128(unsigned long long* p, i128 v)
     atomicAdd(p + 1, hi + carry);
 }
 
-// Median of the G block means (section 3.2, Algorithm 1 final loop).
+// Waits until the atomics this wave has issued have been performed. What the work
+// groups of a query exchange are atomically updated words alone (block sums,
+// split-probe sums, counters), read back by atomic loads, so this order is all
+// they need; everything else a query leaves is read after the launch. A
+// device-scope fence here instead also writes the XCD's whole L2 back and
+// invalidates it: at L = 1 and R = 100 it made 480 us of what takes FENCE_US us.
+__device__ __forceinline__ void atomics_performed()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
+}
+
+// A 128-bit sum as its atomic additions have left it (read by atomics too, so
+// that no cache of this XCD can hold an older value).
+__device__ __forceinline__ i128 read_i128(unsigned long long* p)
+{
+    const unsigned long long lo = atomicAdd(p, 0ull), hi = atomicAdd(p + 1, 0ull);
+    return (i128)(((u128)hi << 64) | (u128)lo);
+}
+
+// Median of the G block means (section 3.2, Algorithm 1 final loop), by the whole
+// work group: a thread per block reads its sum and counts the smaller means.
+// ys: kMaxG + 2 doubles of LDS. (By one thread the G reads, each a round trip to
+// memory, followed one another.)
 __device__ inline void finalize_query(const WalkArgs& A, const QueryDesc& d, double* ys)
 {
-    const uint32_t G = d.G;
-    const unsigned long long* bs = A.blocksum + (size_t)d.slot * A.gdim * 2;
-    for (uint32_t g = 0; g < G; ++g) {
-        const double y = (i128_to_f64(load_i128(bs + 2 * g)) * 0x1p-64) / (double)d.B;
+    const uint32_t G = d.G, g = threadIdx.x;
+    unsigned long long* bs = A.blocksum + (size_t)d.slot * A.gdim * 2;
+    if (g < G) {
+        const double y = (i128_to_f64(read_i128(bs + 2 * g)) * 0x1p-64) / (double)d.B;
         ys[g] = y;
         if (A.ybar_debug) A.ybar_debug[g] = y;
     }
-    for (uint32_t i = 1; i < G; ++i) {
-        const double v = ys[i];
-        uint32_t j = i;
-        while (j > 0 && ys[j - 1] > v) {
-            ys[j] = ys[j - 1];
-            --j;
-        }
-        ys[j] = v;
+    __syncthreads();
+    if (g < G) {
+        const double y = ys[g];
+        uint32_t rank = 0;
+        for (uint32_t i = 0; i < G; ++i) rank += ys[i] < y || (ys[i] == y && i < g) ? 1u : 0u;
+        if (rank == (G - 1u) / 2u) ys[kMaxG] = y;
+        if (rank == G / 2u) ys[kMaxG + 1] = y;
     }
-    const double med = (G & 1u) ? ys[G / 2] : 0.5 * (ys[G / 2 - 1] + ys[G / 2]);
-    A.beta[d.slot] = med;
+    __syncthreads();
     if (A.recycle) {
         // every chunk of this query has finished: the slot can be cleared for reuse
-        unsigned long long* w = A.blocksum + (size_t)d.slot * A.gdim * 2;
-        for (uint32_t g = 0; g < 2 * A.gdim; ++g) w[g] = 0ull;
-        A.done[d.slot] = 0u;
+        for (uint32_t i = g; i < 2 * A.gdim; i += blockDim.x) bs[i] = 0ull;
     }
+    if (g != 0) return;
+    const double med = (G & 1u) ? ys[kMaxG] : 0.5 * (ys[kMaxG] + ys[kMaxG + 1]);
+    A.beta[d.slot] = med;
+    if (A.recycle) A.done[d.slot] = 0u;
     if (A.comp_ring) {
         const uint32_t i = atomicAdd(A.comp_count, 1u);
         Completion c;
@@ -63,7 +87,6 @@ __device__ inline void finalize_query(const WalkArgs& A, const QueryDesc& d, dou
         c.beta = med;
         A.comp_ring[i % A.comp_cap] = c;
     }
-    __threadfence();
 }
 
 // The host watchdog's abort flag (host memory, read at system scope; the
@@ -77,45 +100,49 @@ __device__ __forceinline__ bool abort_raised(const WalkArgs& A)
 
 // Part of a split group: add each probe's partial sums to its accumulator; the
 // chunk that brings a probe's replica count to R forms its Q_R. acc holds the
-// exact S1, S2 of the probes [k0, k0 + kc) over this chunk's pc replicas.
+// exact S1, S2 of the probes [k0, k0 + kc) over this chunk's pc replicas. flag:
+// a word of LDS.
 __device__ __forceinline__ void finish_parts(const WalkArgs& A, const QueryDesc& d, uint32_t k0, uint32_t kc,
-                                             uint32_t pc, const unsigned long long* acc, double* ys)
+                                             uint32_t pc, const unsigned long long* acc, double* ys, uint32_t* flag)
 {
     if (threadIdx.x == 0) {
+        uint32_t last = 0;
         for (uint32_t j = 0; j < kc; ++j) {
             const uint32_t k = k0 + j;
             const size_t pi = (size_t)d.psum_base + k;
             unsigned long long* ps = A.psum + pi * 4;
             atomic_add_i128(ps, (i128)(((u128)acc[4 * j + 1] << 64) | (u128)acc[4 * j]));
             atomic_add_i128(ps + 2, (i128)(((u128)acc[4 * j + 3] << 64) | (u128)acc[4 * j + 2]));
-            __threadfence();
+            atomics_performed();
             const uint32_t prev = atomicAdd(A.pcount + pi, pc);
             if (prev + pc == d.R) {
-                __threadfence();
-                const i128 S1 = load_i128(ps);
-                const u128 S2 = (u128)load_i128(ps + 2);
+                const i128 S1 = read_i128(ps);
+                const u128 S2 = (u128)read_i128(ps + 2);
                 const double Q = probe_q(S1, S2, d.R);
                 if (A.q_debug) A.q_debug[k] = Q;
                 atomic_add_i128(A.blocksum + ((size_t)d.slot * A.gdim + k / d.B) * 2, f64_to_i128_trunc(Q * 0x1p64));
                 // every part of this probe has been added: clear it for reuse
                 ps[0] = ps[1] = ps[2] = ps[3] = 0ull;
                 A.pcount[pi] = 0u;
-                __threadfence();
+                atomics_performed();
                 const uint32_t old = atomicAdd(A.done + d.slot, 1u);
-                if (old + 1u == d.K()) {
-                    __threadfence();
-                    finalize_query(A, d, ys);
-                }
+                if (old + 1u == d.K()) last = 1;
             }
         }
+        *flag = last;
     }
+    __syncthreads();
+    const bool last = *flag != 0u;
+    __syncthreads();
+    if (last) finalize_query(A, d, ys);
     __syncthreads();
 }
 
 // Whole probes [k0, k0 + kc): each forms its Q_R from the exact sums in acc and
 // adds it to its block; the one that completes the query forms the median.
 __device__ __forceinline__ void finish_probes(const WalkArgs& A, const QueryDesc& d, uint32_t k0, uint32_t kc,
-                                              const unsigned long long* acc, double* ys, uint32_t threads)
+                                              const unsigned long long* acc, double* ys, uint32_t* flag,
+                                              uint32_t threads)
 {
     for (uint32_t j = threadIdx.x; j < kc; j += threads) {
         const i128 S1 = (i128)(((u128)acc[4 * j + 1] << 64) | (u128)acc[4 * j]);
@@ -125,15 +152,13 @@ __device__ __forceinline__ void finish_probes(const WalkArgs& A, const QueryDesc
         if (A.q_debug) A.q_debug[k] = Q;
         atomic_add_i128(A.blocksum + ((size_t)d.slot * A.gdim + k / d.B) * 2, f64_to_i128_trunc(Q * 0x1p64));
     }
-    __threadfence();
+    atomics_performed();
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const uint32_t old = atomicAdd(A.done + d.slot, kc);
-        if (old + kc == d.K()) {
-            __threadfence();
-            finalize_query(A, d, ys);
-        }
-    }
+    if (threadIdx.x == 0) *flag = atomicAdd(A.done + d.slot, kc) + kc == d.K() ? 1u : 0u;
+    __syncthreads();
+    const bool last = *flag != 0u;
+    __syncthreads();
+    if (last) finalize_query(A, d, ys);
     __syncthreads();
 }
 

@@ -503,11 +503,4 @@ __device__ __forceinline__ void atomic_add_i128(unsigned long long* p, i128 v)
     atomicAdd(p + 1, hi + carry);
 }
 
-__device__ __forceinline__ i128 load_i128(const unsigned long long* p)
-{
-    const unsigned long long lo = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned long long hi = __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return (i128)(((u128)hi << 64) | (u128)lo);
-}
-
 }  // namespace pw

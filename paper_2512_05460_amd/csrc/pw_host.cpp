@@ -394,13 +394,13 @@ void plan_sign_shapes(const SignTables& mem, const SignTables& lds, uint32_t M, 
         const uint64_t fixed = form ? 4ull * (t.nblk + t.idw) : 16ull * t.nblk;
         const uint64_t per = 4ull * t.tabw + 32;  // a table and its two sums
         for (int i = 0; i < kSignShapes; ++i) {
-            if (fixed + std::max<uint64_t>(M * per, M * 32 + kMaxG * 8) > budget[i]) continue;
+            if (fixed + std::max<uint64_t>(M * per, M * 32 + (kMaxG + 2) * 8) > budget[i]) continue;
             SignShape& s = out[i];
             s.lds = form;
             s.threads = threads[i];
             s.per_cu = per_cu[i];
             s.T = (uint32_t)std::min<uint64_t>(64, (budget[i] - fixed) / per);
-            s.bytes = (uint32_t)(fixed + std::max<uint64_t>(s.T * per, s.T * 32 + kMaxG * 8));
+            s.bytes = (uint32_t)(fixed + std::max<uint64_t>(s.T * per, s.T * 32 + (kMaxG + 2) * 8));
             found = true;
         }
     }
@@ -1426,7 +1426,12 @@ void build_batch(const bd_graph* g, int64_t nq, const int32_t* s, const int32_t*
     if (ex.mode != BD_MODE_PLAIN && spread_chunks && ex.chunk_pairs <= 0 && ex.chunk_probes <= 0) {
         double total[2] = {0.0, 0.0};
         auto walk_pairs = [&](const QueryDesc& d) { return (double)Groups(d).n * d.R * ((double)d.L + 1.0); };
-        for (size_t q = 0; q < b.qd.size(); ++q) total[sign_part(b.part[q]) ? 0 : 1] += walk_pairs(b.qd[q]);
+        double pairs_of[2] = {0.0, 0.0};
+        for (size_t q = 0; q < b.qd.size(); ++q) {
+            const int f = sign_part(b.part[q]) ? 0 : 1;
+            total[f] += walk_pairs(b.qd[q]);
+            pairs_of[f] += (double)Groups(b.qd[q]).n * b.qd[q].R;
+        }
         double lane_steps[2] = {0.0, 0.0};  // of every lane of the device
         uint32_t wg[2] = {0, 0};
         for (const int f : {0, 1}) {
@@ -1439,7 +1444,10 @@ void build_batch(const bd_graph* g, int64_t nq, const int32_t* s, const int32_t*
             const QueryDesc& d = b.qd[q];
             const int f = sign_part(b.part[q]) ? 0 : 1;
             const double passes = std::max(1.0, std::floor(lane_steps[f] / (6.0 * ((double)d.L + 1.0))));
-            const uint32_t fit = (uint32_t)std::min(passes * wg[f], (double)kSplitReplicas);
+            uint32_t fit = (uint32_t)std::min(passes * wg[f], (double)kSplitReplicas);
+            // (less than a pass where the device has a compute unit for every chunk)
+            const double each = std::ceil(pairs_of[f] / (2.0 * g->cus));
+            if (each < fit) fit = std::max((uint32_t)each, 64u);
             const uint32_t whole = std::min<uint32_t>((d.R + 63u) & ~63u, kSplitReplicas);
             pairs[q] = (int32_t)std::max(fit, whole);
         }

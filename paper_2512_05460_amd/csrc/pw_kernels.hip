@@ -236,7 +236,7 @@ __device__ __forceinline__ void walk_pair_m(const DevGraph& G, const Probe* pr, 
 
 template <int kLayout, int kUniform, int kShare>
 __device__ void run_chunk(const WalkArgs& A, const DevGraph& G, uint32_t ci,
-                          unsigned long long* acc, double* ys)
+                          unsigned long long* acc, double* ys, uint32_t* flag)
 {
     const Chunk c = A.chunks[ci];
     const QueryDesc d = A.qd[c.q];
@@ -402,8 +402,8 @@ __device__ void run_chunk(const WalkArgs& A, const DevGraph& G, uint32_t ci,
     }
     __syncthreads();
 
-    if (c.pc < d.R) finish_parts(A, d, c.k0, c.kc, c.pc, acc, ys);
-    else finish_probes(A, d, c.k0, c.kc, acc, ys, kT);
+    if (c.pc < d.R) finish_parts(A, d, c.k0, c.kc, c.pc, acc, ys, flag);
+    else finish_probes(A, d, c.k0, c.kc, acc, ys, flag, kT);
 }
 
 // kUniform: every chunk of the launch has R >= kUniformMinR (see run_chunk).
@@ -416,7 +416,7 @@ __global__ __launch_bounds__(block_threads(kLayout, kShare),
 walk_kernel(WalkArgs A)
 {
     __shared__ unsigned long long acc[kMaxChunkProbes * 4];
-    __shared__ double ys[kMaxG];
+    __shared__ double ys[kMaxG + 2];
     __shared__ uint32_t next;
     constexpr int kT = block_threads(kLayout, kShare);
     constexpr uint32_t kHubs = hub_nodes(kT, kLayout);
@@ -427,7 +427,7 @@ walk_kernel(WalkArgs A)
         // one read of the abort flag for the whole work group (run_chunk has barriers)
         if (threadIdx.x == 0) next = abort_raised(A) ? 1u : 0u;
         __syncthreads();
-        if (blockIdx.x < A.nchunks && next == 0u) run_chunk<kLayout, kUniform, kShare>(A, G, blockIdx.x, acc, ys);
+        if (blockIdx.x < A.nchunks && next == 0u) run_chunk<kLayout, kUniform, kShare>(A, G, blockIdx.x, acc, ys, &next);
         return;
     }
     // (thread 0 keeps the queue state in LDS, so it holds no registers while
@@ -440,7 +440,7 @@ walk_kernel(WalkArgs A)
         const uint32_t ci = next;
         __syncthreads();
         if (ci >= A.nchunks) break;
-        run_chunk<kLayout, kUniform, kShare>(A, G, ci, acc, ys);
+        run_chunk<kLayout, kUniform, kShare>(A, G, ci, acc, ys, &next);
     }
 }
 

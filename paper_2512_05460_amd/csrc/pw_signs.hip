@@ -32,7 +32,7 @@ namespace pw {
 struct SignLds {
     uint4* blk;                 // nblk block entries; kLds: rows, then the adjacency
     unsigned long long* acc;    // T x {S1, S2}
-    uint32_t* tab;              // T tables of tabw words (kMaxG doubles at least)
+    uint32_t* tab;              // T tables of tabw words (kMaxG + 2 doubles at least)
 };
 
 template <int kLds>
@@ -191,7 +191,7 @@ __device__ __forceinline__ void sign_pair(const SignTables& S, const SignLds& M,
 }
 
 template <int kLds, int kUniform, int kShare>
-__device__ __forceinline__ void sign_chunk(const WalkArgs& A, const SignLds& M, uint32_t ci)
+__device__ __forceinline__ void sign_chunk(const WalkArgs& A, const SignLds& M, uint32_t ci, uint32_t* flag)
 {
     double* ys = reinterpret_cast<double*>(M.tab);  // block means, once the tables have been used
     const Chunk c = A.chunks[ci];
@@ -266,8 +266,8 @@ __device__ __forceinline__ void sign_chunk(const WalkArgs& A, const SignLds& M, 
             }
         }
         __syncthreads();
-        if (c.pc < d.R) finish_parts(A, d, kA, kn, c.pc, M.acc, ys);
-        else finish_probes(A, d, kA, kn, M.acc, ys, kT);
+        if (c.pc < d.R) finish_parts(A, d, kA, kn, c.pc, M.acc, ys, flag);
+        else finish_probes(A, d, kA, kn, M.acc, ys, flag, kT);
     }
 }
 
@@ -288,7 +288,7 @@ __global__ __launch_bounds__(1024, kShare == 1 ? 8 : 4) void sign_kernel(WalkArg
     if (!A.persistent) {
         if (threadIdx.x == 0) next = abort_raised(A) ? 1u : 0u;
         __syncthreads();
-        if (blockIdx.x < A.nchunks && next == 0u) sign_chunk<kLds, kUniform, kShare>(A, M, blockIdx.x);
+        if (blockIdx.x < A.nchunks && next == 0u) sign_chunk<kLds, kUniform, kShare>(A, M, blockIdx.x, &next);
         return;
     }
     if (threadIdx.x == 0) first_queue(A, qstate);
@@ -298,7 +298,7 @@ __global__ __launch_bounds__(1024, kShare == 1 ? 8 : 4) void sign_kernel(WalkArg
         const uint32_t ci = next;
         __syncthreads();
         if (ci >= A.nchunks) break;
-        sign_chunk<kLds, kUniform, kShare>(A, M, ci);
+        sign_chunk<kLds, kUniform, kShare>(A, M, ci, &next);
     }
 }
 
