@@ -33,7 +33,7 @@ __device__ __forceinline__ void lds_add_i128(unsigned long long* p, i128 v)
 // split-probe sums, counters), read back by atomic loads, so this order is all
 // they need; everything else a query leaves is read after the launch. A
 // device-scope fence here instead also writes the XCD's whole L2 back and
-// invalidates it: at L = 1 and R = 100 it made 480 us of what takes FENCE_US us.
+// invalidates it: at L = 1 and R = 100 it made 480 us of what takes 261 us.
 __device__ __forceinline__ void atomics_performed()
 {
     asm volatile("" ::: "memory");
@@ -78,7 +78,7 @@ __device__ inline void finalize_query(const WalkArgs& A, const QueryDesc& d, dou
     if (g != 0) return;
     const double med = (G & 1u) ? ys[kMaxG] : 0.5 * (ys[kMaxG] + ys[kMaxG + 1]);
     A.beta[d.slot] = med;
-    if (A.recycle) A.done[d.slot] = 0u;
+    if (A.recycle) A.done[(size_t)d.slot * A.done_stride] = 0u;
     if (A.comp_ring) {
         const uint32_t i = atomicAdd(A.comp_count, 1u);
         Completion c;
@@ -125,7 +125,7 @@ __device__ __forceinline__ void finish_parts(const WalkArgs& A, const QueryDesc&
                 ps[0] = ps[1] = ps[2] = ps[3] = 0ull;
                 A.pcount[pi] = 0u;
                 atomics_performed();
-                const uint32_t old = atomicAdd(A.done + d.slot, 1u);
+                const uint32_t old = atomicAdd(A.done + (size_t)d.slot * A.done_stride, 1u);
                 if (old + 1u == d.K()) last = 1;
             }
         }
@@ -154,7 +154,7 @@ __device__ __forceinline__ void finish_probes(const WalkArgs& A, const QueryDesc
     }
     atomics_performed();
     __syncthreads();
-    if (threadIdx.x == 0) *flag = atomicAdd(A.done + d.slot, kc) + kc == d.K() ? 1u : 0u;
+    if (threadIdx.x == 0) *flag = atomicAdd(A.done + (size_t)d.slot * A.done_stride, kc) + kc == d.K() ? 1u : 0u;
     __syncthreads();
     const bool last = *flag != 0u;
     __syncthreads();
@@ -162,10 +162,13 @@ __device__ __forceinline__ void finish_probes(const WalkArgs& A, const QueryDesc
     __syncthreads();
 }
 
-// Claim chunks from the queue of this XCD first, then from the others in
-// turn. A queue seen empty stays empty (its cursor only grows), so each
-// work group makes at most nqueues failed claims and every wave exits.
-// qstate: the current queue and how many were found empty.
+// Claim chunks from the queue of this XCD first, then from the others in turn.
+// A queue seen empty stays empty (its cursor only grows), so each work group
+// makes at most nqueues failed claims and every wave exits. Once its own queue
+// is empty a work group reads the other cursors before it adds to them: at the
+// end of a launch every work group would otherwise add to every cursor in
+// vain, thousands of additions to a few words one after another.
+// qstate: the current queue and the set of those found empty.
 __device__ __forceinline__ void first_queue(const WalkArgs& A, uint32_t* qstate)
 {
     uint32_t xcc = 0;
@@ -176,21 +179,28 @@ __device__ __forceinline__ void first_queue(const WalkArgs& A, uint32_t* qstate)
 
 __device__ __forceinline__ uint32_t claim_chunk(const WalkArgs& A, uint32_t* qstate)
 {
+    const uint32_t all = (1u << A.nqueues) - 1u;
     uint32_t ci = 0xFFFFFFFFu;
-    uint32_t qi = qstate[0], tried = qstate[1];
-    if (abort_raised(A)) tried = A.nqueues;  // take no further chunk
-    while (tried < A.nqueues) {
-        const uint32_t beg = A.qoff[qi];
-        const uint32_t c = atomicAdd(A.cursor + qi, 1u);
-        if (c < A.qoff[qi + 1] - beg) {
-            ci = beg + c;
-            break;
+    uint32_t qi = qstate[0], empty = qstate[1];
+    if (abort_raised(A)) empty = all;  // take no further chunk
+    while (empty != all) {
+        if (!(empty >> qi & 1u)) {
+            const uint32_t beg = A.qoff[qi];
+            const uint32_t c = atomicAdd(A.cursor + qi * A.cursor_stride, 1u);
+            if (c < A.qoff[qi + 1] - beg) {
+                ci = beg + c;
+                break;
+            }
+            empty |= 1u << qi;
+            for (uint32_t i = 0; i < A.nqueues; ++i)
+                if (__hip_atomic_load(A.cursor + i * A.cursor_stride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >=
+                    A.qoff[i + 1] - A.qoff[i])
+                    empty |= 1u << i;
         }
         qi = qi + 1 == A.nqueues ? 0u : qi + 1;
-        ++tried;
     }
     qstate[0] = qi;
-    qstate[1] = tried;
+    qstate[1] = empty;
     return ci;
 }
 

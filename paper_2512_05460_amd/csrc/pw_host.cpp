@@ -110,7 +110,12 @@ double now_ms()
 // Work buffers of bd_query_batch, kept with the graph and grown on demand, and
 // the captured hipGraph of the last batched launch shape.
 struct Workspace {
-    DevBuf qd, chunks, bs, done, beta, cursor, psum, pcount, qdbg, ydbg;
+    DevBuf in, zeroed, beta, qdbg, ydbg;
+    hipEvent_t ev[2] = {nullptr, nullptr};  // around the walk launches of a call
+    // pinned staging of a call's descriptors, chunks and results (up to kStaged bytes)
+    static constexpr size_t kStaged = size_t(4) << 20;
+    void* staged = nullptr;
+    size_t staged_bytes = 0;
     hipStream_t gstream = nullptr;
     hipGraphExec_t gexec = nullptr;
     std::vector<uint64_t> gkey;
@@ -118,6 +123,34 @@ struct Workspace {
     // the watchdog's abort flag: host memory mapped for the device
     uint32_t* abort_host = nullptr;
     uint32_t* abort_dev = nullptr;
+    int ensure_events()
+    {
+        for (hipEvent_t& e : ev)
+            if (!e && hipEventCreate(&e) != hipSuccess) {
+                e = nullptr;
+                (void)hipGetLastError();
+                return BD_E_HIP;
+            }
+        return BD_OK;
+    }
+    // `bytes` of pinned memory, or null where they are too many or cannot be had
+    // (the copies then come from pageable memory)
+    char* stage(size_t bytes)
+    {
+        if (bytes > kStaged) return nullptr;
+        if (bytes > staged_bytes) {
+            if (staged) (void)hipHostFree(staged);
+            staged = nullptr;
+            staged_bytes = std::min(kStaged, std::max<size_t>(2 * bytes, 65536));
+            if (hipHostMalloc(&staged, staged_bytes, hipHostMallocDefault) != hipSuccess) {
+                (void)hipGetLastError();
+                staged = nullptr;
+                staged_bytes = 0;
+                return nullptr;
+            }
+        }
+        return static_cast<char*>(staged);
+    }
     int ensure(DevBuf& b, size_t bytes)
     {
         if (b.p && b.bytes >= bytes) return BD_OK;
@@ -147,6 +180,9 @@ struct Workspace {
         if (gexec) (void)hipGraphExecDestroy(gexec);
         if (gstream) (void)hipStreamDestroy(gstream);
         if (abort_host) (void)hipHostFree(abort_host);
+        if (staged) (void)hipHostFree(staged);
+        for (hipEvent_t e : ev)
+            if (e) (void)hipEventDestroy(e);
     }
 };
 
@@ -1100,58 +1136,88 @@ struct Batch {
 };
 
 // Device buffers of one batch: either the graph's workspace (grown on demand)
-// or a carving of the library's fixed scratch array (no allocation).
+// or a carving of the library's fixed scratch array (no allocation). The
+// descriptors and the chunk table lie one after the other, and so do the
+// buffers that every launch needs zeroed.
 struct WorkPtrs {
-    void *qd = nullptr, *chunks = nullptr, *bs = nullptr, *done = nullptr, *beta = nullptr, *cursor = nullptr,
-         *psum = nullptr, *pcount = nullptr, *qdbg = nullptr, *ydbg = nullptr;
+    void *qd = nullptr, *chunks = nullptr, *bs = nullptr, *done = nullptr, *cursor = nullptr, *psum = nullptr,
+         *pcount = nullptr, *beta = nullptr, *qdbg = nullptr, *ydbg = nullptr;
+    size_t zero_bytes = 0;  // from bs on
+    uint32_t cursor_stride = 1, done_stride = 1;
 };
 
+// Counters a line apart, for as many queries as that costs little.
+constexpr uint32_t kApart = 32;
+uint32_t done_apart(const Batch& b) { return b.qd.size() <= 4096 ? kApart : 1; }
+
+constexpr size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
+
 // Bytes of each buffer a batch needs (in WorkPtrs order).
-void work_sizes(const Batch& b, bool qdbg, bool ydbg, size_t sz[10])
+void work_sizes(const Batch& b, bool qdbg, bool ydbg, const WorkPtrs& wp, size_t sz[10])
 {
     const size_t nv = b.qd.size();
     sz[0] = nv * sizeof(QueryDesc);
     sz[1] = b.chunks.size() * sizeof(Chunk);
     sz[2] = nv * (size_t)b.G * 16;
-    sz[3] = nv * 4;
-    sz[4] = nv * 8;
-    sz[5] = kKernelParts * kMaxQueues * 4;
-    sz[6] = (size_t)b.split_probes * 32;
-    sz[7] = (size_t)b.split_probes * 4;
+    sz[3] = nv * 4 * wp.done_stride;
+    sz[4] = kKernelParts * kMaxQueues * 4 * wp.cursor_stride;
+    sz[5] = (size_t)b.split_probes * 32;
+    sz[6] = (size_t)b.split_probes * 4;
+    sz[7] = nv * 8;
     sz[8] = qdbg ? (size_t)b.qd[0].K() * 8 : 0;
     sz[9] = ydbg ? (size_t)b.G * 8 : 0;
+    for (int i = 0; i < 8; ++i) sz[i] = align256(std::max<size_t>(sz[i], 16));
+}
+
+// The buffers [first, last) of sz one after another from base on.
+void lay_out(void* base, const size_t sz[10], int first, int last, WorkPtrs* wp)
+{
+    void** out[8] = {&wp->qd, &wp->chunks, &wp->bs, &wp->done, &wp->cursor, &wp->psum, &wp->pcount, &wp->beta};
+    char* p = static_cast<char*>(base);
+    for (int i = first; i < last; ++i) {
+        *out[i] = p;
+        p += sz[i];
+    }
 }
 
 int workspace_ptrs(Workspace& w, const Batch& b, bool qdbg, bool ydbg, WorkPtrs* wp)
 {
     size_t sz[10];
-    work_sizes(b, qdbg, ydbg, sz);
-    DevBuf* bufs[10] = {&w.qd, &w.chunks, &w.bs, &w.done, &w.beta, &w.cursor, &w.psum, &w.pcount, &w.qdbg, &w.ydbg};
-    void** out[10] = {&wp->qd, &wp->chunks, &wp->bs, &wp->done, &wp->beta, &wp->cursor, &wp->psum, &wp->pcount,
-                      &wp->qdbg, &wp->ydbg};
-    for (int i = 0; i < 10; ++i) {
-        if (i >= 8 && sz[i] == 0) continue;
-        const int rc = w.ensure(*bufs[i], sz[i]);
-        if (rc != BD_OK) return rc;
-        *out[i] = bufs[i]->p;
-    }
+    wp->cursor_stride = kApart;
+    wp->done_stride = done_apart(b);
+    work_sizes(b, qdbg, ydbg, *wp, sz);
+    const size_t zero = sz[2] + sz[3] + sz[4] + sz[5] + sz[6];
+    int rc = w.ensure(w.in, sz[0] + sz[1]);
+    if (rc == BD_OK) rc = w.ensure(w.zeroed, zero);
+    if (rc == BD_OK) rc = w.ensure(w.beta, sz[7]);
+    if (rc == BD_OK && qdbg) rc = w.ensure(w.qdbg, sz[8]);
+    if (rc == BD_OK && ydbg) rc = w.ensure(w.ydbg, sz[9]);
+    if (rc != BD_OK) return rc;
+    lay_out(w.in.p, sz, 0, 2, wp);
+    lay_out(w.zeroed.p, sz, 2, 7, wp);
+    wp->beta = w.beta.p;
+    wp->qdbg = w.qdbg.p;
+    wp->ydbg = w.ydbg.p;
+    wp->zero_bytes = zero;
     return BD_OK;
 }
 
 // The buffers laid out one after another, each 256-byte aligned, inside
-// [base, base + cap). BD_E_SCRATCH when they do not fit.
-int carve_ptrs(void* base, size_t cap, const Batch& b, WorkPtrs* wp)
+// [base, base + cap), with the counters apart or, where that does not fit, side
+// by side. BD_E_SCRATCH when they do not fit.
+int carve_ptrs(void* base, size_t cap, const Batch& b, WorkPtrs* wp, bool apart = true)
 {
     size_t sz[10];
-    work_sizes(b, false, false, sz);
-    void** out[8] = {&wp->qd, &wp->chunks, &wp->bs, &wp->done, &wp->beta, &wp->cursor, &wp->psum, &wp->pcount};
+    wp->cursor_stride = apart ? kApart : 1;
+    wp->done_stride = apart ? done_apart(b) : 1;
+    work_sizes(b, false, false, *wp, sz);
     size_t off = 0;
     for (int i = 0; i < 8; ++i) {
-        const size_t need = std::max<size_t>(sz[i], 16);
-        if (need > cap || off > cap - need) return BD_E_SCRATCH;
-        *out[i] = static_cast<char*>(base) + off;
-        off += (need + 255) & ~(size_t)255;
+        if (sz[i] > cap || off > cap - sz[i]) return apart ? carve_ptrs(base, cap, b, wp, false) : BD_E_SCRATCH;
+        off += sz[i];
     }
+    lay_out(base, sz, 0, 8, wp);
+    wp->zero_bytes = sz[2] + sz[3] + sz[4] + sz[5] + sz[6];
     return BD_OK;
 }
 
@@ -1193,9 +1259,19 @@ int run_batch(bd_graph* g, const Batch& b, const bd_exec& ex, hipStream_t user_s
     if (graph_mode && !ws.gstream && hipStreamCreateWithFlags(&ws.gstream, hipStreamNonBlocking) != hipSuccess)
         return BD_E_HIP;
     hipStream_t st = graph_mode ? ws.gstream : user_st;
-    HIP_TRY(hipMemcpyAsync(w.qd, b.qd.data(), nv * sizeof(QueryDesc), hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(w.chunks, b.chunks.data(), b.chunks.size() * sizeof(Chunk), hipMemcpyHostToDevice,
-                           st));
+    // descriptors and chunk table in one copy from pinned memory, the results
+    // back into the same where they fit
+    const size_t chunks_at = (size_t)(static_cast<char*>(w.chunks) - static_cast<char*>(w.qd));
+    const size_t in_bytes = chunks_at + b.chunks.size() * sizeof(Chunk);
+    char* stage = owned ? ws.stage(std::max(in_bytes, nv * 8)) : nullptr;
+    if (stage) {
+        std::memcpy(stage, b.qd.data(), nv * sizeof(QueryDesc));
+        std::memcpy(stage + chunks_at, b.chunks.data(), b.chunks.size() * sizeof(Chunk));
+        HIP_TRY(hipMemcpyAsync(w.qd, stage, in_bytes, hipMemcpyHostToDevice, st));
+    } else {
+        HIP_TRY(hipMemcpyAsync(w.qd, b.qd.data(), nv * sizeof(QueryDesc), hipMemcpyHostToDevice, st));
+        HIP_TRY(hipMemcpyAsync(w.chunks, b.chunks.data(), b.chunks.size() * sizeof(Chunk), hipMemcpyHostToDevice, st));
+    }
 
     WalkArgs a{};
     a.g = tables(g);
@@ -1204,6 +1280,8 @@ int run_batch(bd_graph* g, const Batch& b, const bd_exec& ex, hipStream_t user_s
     a.cursor = static_cast<uint32_t*>(w.cursor);
     a.blocksum = static_cast<unsigned long long*>(w.bs);
     a.done = static_cast<uint32_t*>(w.done);
+    a.cursor_stride = w.cursor_stride;
+    a.done_stride = w.done_stride;
     a.psum = static_cast<unsigned long long*>(w.psum);
     a.pcount = static_cast<uint32_t*>(w.pcount);
     a.beta = static_cast<double*>(w.beta);
@@ -1212,12 +1290,7 @@ int run_batch(bd_graph* g, const Batch& b, const bd_exec& ex, hipStream_t user_s
     a.abort_flag = watch ? g->ws.abort_dev : nullptr;
     // the zeroing every launch needs
     auto zero_all = [&](hipStream_t s2) -> int {
-        if (launch_zero(w.bs, nv * gdim * 16, s2) != hipSuccess) return BD_E_HIP;
-        if (launch_zero(w.done, nv * 4, s2) != hipSuccess) return BD_E_HIP;
-        if (launch_zero(w.cursor, kKernelParts * kMaxQueues * 4, s2) != hipSuccess) return BD_E_HIP;
-        if (launch_zero(w.psum, (size_t)b.split_probes * 32, s2) != hipSuccess) return BD_E_HIP;
-        if (launch_zero(w.pcount, (size_t)b.split_probes * 4, s2) != hipSuccess) return BD_E_HIP;
-        return BD_OK;
+        return launch_zero(w.bs, w.zero_bytes, s2) == hipSuccess ? BD_OK : BD_E_HIP;
     };
     // a launch of one kernel part
     auto launch_part = [&](WalkArgs& aw, int part, int shape, uint32_t grid, hipStream_t s2) -> int {
@@ -1237,8 +1310,9 @@ int run_batch(bd_graph* g, const Batch& b, const bd_exec& ex, hipStream_t user_s
             WalkArgs ab = a;
             ab.chunks = static_cast<const Chunk*>(w.chunks) + b.part_begin[part];
             ab.nchunks = b.part_begin[part + 1] - b.part_begin[part];
-            ab.cursor = static_cast<uint32_t*>(w.cursor) + part * kMaxQueues;
-            ab.persistent = 1;
+            ab.cursor = static_cast<uint32_t*>(w.cursor) + part * kMaxQueues * w.cursor_stride;
+            // (a work group for every chunk: nothing to claim)
+            ab.persistent = grids[part] < ab.nchunks ? 1 : 0;
             ab.nqueues = b.nqueues;
             for (uint32_t i = 0; i <= b.nqueues; ++i) ab.qoff[i] = b.qoff[part][i];
             const int rc = launch_part(ab, part, b.shape, grids[part], s2);
@@ -1247,58 +1321,68 @@ int run_batch(bd_graph* g, const Batch& b, const bd_exec& ex, hipStream_t user_s
         return BD_OK;
     };
 
-    hipEvent_t e0 = nullptr, e1 = nullptr;
     if (owned) {
-        HIP_TRY(hipEventCreate(&e0));
-        if (hipEventCreate(&e1) != hipSuccess) {
-            (void)hipEventDestroy(e0);
-            return BD_E_HIP;
-        }
+        const int rc = ws.ensure_events();
+        if (rc != BD_OK) return rc;
     }
+    hipEvent_t e0 = owned ? ws.ev[0] : nullptr, e1 = owned ? ws.ev[1] : nullptr;
     double kernel_ms = 0.0;
     int64_t launches = 0;
     int status = BD_OK;
-    auto timed = [&](auto&& body) -> int {
-        if (e0 && hipEventRecord(e0, st) != hipSuccess) return BD_E_HIP;
-        const int r = body();
-        if (r != BD_OK) return r;
-        ++launches;
-        if (!e0) return BD_OK;
-        if (hipEventRecord(e1, st) != hipSuccess) return BD_E_HIP;
-        if (watch) {
-            // poll, raising the abort flag once the deadline has passed; a
-            // raised flag ends the launch within one chunk per work group
-            for (;;) {
-                const hipError_t q = hipEventQuery(e1);
-                if (q == hipSuccess) break;
-                if (q != hipErrorNotReady) return BD_E_HIP;
-                past_deadline();
-                std::this_thread::sleep_for(std::chrono::microseconds(200));
-            }
-            (void)hipGetLastError();  // the not-ready answers are no error
-        } else if (hipEventSynchronize(e1) != hipSuccess) {
-            return BD_E_HIP;
-        }
+    auto elapsed = [&]() -> int {
         float ms = 0.f;
         if (hipEventElapsedTime(&ms, e0, e1) != hipSuccess) return BD_E_HIP;
         kernel_ms += ms;
         return BD_OK;
     };
+    // the launches of `body` between the events; under the watchdog their end is awaited
+    auto timed = [&](auto&& body) -> int {
+        if (e0 && hipEventRecord(e0, st) != hipSuccess) return BD_E_HIP;
+        const int r = body();
+        if (r != BD_OK) return r;
+        if (!e0) return BD_OK;
+        if (hipEventRecord(e1, st) != hipSuccess) return BD_E_HIP;
+        if (!watch) return BD_OK;
+        // poll, raising the abort flag once the deadline has passed; a
+        // raised flag ends the launch within one chunk per work group
+        for (;;) {
+            const hipError_t q = hipEventQuery(e1);
+            if (q == hipSuccess) break;
+            if (q != hipErrorNotReady) return BD_E_HIP;
+            past_deadline();
+            std::this_thread::sleep_for(std::chrono::microseconds(200));
+        }
+        (void)hipGetLastError();  // the not-ready answers are no error
+        return elapsed();
+    };
     if (ex.mode == BD_MODE_PLAIN) {
         status = zero_all(st);
         // one query per launch, one work group per chunk
-        for (size_t q = 0; q < nv && status == BD_OK; ++q) {
-            if (past_deadline()) break;  // the remaining queries are not launched
+        auto launch_query = [&](size_t q) -> int {
             const uint32_t c0 = b.chunk_begin[q];
             const uint32_t c1 = q + 1 < nv ? b.chunk_begin[q + 1] : (uint32_t)b.chunks.size();
             WalkArgs aq = a;
             aq.chunks = static_cast<const Chunk*>(w.chunks) + c0;
             aq.nchunks = c1 - c0;
             aq.persistent = 0;
-            status = timed([&] { return launch_part(aq, b.part[q], b.shapes[q], c1 - c0, st); });
+            ++launches;
+            return launch_part(aq, b.part[q], b.shapes[q], c1 - c0, st);
+        };
+        if (watch) {
+            for (size_t q = 0; q < nv && status == BD_OK; ++q) {
+                if (past_deadline()) break;  // the remaining queries are not launched
+                status = timed([&] { return launch_query(q); });
+            }
+        } else if (status == BD_OK) {
+            status = timed([&] {
+                int rc = BD_OK;
+                for (size_t q = 0; q < nv && rc == BD_OK; ++q) rc = launch_query(q);
+                return rc;
+            });
         }
     } else if (!graph_mode) {
         status = zero_all(st);
+        launches = 1;
         if (status == BD_OK) status = timed([&] { return launch_persistent(st); });
     } else {
         // key: everything the captured launches depend on
@@ -1307,7 +1391,8 @@ int run_batch(bd_graph* g, const Batch& b, const bd_exec& ex, hipStream_t user_s
                                      (uint64_t)(uintptr_t)w.qd, (uint64_t)(uintptr_t)w.chunks,
                                      (uint64_t)(uintptr_t)w.bs, (uint64_t)(uintptr_t)w.psum,
                                      (uint64_t)(uintptr_t)w.pcount, (uint64_t)(uintptr_t)w.done,
-                                     (uint64_t)(uintptr_t)w.beta, (uint64_t)(uintptr_t)w.cursor};
+                                     (uint64_t)(uintptr_t)w.beta, (uint64_t)(uintptr_t)w.cursor,
+                                     w.cursor_stride, w.done_stride};
         for (int part = 0; part < kKernelParts; ++part) {
             key.push_back(b.part_begin[part + 1]);
             key.push_back(grids[part]);
@@ -1337,28 +1422,33 @@ int run_batch(bd_graph* g, const Batch& b, const bd_exec& ex, hipStream_t user_s
             ws.gkey = key;
             ++ws.graph_builds;
         }
+        launches = 1;
         status = timed([&] { return hipGraphLaunch(ws.gexec, st) == hipSuccess ? BD_OK : BD_E_HIP; });
         ++ws.graph_replays;
     }
-    if (e0) (void)hipEventDestroy(e0);
-    if (e1) (void)hipEventDestroy(e1);
-    if (status != BD_OK) return status;
+    if (status != BD_OK) {
+        (void)hipStreamSynchronize(st);  // the copies in read the caller's vectors or the staging memory
+        return status;
+    }
     beta.resize(nv);
-    HIP_TRY(hipMemcpyAsync(beta.data(), w.beta, nv * 8, hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipMemcpyAsync(stage ? (void*)stage : (void*)beta.data(), w.beta, nv * 8, hipMemcpyDeviceToHost, st));
     if (q_dbg_host)
         HIP_TRY(hipMemcpyAsync(q_dbg_host, w.qdbg, (size_t)b.qd[0].K() * 8, hipMemcpyDeviceToHost, st));
     if (y_dbg_host) HIP_TRY(hipMemcpyAsync(y_dbg_host, w.ydbg, gdim * 8, hipMemcpyDeviceToHost, st));
     std::vector<uint32_t> done_count;
     if (fired) {
         // which queries the aborted launches finished: those whose probe count reached K
-        done_count.resize(nv);
-        HIP_TRY(hipMemcpyAsync(done_count.data(), w.done, nv * 4, hipMemcpyDeviceToHost, st));
+        done_count.resize(nv * w.done_stride);
+        HIP_TRY(hipMemcpyAsync(done_count.data(), w.done, done_count.size() * 4, hipMemcpyDeviceToHost, st));
     }
     HIP_TRY(hipStreamSynchronize(st));
+    if (stage) std::memcpy(beta.data(), stage, nv * 8);
+    if (e0 && !watch && elapsed() != BD_OK) return BD_E_HIP;
     if (watch) __atomic_store_n(g->ws.abort_host, 0u, __ATOMIC_SEQ_CST);
     if (incomplete) {
         incomplete->assign(nv, 0);
-        for (size_t q = 0; q < done_count.size(); ++q) (*incomplete)[q] = done_count[q] != b.qd[q].K();
+        for (size_t q = 0; q < done_count.size() / w.done_stride; ++q)
+            (*incomplete)[q] = done_count[q * w.done_stride] != b.qd[q].K();
     }
     if (stats) {
         stats->walk_kernel_ms += kernel_ms;
@@ -1687,11 +1777,11 @@ extern "C" int bd_truncated_beta(bd_graph* g, int64_t nq, const int32_t* s, cons
                 pairs[q] = SeriesPair{g->sid4[storage_id(g, a)] / 4u, g->sid4[storage_id(g, b)] / 4u, inverse_degree(a),
                                       -inverse_degree(b)};
             }
-            int rc = g->ws.ensure(g->ws.qd, Q * sizeof(SeriesPair));
+            int rc = g->ws.ensure(g->ws.in, Q * sizeof(SeriesPair));
             if (rc == BD_OK) rc = g->ws.ensure(g->ws.beta, Q * 8);
             if (rc != BD_OK) return rc;
-            HIP_TRY(hipMemcpyAsync(g->ws.qd.p, pairs.data(), Q * sizeof(SeriesPair), hipMemcpyHostToDevice, st));
-            HIP_TRY(launch_series_small(lt.blk, lt.nblk, lt.idw, n, (uint32_t)Q, L, g->ws.qd.as<const SeriesPair>(),
+            HIP_TRY(hipMemcpyAsync(g->ws.in.p, pairs.data(), Q * sizeof(SeriesPair), hipMemcpyHostToDevice, st));
+            HIP_TRY(launch_series_small(lt.blk, lt.nblk, lt.idw, n, (uint32_t)Q, L, g->ws.in.as<const SeriesPair>(),
                                         g->ws.beta.as<double>(), st));
             HIP_TRY(hipMemcpyAsync(beta_L + q0, g->ws.beta.p, Q * 8, hipMemcpyDeviceToHost, st));
             HIP_TRY(hipStreamSynchronize(st));
@@ -2542,6 +2632,7 @@ int launch_slice(bd_server* S, Slice& sl)
     a.cursor = sl.d_cursor.as<uint32_t>();
     a.blocksum = S->d_bs.as<unsigned long long>();
     a.done = S->d_done.as<uint32_t>();
+    a.cursor_stride = a.done_stride = 1;
     a.psum = S->d_psum.as<unsigned long long>();
     a.pcount = S->d_pcount.as<uint32_t>();
     a.beta = S->d_beta.as<double>();
