@@ -41,6 +41,7 @@ constexpr int64_t kAutoCompactBytes = int64_t(12) << 20;
 // steps/s with 20.7 GB of tables (Chung-Lu n=4e7), -3.5% with 2.2 GB (n=1e7)
 // and -46% with 192 MB (the grid, whose locality lives in the caches).
 constexpr int64_t kFatNontemporalBytes = int64_t(4) << 30;
+constexpr int64_t kAllL2Bytes = int64_t(32) << 20;  // the eight XCDs' L2s
 
 #define HIP_TRY(expr)                                  \
     do {                                               \
@@ -414,6 +415,27 @@ int resident_wgs(const bd_graph* g, int part, int share, int shape)
 uint32_t storage_id(const bd_graph* g, int32_t v)
 {
     return g->internal.empty() ? (uint32_t)v : g->internal[(size_t)v];
+}
+
+// Work groups of a persistent launch of the general kernels, at most the
+// resident ones. Two 256-thread groups per CU already keep enough reads in
+// flight (Chung-Lu-like graphs of 1e5 to 1e7 nodes and the grid run within 2% of
+// the full device's rate or above it), and every further one brings other
+// queries' neighbourhoods into the same L2. Queries with fewer pairs than an XCD
+// then runs at once get one group per CU: 1,024 grid queries of 1,332 pairs took
+// 78.5 ms on all resident groups, 49.7 on two and 33.3 on one, and one costs a
+// single large query 2%. The 1,024-thread kernels do the same only where
+// their tables exceed the L2s together (the grid 46.3 ms on two, 35.0 on one):
+// within L2 their two groups hide its latency. Walk sharing, bound by the
+// probes' arithmetic, keeps all.
+int persistent_wgs(const bd_graph* g, int part, int share, int shape, double pairs_per_query)
+{
+    const int r = resident_wgs(g, part, share, shape);
+    if (sign_part(part) || share > 1) return r;
+    const int threads = block_threads(run_kernel(g, share), share), cus = (int)g->cus;
+    const bool small = pairs_per_query <= (double)cus / kMaxQueues * threads;
+    if (threads == kBlockThreads) return std::min(r, small ? cus : 2 * cus);
+    return small && g->device_bytes > kAllL2Bytes ? std::min(r, cus) : r;
 }
 
 // Launch shapes of the sign-table kernels for M probes per walk: four to one
@@ -1128,6 +1150,7 @@ struct Batch {
     std::vector<uint8_t> part;          // per valid query, its kernel part
     std::vector<int> shapes;            // per valid query, the sign-table kernels' shape for it (-1: general kernel)
     int shape = 0;                      // the shape of the batched sign-table launches
+    double pairs_per_query = 0.0;       // of the queries on the general kernels
     // chunk queues of the persistent launches: qoff[part][i] is the first chunk
     // of queue i relative to the part
     uint32_t nqueues = 1;
@@ -1301,7 +1324,8 @@ int run_batch(bd_graph* g, const Batch& b, const bd_exec& ex, hipStream_t user_s
     for (int part = 0; part < kKernelParts; ++part) {
         const uint32_t nch = b.part_begin[part + 1] - b.part_begin[part];
         if (nch == 0) continue;
-        uint32_t grid = ex.grid_wgs > 0 ? (uint32_t)ex.grid_wgs : (uint32_t)resident_wgs(g, part, b.share, b.shape);
+        uint32_t grid = ex.grid_wgs > 0 ? (uint32_t)ex.grid_wgs
+                                         : (uint32_t)persistent_wgs(g, part, b.share, b.shape, b.pairs_per_query);
         grids[part] = std::min<uint32_t>(grid, nch);
     }
     auto launch_persistent = [&](hipStream_t s2) -> int {
@@ -1513,22 +1537,25 @@ void build_batch(const bd_graph* g, int64_t nq, const int32_t* s, const int32_t*
     // most compute units idle: 1,024 grid queries of up to L = 5,000 ran 92 ms in
     // chunks of 4,096 pairs and 80 ms so.
     std::vector<int32_t> pairs(b.qd.size(), ex.chunk_pairs);
+    double total[2] = {0.0, 0.0}, pairs_of[2] = {0.0, 0.0};  // walk pairs times steps, walk pairs
+    size_t general = 0;
+    for (size_t q = 0; q < b.qd.size(); ++q) {
+        const QueryDesc& d = b.qd[q];
+        const int f = sign_part(b.part[q]) ? 0 : 1;
+        const double n = (double)Groups(d).n * d.R;
+        total[f] += n * ((double)d.L + 1.0);
+        pairs_of[f] += n;
+        general += f;
+    }
+    b.pairs_per_query = general ? pairs_of[1] / (double)general : 0.0;
     if (ex.mode != BD_MODE_PLAIN && spread_chunks && ex.chunk_pairs <= 0 && ex.chunk_probes <= 0) {
-        double total[2] = {0.0, 0.0};
-        auto walk_pairs = [&](const QueryDesc& d) { return (double)Groups(d).n * d.R * ((double)d.L + 1.0); };
-        double pairs_of[2] = {0.0, 0.0};
-        for (size_t q = 0; q < b.qd.size(); ++q) {
-            const int f = sign_part(b.part[q]) ? 0 : 1;
-            total[f] += walk_pairs(b.qd[q]);
-            pairs_of[f] += (double)Groups(b.qd[q]).n * b.qd[q].R;
-        }
         double lane_steps[2] = {0.0, 0.0};  // of every lane of the device
         uint32_t wg[2] = {0, 0};
         for (const int f : {0, 1}) {
             if (total[f] == 0.0) continue;
             wg[f] = f == 0 ? sign_shape(g, b.share, b.shape).threads : (uint32_t)group_pairs(g->kernel_layout, b.share);
             const int part = f == 0 ? kSignUniform : kWalkAny;
-            lane_steps[f] = total[f] / ((double)resident_wgs(g, part, b.share, b.shape) * wg[f]);
+            lane_steps[f] = total[f] / ((double)persistent_wgs(g, part, b.share, b.shape, b.pairs_per_query) * wg[f]);
         }
         for (size_t q = 0; q < b.qd.size(); ++q) {
             const QueryDesc& d = b.qd[q];
@@ -1560,7 +1587,7 @@ void build_batch(const bd_graph* g, int64_t nq, const int32_t* s, const int32_t*
         // otherwise the kernel that runs any query takes them all
         for (const int part : {kSignUniform, kWalkUniform}) {
             const int i = part == kSignUniform ? 0 : 1;
-            if (!others[i] || uniform_chunks[i] >= (uint64_t)resident_wgs(g, part, b.share, b.shape)) continue;
+            if (!others[i] || uniform_chunks[i] >= (uint64_t)persistent_wgs(g, part, b.share, b.shape, b.pairs_per_query)) continue;
             for (uint8_t& p : b.part)
                 if (p == part) p = (uint8_t)(part + 1);
         }
@@ -2329,6 +2356,12 @@ bd_exec server_exec(const bd_server* S, uint32_t lanes)
     return ex;
 }
 
+// Work groups of a slice's launch (its chunks come from many requests).
+int server_wgs(const bd_server* S, int part, int shape)
+{
+    return persistent_wgs(S->g, part, share_class(policy_share(S->pol)), shape, 1e18);
+}
+
 // Whether the query's replicas are split over chunks (it then needs accumulators).
 bool server_splits(const bd_server* S, const QueryDesc& d)
 {
@@ -2600,7 +2633,7 @@ void fill_slice(bd_server* S, Slice& sl)
     const int share = share_class(policy_share(S->pol));
     for (const int part : {kSignUniform, kWalkUniform}) {
         std::vector<Item>&u = items[part], &any = items[part + 1];
-        if (any.empty() || u.empty() || u.size() >= (size_t)resident_wgs(S->g, part, share, sl.shape)) continue;
+        if (any.empty() || u.empty() || u.size() >= (size_t)server_wgs(S, part, sl.shape)) continue;
         any.insert(any.begin(), u.begin(), u.end());
         u.clear();
     }
@@ -2651,7 +2684,7 @@ int launch_slice(bd_server* S, Slice& sl)
         ap.qoff[0] = 0;
         ap.qoff[1] = ap.nchunks;
         if (ap.nchunks == 0) continue;
-        const uint32_t grid = std::min<uint32_t>((uint32_t)resident_wgs(S->g, part, share, sl.shape), ap.nchunks);
+        const uint32_t grid = std::min<uint32_t>((uint32_t)server_wgs(S, part, sl.shape), ap.nchunks);
         const hipError_t e = launch_kernel(S->g, ap, part, share, sl.shape, grid, st);
         if (e != hipSuccess) return BD_E_HIP;
     }
@@ -2769,8 +2802,8 @@ extern "C" int bd_server_create(bd_graph* g, const bd_server_cfg* cfg, bd_server
         delete S;
         return BD_E_BUDGET;
     }
-    S->resident[0] = resident_wgs(g, kWalkAny, share_class(policy_share(S->pol)), 0);
-    S->resident[1] = resident_wgs(g, kWalkUniform, share_class(policy_share(S->pol)), 0);
+    S->resident[0] = server_wgs(S, kWalkAny, 0);
+    S->resident[1] = server_wgs(S, kWalkUniform, 0);
     int rc = S->d_qd.alloc((size_t)S->slots * sizeof(QueryDesc));
     if (rc == BD_OK) rc = S->d_bs.alloc((size_t)S->slots * S->gdim * 16);
     if (rc == BD_OK) rc = S->d_done.alloc((size_t)S->slots * 4);
