@@ -325,6 +325,13 @@ int upload(DevBuf& b, const std::vector<T>& v, hipStream_t st)
     return BD_OK;
 }
 
+// the words behind `nnz` 3-byte ids, in the 8 bytes that are allocated behind them
+hipError_t zero_pad24(const DevBuf& ids, size_t nnz, hipStream_t st)
+{
+    const size_t from = 3 * nnz & ~(size_t)3;
+    return launch_zero(ids.as<char>() + from, (3 * nnz + 8 - from) & ~(size_t)3, st);
+}
+
 // The caller's CSR on the device: its own arrays, or copies of host ones.
 struct LoadCsr {
     CsrView view{};
@@ -343,13 +350,13 @@ struct LoadCsr {
         return BD_OK;
     }
     // ids in range; with `deep` also simple, sorted, symmetric and connected
-    int check(bool deep, int32_t* bipartite, hipStream_t st) const
+    int check(int64_t nnz, bool deep, int32_t* bipartite, hipStream_t st) const
     {
         DevBuf word, parent;
         int rc = word.alloc(16);
         if (rc != BD_OK) return rc;
         HIP_TRY(launch_zero(word.p, 16, st));
-        HIP_TRY(launch_check(view, deep ? 1 : 0, word.as<uint32_t>(), st));
+        HIP_TRY(launch_check(view, nnz, deep ? 1 : 0, word.as<uint32_t>(), st));
         uint32_t got[2] = {0, 0};
         HIP_TRY(hipMemcpyAsync(got, word.p, 8, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
@@ -357,7 +364,7 @@ struct LoadCsr {
         if (!deep) return BD_OK;
         rc = parent.alloc((size_t)view.n * 8);
         if (rc != BD_OK) return rc;
-        HIP_TRY(launch_components(view, parent.as<uint32_t>(), word.as<uint32_t>() + 1, st));
+        HIP_TRY(launch_components(view, nnz, parent.as<uint32_t>(), word.as<uint32_t>() + 1, st));
         HIP_TRY(hipMemcpyAsync(got, word.p, 8, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
         if (got[1] & 1u) return BD_E_GRAPH;
@@ -567,9 +574,9 @@ int load_sign_tables(bd_graph* g, const std::vector<uint32_t>& order_in, const L
         if (rc == BD_OK) rc = upload(d_rp, rp, st);
         if (rc == BD_OK) rc = g->sids.alloc(3 * nnz + 8);
         if (rc != BD_OK) return rc;
-        HIP_TRY(launch_zero(g->sids.as<char>() + (3 * nnz & ~(size_t)3), 12, st));
-        HIP_TRY(launch_rename(csr.view, d_order.as<const uint32_t>(), d_at.as<const uint32_t>(), d_rp.as<const uint32_t>(),
-                              nullptr, g->sids.as<uint8_t>(), st));
+        HIP_TRY(zero_pad24(g->sids, (size_t)nnz, st));
+        HIP_TRY(launch_rename(csr.view, (uint32_t)nnz, d_order.as<const uint32_t>(), d_at.as<const uint32_t>(),
+                              d_rp.as<const uint32_t>(), nullptr, g->sids.as<uint8_t>(), st));
         HIP_TRY(hipStreamSynchronize(st));
         mem.blk = g->sblk.as<const uint4>();
         mem.pid = g->spid.as<const uint32_t>();
@@ -656,7 +663,7 @@ extern "C" int graph_load_csr(int64_t n, const int64_t* row_ptr, const int32_t* 
     hipStream_t st = (hipStream_t)stream;
     LoadCsr csr;
     int rc = csr.set(n, nnz, on_device ? row_ptr_dev : row_ptr, col_idx, on_device, st);
-    if (rc == BD_OK) rc = csr.check(deep, &bip, st);
+    if (rc == BD_OK) rc = csr.check(nnz, deep, &bip, st);
     if (rc != BD_OK) return rc;
 
     bd_graph* g = new (std::nothrow) bd_graph();
@@ -711,8 +718,8 @@ extern "C" int graph_load_csr(int64_t n, const int64_t* row_ptr, const int32_t* 
     if (rc == BD_OK && (g->layout == 3 || g->layout == 4)) rc = g->node8.alloc(((size_t)n + 1) * 8);
     if (rc == BD_OK && g->layout == 1) rc = g->adj.alloc((size_t)std::max<int64_t>(nnz, 1) * 16);
     if (rc == BD_OK &&
-        ((packed && launch_zero(g->col24.as<char>() + (3 * (size_t)nnz & ~(size_t)3), 12, st) != hipSuccess) ||
-         launch_rename(csr.view, d_order.as<const uint32_t>(), d_internal.as<const uint32_t>(),
+        ((packed && zero_pad24(g->col24, (size_t)nnz, st) != hipSuccess) ||
+         launch_rename(csr.view, (uint32_t)nnz, d_order.as<const uint32_t>(), d_internal.as<const uint32_t>(),
                        g->rp32.as<const uint32_t>(), g->col.as<uint32_t>(), g->col24.as<uint8_t>(), st) != hipSuccess ||
          launch_nodes((uint32_t)n, d_order.as<const uint32_t>(), g->rp32.as<const uint32_t>(), g->node.as<uint4>(),
                       g->node8.as<uint2>(), st) != hipSuccess))

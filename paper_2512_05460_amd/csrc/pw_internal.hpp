@@ -253,11 +253,11 @@ struct CsrView {
     const int32_t* col;
 };
 // *bad (zeroed): bit 0 an id out of range, bit 1 (deep) not simple, sorted and symmetric.
-hipError_t launch_check(const CsrView& g, int deep, uint32_t* bad, hipStream_t st);
+hipError_t launch_check(const CsrView& g, int64_t nnz, int deep, uint32_t* bad, hipStream_t st);
 // parent: 2 n words; *verdict (zeroed): bit 0 not connected, bit 1 not bipartite.
-hipError_t launch_components(const CsrView& g, uint32_t* parent, uint32_t* verdict, hipStream_t st);
-hipError_t launch_rename(const CsrView& g, const uint32_t* order, const uint32_t* map, const uint32_t* rp, uint32_t* ids,
-                         uint8_t* ids24, hipStream_t st);
+hipError_t launch_components(const CsrView& g, int64_t nnz, uint32_t* parent, uint32_t* verdict, hipStream_t st);
+hipError_t launch_rename(const CsrView& g, uint32_t nnz, const uint32_t* order, const uint32_t* map, const uint32_t* rp,
+                         uint32_t* ids, uint8_t* ids24, hipStream_t st);
 hipError_t launch_nodes(uint32_t n, const uint32_t* order, const uint32_t* rp, uint4* node, uint2* node8, hipStream_t st);
 hipError_t build_fat_adjacency(const uint4* node, const uint32_t* col, uint4* adj, uint32_t nnz,
                                hipStream_t st);

