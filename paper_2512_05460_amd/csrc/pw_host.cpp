@@ -447,28 +447,42 @@ int persistent_wgs(const bd_graph* g, int part, int share, int shape, double pai
 
 // Launch shapes of the sign-table kernels for M probes per walk: four to one
 // work groups per CU, each with as many tables as its share of the LDS holds,
-// the adjacency in LDS where it fits beside one group's tables.
+// the adjacency in LDS where it fits beside one group's tables. With the
+// adjacency in memory, the kernels that share walks take up to 105 registers,
+// 1,024 threads a CU: two groups of 512 (one builds its tables while the other
+// walks; 384 probes at n = 1e5, four a walk, 13.5 ms on one group of 1,024, 11.7
+// so, 9.6 with chunks of one phase) or one of 1,024. Groups of 256 are better in
+// batches (8 queries at n = 5,000 1.06 -> 0.89 ms) but worse for one query.
 void plan_sign_shapes(const SignTables& mem, const SignTables& lds, uint32_t M, SignShape out[kSignShapes])
 {
-    const uint32_t threads[kSignShapes] = {512, 512, 1024, 1024}, per_cu[kSignShapes] = {4, 3, 2, 1};
+    const uint32_t most[kSignShapes] = {512, 512, 1024, 1024}, sharing[kSignShapes] = {0, 0, 512, 1024};
+    const uint32_t per_cu[kSignShapes] = {4, 3, 2, 1};
     const uint32_t budget[kSignShapes] = {39680, 53480, 80640, kSignLdsMost};
     bool found = false;
     for (int form = 1; form >= 0 && !found; --form) {
         const SignTables& t = form ? lds : mem;
         if (!t.tabw) continue;
-        const uint64_t fixed = form ? 4ull * (t.nblk + t.idw) : 16ull * t.nblk;
-        const uint64_t per = 4ull * t.tabw + 32;  // a table and its two sums
+        const uint64_t fixed = form ? 4ull * (t.nblk + t.idw) : 8ull * t.nblk;
+        const uint64_t per = 4ull * t.tabw + 40;  // a table, its two sums and zeros
+        const uint32_t* threads = form || M == 1 ? most : sharing;
         for (int i = 0; i < kSignShapes; ++i) {
-            if (fixed + std::max<uint64_t>(M * per, M * 32 + (kMaxG + 2) * 8) > budget[i]) continue;
+            if (!threads[i] || fixed + std::max<uint64_t>(M * per, M * 40 + (kMaxG + 2) * 8) > budget[i]) continue;
             SignShape& s = out[i];
             s.lds = form;
             s.threads = threads[i];
             s.per_cu = per_cu[i];
             s.T = (uint32_t)std::min<uint64_t>(64, (budget[i] - fixed) / per);
-            s.bytes = (uint32_t)(fixed + std::max<uint64_t>(s.T * per, s.T * 32 + (kMaxG + 2) * 8));
+            s.bytes = (uint32_t)(fixed + std::max<uint64_t>(s.T * per, s.T * 40 + (kMaxG + 2) * 8));
             found = true;
         }
     }
+}
+
+// Groups whose tables a work group holds at once (from memory a group takes as
+// many tables as its kernel scores).
+uint32_t sign_groups(const SignShape& s, uint32_t share)
+{
+    return s.T / (s.lds ? share : (uint32_t)share_class((int)share));
 }
 
 // Waves per CU with walks to run when probes have R replicas: as many as the
@@ -476,7 +490,7 @@ void plan_sign_shapes(const SignTables& mem, const SignTables& lds, uint32_t M, 
 uint32_t sign_waves(const SignShape& s, uint32_t share, uint32_t R)
 {
     if (!s.threads) return 0;
-    const uint64_t groups = s.T / share, waves = R >= kUniformMinR ? groups * ((R + 63ull) / 64) : groups * R / 64;
+    const uint64_t groups = sign_groups(s, share), waves = R >= kUniformMinR ? groups * ((R + 63ull) / 64) : groups * R / 64;
     return s.per_cu * (uint32_t)std::min<uint64_t>(s.threads / 64, waves);
 }
 
@@ -494,11 +508,11 @@ int load_sign_tables(bd_graph* g, const std::vector<uint32_t>& order_in, const L
     for (size_t i = 0; i < n; ++i) rp[i + 1] = rp[i] + (uint32_t)g->deg[order[i]];
     SignOrder so;
     SignTables mem{}, lds{};
-    if (plan_sign_order(rp, &so)) {
+    if (g->d_max < (1 << 20) && plan_sign_order(rp, &so)) {
         mem.np = so.np;
         mem.shift = so.shift;
-        mem.nblk = so.nblk;
-        mem.tabw = so.np / 16;
+        mem.nblk = (so.nblk + 1) & ~1u;
+        mem.tabw = (so.np + 31) / 32;
     }
     if (n <= 16384 && nnz <= 65535 && g->d_max <= 65535) {
         lds.np = (uint32_t)n;
@@ -546,28 +560,33 @@ int load_sign_tables(bd_graph* g, const std::vector<uint32_t>& order_in, const L
     if (use[0]) {
         std::vector<uint32_t> pos, blk;
         build_sign_order(rp, so, &pos, &blk);
-        // positions by caller id; the table words that hold nodes, and the ids
-        // that their 16 positions' probe values are evaluated on
+        std::vector<uint32_t> entry(2 * (size_t)mem.nblk, 0u);
+        for (uint32_t b = 0; b < so.nblk; ++b) {
+            entry[2 * b] = blk[4 * (size_t)b];
+            entry[2 * b + 1] = blk[4 * (size_t)b + 2];
+        }
+        // positions by caller id; the groups of 32 that hold nodes, and the ids that
+        // their probe values are evaluated on (padding repeats the id before it)
         std::vector<uint32_t> at(n), word, pid;
         for (size_t i = 0; i < n; ++i) {
-            at[order[i]] = pos[i];
-            if (word.empty() || word.back() != pos[i] / 16) {
-                word.push_back(pos[i] / 16);
-                pid.resize(pid.size() + 16, 0u);
-            }
-            pid[pid.size() - 16 + pos[i] % 16] = g->layout == 5 ? (uint32_t)i : order[i];
+            const uint32_t id = g->layout == 5 ? (uint32_t)i : order[i], x = pos[i];
+            at[order[i]] = x;
+            if (word.empty() || word.back() != x / 32) word.push_back(x / 32);
+            pid.resize(32 * word.size() - 32 + x % 32, pid.empty() ? 0u : pid.back());
+            pid.push_back(id);
         }
-        // as the kernel reads them: of 64 words, each one's first four ids, then the next four, ...
+        pid.resize(32 * word.size(), pid.back());
+        // as the kernel reads them: of 64 groups, each one's first four ids, then the next four, ...
         const size_t segs = (word.size() + 63) / 64;
-        std::vector<uint32_t> ids_by_lane(segs * 1024, 0u);
+        std::vector<uint32_t> ids_by_lane(segs * 2048, 0u);
         for (size_t w = 0; w < word.size(); ++w)
-            for (size_t i = 0; i < 16; ++i)
-                ids_by_lane[(w / 64) * 1024 + (i / 4) * 256 + (w % 64) * 4 + i % 4] = pid[16 * w + i];
+            for (size_t i = 0; i < 32; ++i)
+                ids_by_lane[(w / 64) * 2048 + (i / 4) * 256 + (w % 64) * 4 + i % 4] = pid[32 * w + i];
         pid.swap(ids_by_lane);
         mem.words = (uint32_t)word.size();
         pid.insert(pid.end(), word.begin(), word.end());
         DevBuf d_order, d_at, d_rp;
-        rc = upload(g->sblk, blk, st);
+        rc = upload(g->sblk, entry, st);
         if (rc == BD_OK) rc = upload(g->spid, pid, st);
         if (rc == BD_OK) rc = upload(d_order, order, st);
         if (rc == BD_OK) rc = upload(d_at, at, st);
@@ -991,8 +1010,11 @@ GraphTables tables(const bd_graph* g)
 // overlap one's table building with the others' walks. A table costs one
 // evaluation of the probe per node position and saves one per scored step,
 // 2 (L + 1) min(R, kSplitReplicas) of them in a chunk: taken from one per
-// position on (eight against the degree-run kernel, which also reads once per
-// step and is bound by those reads), and from 4 waves per CU.
+// position on (against the degree-run kernel, which also reads once per step
+// and is bound by those reads, from eight; with walk sharing, where the probes'
+// arithmetic weighs more, from one and a half: two probes a walk at 1.14 per
+// position took 8.9 ms for its 8.0 at n = 150,000, and 3.2 for its 6.5 on a grid
+// of 300,000 at 2.0), and from 4 waves per CU.
 int query_shape(const bd_graph* g, const QueryDesc& d)
 {
     const int share = share_class(d.share);
@@ -1009,8 +1031,8 @@ int query_shape(const bd_graph* g, const QueryDesc& d)
     }
     if (best < 0) return -1;
     const uint64_t positions = (sign_shape(g, share, best).lds ? g->signs_lds : g->signs).np;
-    const bool one_read = runs_layout(g->kernel_layout) && share == 1 && !sign_shape(g, share, best).lds;
-    return scored >= positions * (one_read ? 8 : 1) ? best : -1;
+    const bool one_read = runs_layout(g->kernel_layout) && !sign_shape(g, share, best).lds;
+    return 2 * scored >= positions * (!one_read ? 2 : share == 1 ? 16 : 3) ? best : -1;
 }
 
 // The one shape that a launch over several queries takes: the one that most of
@@ -1544,6 +1566,14 @@ void build_batch(const bd_graph* g, int64_t nq, const int32_t* s, const int32_t*
     // most compute units idle: 1,024 grid queries of up to L = 5,000 ran 92 ms in
     // chunks of 4,096 pairs and 80 ms so.
     std::vector<int32_t> pairs(b.qd.size(), ex.chunk_pairs);
+    if (ex.mode == BD_MODE_PLAIN && spread_chunks && ex.chunk_pairs <= 0)
+        // plain chunks on sign tables hold the groups that a work group has tables
+        // for: more only leave the last ones late (where the adjacency is staged in
+        // LDS, once a chunk, they save that work: 1.65 ms for 1.90 at n = 5,000)
+        for (size_t q = 0; q < b.qd.size(); ++q)
+            if (b.shapes[q] >= 0 && !sign_shape(g, b.share, b.shapes[q]).lds)
+                lanes[q] = (uint32_t)std::min<uint64_t>(
+                    lanes[q], std::max<uint64_t>(1, (uint64_t)sign_groups(sign_shape(g, b.share, b.shapes[q]), share) * b.qd[q].R));
     double total[2] = {0.0, 0.0}, pairs_of[2] = {0.0, 0.0};  // walk pairs times steps, walk pairs
     size_t general = 0;
     for (size_t q = 0; q < b.qd.size(); ++q) {

@@ -63,17 +63,17 @@ struct GraphTables {
 // nodes go by the ids their probes are evaluated on; else they are in descending
 // degree, every run of equal degree padded to whole blocks of 2^shift positions.
 struct SignTables {
-    const uint4* blk;     // per block {base, d, bits of 1.0f/d, 0}: row offset of position x = base + x d;
+    const uint4* blk;     // per block {base, bits of 1.0f/d}: row offset of position x = base + x d;
                           // or row offset | degree << 16 of every node, then the adjacency as 2-byte 4 x id
     const uint32_t* ids;  // adjacency as positions, 3 bytes each (not in LDS)
-    const uint32_t* pid;  // of each table word with nodes, the ids that its 16 positions' probe values are
-                          // evaluated on (0 in the padding), 64 words by 4 ids at a time; then the words'
-                          // indices (not in LDS)
-    uint32_t words;       // such words
+    const uint32_t* pid;  // of each 32 positions with nodes, the ids that their probe values are evaluated on
+                          // (the one before it in the padding), of 64 such groups 4 ids at a time; then the
+                          // groups' indices (not in LDS)
+    uint32_t words;       // such groups
     uint32_t np;          // positions
-    uint32_t nblk, shift; // blocks; words of rows (a multiple of 4) with the adjacency in LDS
+    uint32_t nblk, shift; // blocks (an even number); words of rows (a multiple of 4) with the adjacency in LDS
     uint32_t idw;         // words of the adjacency in LDS (a multiple of 4)
-    uint32_t tabw;        // words of one sign table: 16 positions a word, or 1 with the adjacency in LDS
+    uint32_t tabw;        // words of one sign table: 32 positions a word, or 1 with the adjacency in LDS
     uint32_t T;           // sign tables a work group holds
 };
 

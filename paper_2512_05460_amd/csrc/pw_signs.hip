@@ -15,13 +15,22 @@
 //   * Larger ones: nodes are stored in descending degree, each run of equal
 //     degree padded to whole blocks of 2^shift positions, so a block has one
 //     degree d and a node x of it has row offset base + x d. One LDS read of
-//     the block's entry {base, d, bits of 1.0f/d} resolves a node: no search,
-//     no division, no second dependent read from memory. A step reads one
+//     the block's entry {base, bits of 1.0f/d} resolves a node: no search, no
+//     second dependent read from memory. A step reads one
 //     neighbour position, 3 bytes, from memory (an L2 hit up to about 1.3
-//     million adjacency entries); a table holds two bits a node.
+//     million adjacency entries); a table holds a bit a node, the sign. z = 0 has
+//     one or two nodes a probe at most, which the walks compare with.
 //
 // The walks, their random streams, the order of the binary32 sums and all
 // results are those of the other kernels.
+//
+// Bounds, and times before (the general kernels) and now: small graphs by LDS
+// reads and Philox (32 queries, n = 1,000: 34.0 -> 5.24 ms); one probe a walk by
+// the L2s' requests, 2.7e11 a second (256 probes in 37 blocks, L = 1,000, n =
+// 1e5: 71.4 -> 68.0 ms of 66; 17 queries on 3-byte ids without hub tables: 60.4
+// -> 37.6 of 35); four probes a walk by those and the table building about alike
+// (n = 1e5: 24.3 -> 9.5 ms of 8.5). Two bits a node and 16-byte block entries
+// took 13.7 ms there: a CU held one work group, and built or walked.
 #include "pw_chunk.hpp"
 #include "pw_device.hpp"
 #include "pw_internal.hpp"
@@ -30,8 +39,9 @@ namespace pw {
 
 // Dynamic LDS of a work group, in this order.
 struct SignLds {
-    uint4* blk;                 // nblk block entries; kLds: rows, then the adjacency
+    uint4* blk;                 // nblk block entries of 8 bytes; kLds: rows, then the adjacency
     unsigned long long* acc;    // T x {S1, S2}
+    uint32_t* zero;             // T x two positions with z = 0, ~0 for none (not with kLds)
     uint32_t* tab;              // T tables of tabw words (kMaxG + 2 doubles at least)
 };
 
@@ -56,8 +66,11 @@ __device__ __forceinline__ SignNode<kLds> sign_node(const SignTables& S, const S
     if constexpr (kLds) {
         return SignNode<1>{x, *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(M.blk) + x)};
     } else {
-        const uint4 e = M.blk[x >> S.shift];
-        return SignNode<0>{x, umul24(x, e.y) + e.x, e.y, __uint_as_float(e.z)};
+        const uint2 e = reinterpret_cast<const uint2*>(M.blk)[x >> S.shift];
+        const float inv = __uint_as_float(e.y);
+        // d < 2^20: v_rcp_f32's 1 ulp and inv's half leave 1/inv less than 1/4 away from it
+        const uint32_t d = (uint32_t)(__builtin_amdgcn_rcpf(inv) + 0.5f);
+        return SignNode<0>{x, umul24(x, d) + e.x, d, inv};
     }
 }
 
@@ -75,67 +88,134 @@ __device__ __forceinline__ uint32_t sign_next(const SignTables& S, const SignLds
     }
 }
 
-// acc + z(x) / d. From the two-bit table z in {-1, 0, 1} is exact, so the fused
-// form rounds as the plain sum does; z = 0 leaves acc as it is (acc is never
-// -0). The first of a word's 16 positions is in its top bits.
-template <int kLds>
-__device__ __forceinline__ float sign_add(const uint32_t* tab, const SignNode<kLds>& w, float acc)
-{
-    if constexpr (kLds) {
-        return __fadd_rn(acc, *reinterpret_cast<const float*>(reinterpret_cast<const char*>(tab) + w.x4));
-    } else {
-        const int z = (int)(tab[w.x >> 4] << ((2u * w.x) & 31u)) >> 30;
-        return __builtin_fmaf((float)z, w.inv, acc);
-    }
-}
-
-// Fills the tables of probes [kA, kA + kn): each wave takes 64 words of one
-// probe at a time (its keys are wave-uniform).
-template <int kLds>
+// Fills the tables of the phase's gn groups from gi on, whose kn probes start at
+// kA. Each wave takes 64 words of one probe (kLds), or of one group, whose words
+// hold its kShare probes' bits of a position side by side; the keys are
+// wave-uniform. A bit tells a sign and the first position's are on top; a
+// probe's one or two zeros are kept as positions.
+template <int kLds, int kShare>
 __device__ __forceinline__ void sign_build(const SignTables& S, const SignLds& M, const Domain& dom, const QueryDesc& d,
-                                           uint32_t kA, uint32_t kn)
+                                           uint32_t gi, uint32_t gn, uint32_t M_, uint32_t gpb, uint32_t kA, uint32_t kn)
 {
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t lane = threadIdx.x & 63u, nw = blockDim.x >> 6;
-    const uint32_t words = kLds ? S.tabw : S.words;
-    const uint32_t segs = (words + 63u) >> 6;
     uint32_t cur = 0xFFFFFFFFu;
-    Probe pr{};
-    for (uint32_t u = wave; u < kn * segs; u += nw) {
-        const uint32_t j = u / segs;
-        if (j != cur) {
-            pr = make_probe(d.seed_lo, d.seed_hi, d.uid, kA + j, dom.n);
-            cur = j;
-        }
-        const uint32_t w = (u - j * segs) * 64u + lane;
-        if (w >= words) continue;
-        if constexpr (kLds) {
+    if constexpr (kLds) {
+        const uint32_t segs = (S.tabw + 63u) >> 6;
+        Probe pr{};
+        for (uint32_t u = wave; u < kn * segs; u += nw) {
+            const uint32_t j = u / segs;
+            if (j != cur) {
+                pr = make_probe(d.seed_lo, d.seed_hi, d.uid, kA + j, dom.n);
+                cur = j;
+            }
+            const uint32_t w = (u - j * segs) * 64u + lane;
+            if (w >= S.tabw) continue;
             uint32_t y;
             const uint32_t deg = reinterpret_cast<const uint32_t*>(M.blk)[w] >> 16;
             M.tab[j * S.tabw + w] =
                 __float_as_uint(__fmul_rn((float)probe_value(w, pr, dom, &y), __fdiv_rn(1.0f, (float)deg)));
-        } else {
-            // a quarter of 64 words' ids at a time, one after another
-            const uint4* ids = reinterpret_cast<const uint4*>(S.pid) + (size_t)(u - j * segs) * 256u + lane;
+        }
+    } else {
+        constexpr uint32_t kQuads = 8 / kShare;  // a word's positions, four at a time
+        const uint32_t segs = (S.words + 63u) >> 6, units = segs * kShare;
+        Probe pr[kShare];
+        uint32_t m = 0;
+        for (uint32_t u = wave; u < gn * units; u += nw) {
+            const uint32_t gg = u / units, r = u - gg * units, seg = r / kShare, part = r % kShare;
+            if (gg != cur) {
+                uint32_t kf;
+                group_probes(gi + gg, d.B, M_, gpb, &kf, &m);
+#pragma unroll
+                for (int j = 0; j < kShare; ++j)
+                    if (kShare == 1 || (uint32_t)j < m) pr[j] = make_probe(d.seed_lo, d.seed_hi, d.uid, kf + j, dom.n);
+                cur = gg;
+            }
+            const uint32_t w = seg * 64u + lane;
+            if (w >= S.words) continue;
+            const uint32_t at = S.pid[2048u * segs + w];  // 32 positions from 32 at on
+            const uint4* ids = reinterpret_cast<const uint4*>(S.pid) + (size_t)seg * 512u + part * kQuads * 64u + lane;
             uint32_t word = 0;
 #pragma unroll 1
-            for (uint32_t i = 0; i < 4; ++i) {
+            for (uint32_t i = 0; i < kQuads; ++i) {
                 const uint4 v = ids[64u * i];
-                // four permutations at once; the few values that land past n are walked on
-                uint32_t y[4] = {feistel_once(v.x, pr, dom), feistel_once(v.y, pr, dom), feistel_once(v.z, pr, dom),
-                                 feistel_once(v.w, pr, dom)};
-                while (max(max(y[0], y[1]), max(y[2], y[3])) >= dom.n) {
+                uint32_t bits = 0;
+#pragma unroll
+                for (int j = 0; j < kShare; ++j) {
+                    if (kShare != 1 && (uint32_t)j >= m) break;
+                    const Probe& q = pr[j];
+                    // four permutations at once; the few values that land past n are walked on
+                    uint32_t y[4] = {feistel_once(v.x, q, dom), feistel_once(v.y, q, dom), feistel_once(v.z, q, dom),
+                                     feistel_once(v.w, q, dom)};
+                    while (max(max(y[0], y[1]), max(y[2], y[3])) >= dom.n) {
+#pragma unroll
+                        for (int h = 0; h < 4; ++h)
+                            if (y[h] >= dom.n) y[h] = feistel_once(y[h], q, dom);
+                    }
 #pragma unroll
                     for (int h = 0; h < 4; ++h)
-                        if (y[h] >= dom.n) y[h] = feistel_once(y[h], pr, dom);
-                }
+                        bits |= (hash_bit(q, y[h] >> 1) ^ (y[h] & 1u)) << (kShare * (3 - h) + kShare - 1 - j);
+                    if (max(max(y[0], y[1]), max(y[2], y[3])) >= q.zlo) {
+                        // padding repeats the id before it, whose position is the lower one
+                        const uint32_t x = 32u * at + 4u * (part * kQuads + i);
+                        uint32_t* z = M.zero + 2u * (gg * kShare + j);
 #pragma unroll
-                for (int h = 0; h < 4; ++h) {
-                    const uint32_t neg = hash_bit(pr, y[h] >> 1) ^ (y[h] & 1u);
-                    word = (word << 2) | (y[h] >= pr.zlo ? 0u : 2u * neg + 1u);  // 1, -1 as 3, or 0
+                        for (int h = 0; h < 4; ++h)
+                            if (y[h] >= q.zlo) atomicMin(z + (y[h] - q.zlo), x + h);
+                    }
                 }
+                word = (word << (4 * kShare)) | bits;
             }
-            M.tab[j * S.tabw + S.pid[1024u * segs + w]] = word;
+            M.tab[(gg * S.tabw + at) * kShare + part] = word;
+        }
+    }
+}
+
+// The positions of a group's zeros, two a probe.
+template <int kLds, int kUniform, int kShare>
+struct SignZeros {
+    uint32_t z[kLds ? 1 : 2 * kShare];
+    __device__ __forceinline__ void read(const uint32_t* zero)
+    {
+        if constexpr (!kLds) {
+#pragma unroll
+            for (int i = 0; i < 2 * kShare; ++i) z[i] = kUniform ? __builtin_amdgcn_readfirstlane(zero[i]) : zero[i];
+        }
+    }
+};
+
+// z_j of node w from its word, times 1 / d: +0 for z = 0, which leaves a sum as it
+// is (they are never -0).
+__device__ __forceinline__ float sign_term(const SignNode<0>& w, uint32_t word, int j, const uint32_t* z)
+{
+    const uint32_t v = ((word << j) & 0x80000000u) | __float_as_uint(w.inv);
+    return w.x == z[2 * j] || w.x == z[2 * j + 1] ? 0.0f : __uint_as_float(v);
+}
+
+// Scores both walks' nodes against the m probes of a group whose tables start at tab.
+template <int kLds, int kUniform, int kShare>
+__device__ __forceinline__ void sign_score(const SignTables& S, const uint32_t* tab,
+                                           const SignZeros<kLds, kUniform, kShare>& Z, uint32_t m, const SignNode<kLds>& s,
+                                           const SignNode<kLds>& t, float* a, float* b)
+{
+    if constexpr (kLds) {
+#pragma unroll
+        for (int j = 0; j < kShare; ++j) {
+            if (kShare == 1 || (uint32_t)j < m) {
+                const char* row = reinterpret_cast<const char*>(tab + j * S.tabw);
+                a[j] = __fadd_rn(a[j], *reinterpret_cast<const float*>(row + s.x4));
+                b[j] = __fadd_rn(b[j], *reinterpret_cast<const float*>(row + t.x4));
+            }
+        }
+    } else {
+        const uint32_t bs = s.x * kShare, bt = t.x * kShare;
+        const uint32_t ws = tab[bs >> 5] << (bs & 31u), wt = tab[bt >> 5] << (bt & 31u);
+#pragma unroll
+        for (int j = 0; j < kShare; ++j) {
+            if (kShare == 1 || (uint32_t)j < m) {
+                a[j] = __fadd_rn(a[j], sign_term(s, ws, j, Z.z));
+                b[j] = __fadd_rn(b[j], sign_term(t, wt, j, Z.z));
+            }
         }
     }
 }
@@ -143,23 +223,16 @@ __device__ __forceinline__ void sign_build(const SignTables& S, const SignLds& M
 // U_p of replica p for the m probes of a group, whose tables start at tab (the
 // streams are keyed by kw, the group's first probe). The two neighbour reads of
 // a step are issued before the nodes just left are scored.
-template <int kLds, int kShare>
-__device__ __forceinline__ void sign_pair(const SignTables& S, const SignLds& M, const uint32_t* tab, uint32_t m,
+template <int kLds, int kUniform, int kShare>
+__device__ __forceinline__ void sign_pair(const SignTables& S, const SignLds& M, const uint32_t* tab,
+                                          const SignZeros<kLds, kUniform, kShare>& Z, uint32_t m,
                                           SignNode<kLds> s, SignNode<kLds> t, int L, uint32_t p, uint32_t kw, uint32_t uid,
                                           uint32_t slo, uint32_t shi, float* U)
 {
     float a[kShare], b[kShare];
 #pragma unroll
     for (int j = 0; j < kShare; ++j) a[j] = b[j] = 0.0f;
-    auto score = [&]() {
-#pragma unroll
-        for (int j = 0; j < kShare; ++j) {
-            if (kShare == 1 || (uint32_t)j < m) {
-                a[j] = sign_add<kLds>(tab + j * S.tabw, s, a[j]);
-                b[j] = sign_add<kLds>(tab + j * S.tabw, t, b[j]);
-            }
-        }
-    };
+    auto score = [&]() { sign_score<kLds, kUniform, kShare>(S, tab, Z, m, s, t, a, b); };
     auto advance2 = [&](uint32_t us, uint32_t ut) {
         const uint32_t xs = sign_next<kLds>(S, M, s, us);
         const uint32_t xt = sign_next<kLds>(S, M, t, ut);
@@ -206,7 +279,8 @@ __device__ __forceinline__ void sign_chunk(const WalkArgs& A, const SignLds& M, 
     dom.A8 = A.g.dom.A8;
     const uint32_t M_ = kShare == 1 ? 1u : d.share;
     const uint32_t gpb = (d.B + M_ - 1) / M_;
-    const uint32_t per_phase = max(1u, S.T / M_);
+    const uint32_t slots = kLds ? M_ : (uint32_t)kShare;  // tables of a group
+    const uint32_t per_phase = max(1u, S.T / slots);
     const uint32_t tid = threadIdx.x, kT = blockDim.x;
     const SignNode<kLds> s0 = sign_node<kLds>(S, M, d.ss), t0 = sign_node<kLds>(S, M, d.st);
     // phases of as many groups as there are tables
@@ -217,7 +291,11 @@ __device__ __forceinline__ void sign_chunk(const WalkArgs& A, const SignLds& M, 
         group_probes(c.g0 + g + gn - 1u, d.B, M_, gpb, &kl, &sz);
         const uint32_t kn = kl + sz - kA;
         for (uint32_t j = tid; j < kn * 4u; j += kT) M.acc[j] = 0ull;
-        sign_build<kLds>(S, M, dom, d, kA, kn);
+        if constexpr (!kLds) {
+            for (uint32_t j = tid; j < gn * kShare * 2u; j += kT) M.zero[j] = 0xFFFFFFFFu;
+            __syncthreads();
+        }
+        sign_build<kLds, kShare>(S, M, dom, d, c.g0 + g, gn, M_, gpb, kA, kn);
         __syncthreads();
         if constexpr (kUniform) {
             // each wave takes 64 consecutive replicas of one group
@@ -230,9 +308,12 @@ __device__ __forceinline__ void sign_chunk(const WalkArgs& A, const SignLds& M, 
                 const uint32_t p = c.p0 + (u - gg * nb) * 64u + lane;
                 uint32_t kf, m;
                 group_probes(c.g0 + g + gg, d.B, M_, gpb, &kf, &m);
+                const uint32_t slot = kLds ? kf - kA : gg * kShare;
+                SignZeros<kLds, kUniform, kShare> Z;
+                Z.read(M.zero + 2u * slot);
                 if (p < pend) {
                     float U[kShare];
-                    sign_pair<kLds, kShare>(S, M, M.tab + (kf - kA) * S.tabw, m, s0, t0, d.L, p, kf, d.uid, d.seed_lo,
+                    sign_pair<kLds, kUniform, kShare>(S, M, M.tab + slot * S.tabw, Z, m, s0, t0, d.L, p, kf, d.uid, d.seed_lo,
                                             d.seed_hi, U);
 #pragma unroll
                     for (int j = 0; j < kShare; ++j) {
@@ -252,8 +333,11 @@ __device__ __forceinline__ void sign_chunk(const WalkArgs& A, const SignLds& M, 
                 const uint32_t p = c.p0 + (uint32_t)(w - (uint64_t)gg * c.pc);
                 uint32_t kf, m;
                 group_probes(c.g0 + g + gg, d.B, M_, gpb, &kf, &m);
+                const uint32_t slot = kLds ? kf - kA : gg * kShare;
+                SignZeros<kLds, kUniform, kShare> Z;
+                Z.read(M.zero + 2u * slot);
                 float U[kShare];
-                sign_pair<kLds, kShare>(S, M, M.tab + (kf - kA) * S.tabw, m, s0, t0, d.L, p, kf, d.uid, d.seed_lo,
+                sign_pair<kLds, kUniform, kShare>(S, M, M.tab + slot * S.tabw, Z, m, s0, t0, d.L, p, kf, d.uid, d.seed_lo,
                                         d.seed_hi, U);
 #pragma unroll
                 for (int j = 0; j < kShare; ++j) {
@@ -280,10 +364,11 @@ __global__ __launch_bounds__(1024, kShare == 1 ? 8 : 4) void sign_kernel(WalkArg
     const SignTables& S = A.signs;
     SignLds M;
     // staged: the block entries, or the rows and the adjacency (whole 16 bytes)
-    const uint32_t staged = kLds ? (S.nblk + S.idw) / 4u : S.nblk;
+    const uint32_t staged = kLds ? (S.nblk + S.idw) / 4u : S.nblk / 2u;
     M.blk = reinterpret_cast<uint4*>(lds);
     M.acc = reinterpret_cast<unsigned long long*>(M.blk + staged);
-    M.tab = reinterpret_cast<uint32_t*>(M.acc + 4u * S.T);
+    M.zero = reinterpret_cast<uint32_t*>(M.acc + 4u * S.T);
+    M.tab = M.zero + 2u * S.T;
     for (uint32_t i = threadIdx.x; i < staged; i += blockDim.x) M.blk[i] = S.blk[i];
     if (!A.persistent) {
         if (threadIdx.x == 0) next = abort_raised(A) ? 1u : 0u;

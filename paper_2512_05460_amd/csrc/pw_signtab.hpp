@@ -22,8 +22,8 @@ struct SignOrder {
     std::vector<uint32_t> run;   // first storage id of each run, then n
 };
 
-// The block size for which the block table (16 bytes a block) and two sign
-// tables (2 bits a position each) take least; false beyond 2^24 positions,
+// The block size for which the block table (8 bytes a block) and four sign
+// tables (a bit a position each) take least; false beyond 2^24 positions,
 // which the 24-bit products of the kernels could not hold.
 inline bool plan_sign_order(const std::vector<uint32_t>& rp, SignOrder* o)
 {
@@ -37,7 +37,7 @@ inline bool plan_sign_order(const std::vector<uint32_t>& rp, SignOrder* o)
         uint64_t blocks = 0;
         for (size_t r = 0; r + 1 < o->run.size(); ++r)
             blocks += ((uint64_t)(o->run[r + 1] - o->run[r]) + (1u << s) - 1) >> s;
-        const uint64_t np = blocks << s, bytes = 16 * blocks + np / 2;
+        const uint64_t np = blocks << s, bytes = 8 * blocks + np / 2;
         if (np <= (1u << 24) && bytes < best) {
             best = bytes;
             o->shift = s;

@@ -111,3 +111,23 @@ def test_served_and_replayed():
         for i in ids:
             assert np.array_equal(srv.wait(i)[0]["beta"], ref["beta"])
         srv.destroy()
+
+
+@pytest.mark.parametrize("n", [1601, 1634])
+@pytest.mark.parametrize("M", [1, 2, 3, 4])
+def test_zeros_from_memory(n, M):
+    """One or two nodes of a probe have sign 0: read often on a graph of few nodes
+    (too many entries for the LDS form), with a last group of fewer probes."""
+    key = f"dense{n}"
+    GRAPHS.setdefault(key, lambda: graphs.random_connected(n, 0.0375, 6))
+    s, t = queries.uniform_pairs(n, 3, M)
+    _check(key, B.BD_LAYOUT_CSR, s, t, 61, 5, 70, M)
+    _check(key, B.BD_LAYOUT_CSR, s, t, 90, 5, 40, M, modes=("batched",))
+
+
+@pytest.mark.parametrize("hub", [(1 << 20) - 1, 1 << 20])
+def test_hub_of_highest_degree(hub):
+    """Degrees are taken from their binary32 reciprocals up to 2^20 - 1."""
+    key = f"star{hub}"
+    GRAPHS.setdefault(key, lambda: graphs.csr_from_edges(hub + 1, np.zeros(hub, int), np.arange(1, hub + 1)))
+    _check(key, B.BD_LAYOUT_CSR, np.array([0], np.int32), np.array([hub], np.int32), 3000, 1, 300, modes=("batched",))

@@ -39,5 +39,5 @@ def test_nodes_resolve(check):
         cases.append(np.sort(rng.zipf(1.8, size=int(rng.integers(1, 5000))).clip(1, 3000))[::-1].tolist())
     res = check(cases)
     assert len(res) == len(cases) and all(r[0] == "ok" for r in res), [r for r in res if r[0] != "ok"]
-    assert res[1][1] == "7"  # cl100k: blocks of 128
+    assert res[1][1] == "6"  # cl100k: blocks of 64
     assert all(int(r[2]) >= len(d) and int(r[2]) % 16 == 0 for r, d in zip(res, cases))
