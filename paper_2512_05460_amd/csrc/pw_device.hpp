@@ -135,10 +135,8 @@ __device__ __forceinline__ uint32_t fmix(uint32_t v, uint32_t key)
 }
 
 // Feistel rounds alternate L <- (L + F(R)) mod A and R <- R ^ top_rb(F(L)).
-__device__ __forceinline__ uint32_t feistel_once(uint32_t x, const Probe& pr, const Domain& dm)
+__device__ __forceinline__ uint32_t feistel_rounds(uint32_t L, uint32_t R, const Probe& pr, const Domain& dm)
 {
-    uint32_t L = x >> dm.rb;
-    uint32_t R = x & dm.mask;
 #pragma unroll
     for (int r = 0; r < kFeistelRounds; r += 2) {
         const uint32_t f = umul24hi(fmix(R, pr.K[r]) >> 8, dm.A8);
@@ -147,6 +145,11 @@ __device__ __forceinline__ uint32_t feistel_once(uint32_t x, const Probe& pr, co
         R ^= (fmix(L, pr.K[r + 1]) >> dm.rsh) & dm.mask;
     }
     return (L << dm.rb) | R;
+}
+
+__device__ __forceinline__ uint32_t feistel_once(uint32_t x, const Probe& pr, const Domain& dm)
+{
+    return feistel_rounds(x >> dm.rb, x & dm.mask, pr, dm);
 }
 
 // pi_k(x): values that land in [n, A*2^rb) are walked again until they fall in [n].
@@ -168,11 +171,18 @@ __device__ __forceinline__ uint32_t hash_bit(const Probe& pr, uint32_t u)
     return t & 1u;
 }
 
-// acc + z^(k)_x * inv, skipping the term when z = 0
+// acc + z^(k)_x * inv, skipping the term when z = 0 (x as the layout's states hold it)
+template <int kLayout = 0>
 __device__ __forceinline__ float add_term(float acc, uint32_t x, float inv, const Probe& pr,
                                           const Domain& dm)
 {
-    const uint32_t y = feistel_pi(x, pr, dm);
+    uint32_t y;
+    if (kLayout == kLayoutFat8) {
+        y = feistel_rounds(x >> (dm.rb + kFat8Shift), __builtin_amdgcn_ubfe(x, kFat8Shift, dm.rb), pr, dm);
+        while (y >= dm.n) y = feistel_once(y, pr, dm);
+    } else {
+        y = feistel_pi(x, pr, dm);
+    }
     const uint32_t neg = hash_bit(pr, y >> 1) ^ (y & 1u);
     const float v = neg ? -inv : inv;
     const float s = __fadd_rn(acc, v);
@@ -334,7 +344,33 @@ __device__ __forceinline__ WalkState start_at(const DevGraph& G, uint32_t x)
         hubid_row(G, x, w);
         return w;
     }
-    return start_state(G.node[x]);
+    WalkState w = start_state(G.node[x]);
+    if (kLayout == kLayoutFat8) {
+        w.x = w.x << kFat8Shift | w.deg << 3;
+        w.off <<= 3;
+    }
+    return w;
+}
+
+// Code 10's states arrive as read: whatever needs the value just loaded waits for
+// it, and the arithmetic of the node left before is to run meanwhile (36.4 ms
+// became 56.7 with the reciprocal looked up on arrival, and 31.0 so). The id stays
+// above 8 times the degree, which serves as the reciprocal's byte offset and in
+// the next draw. Before a node is scored or left.
+template <int kLayout>
+__device__ __forceinline__ void resolve(WalkState& w, const DevGraph& G)
+{
+    if (kLayout == kLayoutFat8) {
+        w.deg = w.x & ((1u << kFat8Shift) - 8u);
+        w.inv = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(G.inv) + w.deg);
+    }
+}
+
+// The id of a state on arrival.
+template <int kLayout>
+__device__ __forceinline__ uint32_t node_id(const WalkState& w)
+{
+    return kLayout == kLayoutFat8 ? w.x >> kFat8Shift : w.x;
 }
 
 // Uniform neighbour: j = floor(u * d / 2^32) into the ascending neighbour list.
@@ -356,6 +392,11 @@ __device__ __forceinline__ void step(WalkState& w, uint32_t u, const DevGraph& G
         w.off = e.y;
         w.deg = e.z;
         w.inv = __uint_as_float(e.w);
+    } else if (kLayout == kLayoutFat8) {
+        // j is 8 floor(u d / 2^32) and up to 7 more, as w.deg is 8 d
+        const uint2 e = *reinterpret_cast<const uint2*>(reinterpret_cast<const char*>(G.adj) + (w.off + (j & ~7u)));
+        w.x = e.x;
+        w.off = e.y;
     } else if (kLayout == kLayoutCompact || kLayout == kLayoutCompactHub || hubid_layout(kLayout)) {
         // the 3 bytes at byte offset 3*pos lie in the aligned 8 bytes at word (3*pos)/4
         const uint32_t o = pos * 3u;
@@ -404,6 +445,12 @@ __device__ __forceinline__ void stage_hubs(DevGraph& G, uint32_t* lds, uint32_t 
         G.nhub = G.run_h1;
         G.rec_word = run_records_at(G.run_h1);
         G.inv = reinterpret_cast<const float*>(lds + inv_at);
+        (void)capacity;
+    } else if constexpr (kLayout == kLayoutFat8) {
+        for (uint32_t i = threadIdx.x; i <= kFat8Degree; i += blockDim.x)
+            lds[2u * i] = __float_as_uint(__fdiv_rn(1.0f, (float)max(i, 1u)));
+        __syncthreads();
+        G.inv = reinterpret_cast<const float*>(lds);
         (void)capacity;
     } else if constexpr (hubid_layout(kLayout)) {
         const uint32_t nh = min(capacity, G.dom.n);

@@ -192,8 +192,8 @@ struct bd_graph {
     int32_t d_min = 0, d_max = 0;
     int32_t bipartite = 0;
     int32_t layout = 0;  // 0 CSR, 1 fat, 2 compact, ... (kLayout* of the kernels)
-    int32_t kernel_layout = 0;  // the kernels' layout code: layout, 6 for fat with non-temporal
-                                // loads, 7, 8 or 9 for layout 5 (kLayout* of the kernels)
+    int32_t kernel_layout = 0;  // the kernels' layout code: layout, 6 or 10 for fat, 7, 8 or 9 for
+                                // layout 5 (kLayout* of the kernels)
     int device = 0;
     uint32_t cus = 0;                // compute units of the device
     std::vector<int32_t> deg;        // host copy for the planner, by caller id
@@ -430,8 +430,9 @@ uint32_t storage_id(const bd_graph* g, int32_t v)
 // the full device's rate or above it), and every further one brings other
 // queries' neighbourhoods into the same L2. Queries with fewer pairs than an XCD
 // then runs at once get one group per CU: 1,024 grid queries of 1,332 pairs took
-// 78.5 ms on all resident groups, 49.7 on two and 33.3 on one, and one costs a
-// single large query 2%. The 1,024-thread kernels do the same only where
+// 78.5 ms on all resident groups, 49.7 on two and 33.3 on one with 16-byte
+// entries (with 8 bytes, twice as many queries 165, 112 and 72 ms), and one
+// costs a single large query 2%. The 1,024-thread kernels do the same only where
 // their tables exceed the L2s together (the grid 46.3 ms on two, 35.0 on one):
 // within L2 their two groups hide its latency. Walk sharing, bound by the
 // probes' arithmetic, keeps all.
@@ -701,7 +702,9 @@ extern "C" int graph_load_csr(int64_t n, const int64_t* row_ptr, const int32_t* 
         const bool nt = (flags & BD_NONTEMPORAL) ? true
                         : (flags & BD_TEMPORAL)  ? false
                                                  : fat_bytes >= kFatNontemporalBytes;
-        if (nt) g->kernel_layout = 6;
+        if (nt) g->kernel_layout = kLayoutFatNT;
+        else if (n <= (int64_t(1) << 22) && nnz < (int64_t(1) << 29) && dmax <= kFat8Degree)
+            g->kernel_layout = kLayoutFat8;
     }
     g->device = dev;
     {
@@ -735,7 +738,8 @@ extern "C" int graph_load_csr(int64_t n, const int64_t* row_ptr, const int32_t* 
     if (rc == BD_OK && !packed) rc = g->col.alloc((size_t)std::max<int64_t>(nnz, 1) * 4);
     if (rc == BD_OK && g->layout < 2) rc = g->node.alloc((size_t)n * 16);
     if (rc == BD_OK && (g->layout == 3 || g->layout == 4)) rc = g->node8.alloc(((size_t)n + 1) * 8);
-    if (rc == BD_OK && g->layout == 1) rc = g->adj.alloc((size_t)std::max<int64_t>(nnz, 1) * 16);
+    const size_t fat_entry = g->kernel_layout == kLayoutFat8 ? 8 : 16;
+    if (rc == BD_OK && g->layout == 1) rc = g->adj.alloc((size_t)std::max<int64_t>(nnz, 1) * fat_entry);
     if (rc == BD_OK &&
         ((packed && zero_pad24(g->col24, (size_t)nnz, st) != hipSuccess) ||
          launch_rename(csr.view, (uint32_t)nnz, d_order.as<const uint32_t>(), d_internal.as<const uint32_t>(),
@@ -749,8 +753,8 @@ extern "C" int graph_load_csr(int64_t n, const int64_t* row_ptr, const int32_t* 
         return rc;
     }
     if (g->layout == 1 &&
-        build_fat_adjacency(g->node.as<uint4>(), g->col.as<uint32_t>(), g->adj.as<uint4>(),
-                            (uint32_t)nnz, st) != hipSuccess) {
+        build_fat_adjacency(g->node.as<uint4>(), g->col.as<uint32_t>(), g->adj.p, g->kernel_layout, (uint32_t)nnz, st) !=
+            hipSuccess) {
         delete g;
         return BD_E_HIP;
     }

@@ -140,7 +140,7 @@ constexpr uint32_t kMaxShare = 4;
 inline int share_class(uint32_t M) { return M <= 1 ? 1 : M <= 2 ? 2 : 4; }
 
 // Layout codes of the kernels (0-5 are the graph layouts bd_graph_get_info
-// reports; 6 is a kernel variant of layout 1, 7 and 8 of layout 5), and the hub
+// reports; 6 and 10 are kernel variants of layout 1, 7 to 9 of layout 5), and the hub
 // nodes they stage in LDS.
 constexpr int kLayoutCsr = 0, kLayoutFat = 1, kLayoutCompact = 2, kLayoutCompactHub = 3, kLayoutHub32 = 4,
               kLayoutHubId = 5;
@@ -149,6 +149,15 @@ constexpr int kLayoutCsr = 0, kLayoutFat = 1, kLayoutCompact = 2, kLayoutCompact
 // anyway and keeping the entries out of the caches' replacement order leaves
 // them to the node entries of the walks' start nodes.
 constexpr int kLayoutFatNT = 6;
+// The fat layout in 8 bytes an entry, {id << kFat8Shift | degree << 3, byte offset
+// of the row}, for graphs of at most 2^22 nodes, 2^29 - 1 entries and degrees of
+// at most kFat8Degree; 1.0f/d comes from LDS.
+// Twice as much of a walk's neighbourhood stays in L2: of 1,024 grid queries
+// (n = 2e6, L up to 5,000) 1.67e9 reads missed it and 0.60e9 do, 36.4 -> 30.9 ms;
+// one query of 37 x 64 x 300 pairs on a grid of 500,000 12.5 -> 9.0 ms. Launches
+// of less than a wave a SIMD, bound by a step's latency, lose 2 to 5%.
+constexpr int kLayoutFat8 = 10;
+constexpr int kFat8Degree = 127, kFat8Shift = 10;
 // Layout 5's tables with one 1,024-thread work group per CU: 36,864 hub row
 // offsets (144 KB of LDS) and two replica pairs per lane, so four dependent
 // load chains per lane keep as many loads in flight at four waves per SIMD as
@@ -198,10 +207,11 @@ constexpr uint32_t hub_nodes(int threads, int layout)
     if (layout == kLayoutHubRunsNarrow) return threads >= 1024 ? 16383u : kRunWordsShared - 1u;
     return (threads >= 1024 ? 8192u : 1024u) * (layout == kLayoutHubIdX2 ? 4u : layout == kLayoutHubId ? 2u : 1u);
 }
-// 32-bit words of the LDS hub copy (entries 0 .. hub_nodes, inclusive)
+// 32-bit words of the LDS hub copy (entries 0 .. hub_nodes, inclusive), or of
+// layout code 10's reciprocals
 constexpr uint32_t hub_words(int threads, int layout)
 {
-    return !hub_layout(layout) ? 2u : hubid_layout(layout) ? hub_nodes(threads, layout) + 1u
+    return layout == kLayoutFat8 ? 2u * (kFat8Degree + 1u) : !hub_layout(layout) ? 2u : hubid_layout(layout) ? hub_nodes(threads, layout) + 1u
                                                             : 2u * (hub_nodes(threads, layout) + 1u);
 }
 
@@ -259,7 +269,7 @@ hipError_t launch_components(const CsrView& g, int64_t nnz, uint32_t* parent, ui
 hipError_t launch_rename(const CsrView& g, uint32_t nnz, const uint32_t* order, const uint32_t* map, const uint32_t* rp,
                          uint32_t* ids, uint8_t* ids24, hipStream_t st);
 hipError_t launch_nodes(uint32_t n, const uint32_t* order, const uint32_t* rp, uint4* node, uint2* node8, hipStream_t st);
-hipError_t build_fat_adjacency(const uint4* node, const uint32_t* col, uint4* adj, uint32_t nnz,
+hipError_t build_fat_adjacency(const uint4* node, const uint32_t* col, void* adj, int layout, uint32_t nnz,
                                hipStream_t st);
 // Gather-roofline microbenchmark: `chains` in {1, 2, 4, 8} chains per lane.
 hipError_t launch_gather(const GraphTables& g, int layout, int chains, uint32_t grid, int32_t steps, uint32_t seed,

@@ -58,10 +58,11 @@ template <int kLayout>
 __device__ __forceinline__ float advance(WalkState& w, float acc, uint32_t u, const DevGraph& G,
                                          const Probe& pr)
 {
+    resolve<kLayout>(w, G);
     const uint32_t xp = w.x;
     const float ip = w.inv;
     step<kLayout>(w, u, G);
-    return add_term(acc, xp, ip, pr, G.dom);
+    return add_term<kLayout>(acc, xp, ip, pr, G.dom);
 }
 
 // U_p = a - b for replica p of probe k (Algorithm 1 walk loop, eq. for phi-hat).
@@ -100,8 +101,10 @@ __device__ __forceinline__ float walk_pair(const DevGraph& G, const Probe& pr, W
             b = advance<kLayout>(wt, b, rt.z, G, pr);
         }
     }
-    a = add_term(a, ws.x, ws.inv, pr, G.dom);
-    b = add_term(b, wt.x, wt.inv, pr, G.dom);
+    resolve<kLayout>(ws, G);
+    resolve<kLayout>(wt, G);
+    a = add_term<kLayout>(a, ws.x, ws.inv, pr, G.dom);
+    b = add_term<kLayout>(b, wt.x, wt.inv, pr, G.dom);
     return __fsub_rn(a, b);
 }
 
@@ -162,10 +165,10 @@ __device__ __forceinline__ void walk_pair2(const DevGraph& G, const Probe& pr1, 
             b2 = advance<kLayout>(t2, b2, rt2.z, G, pr2);
         }
     }
-    a1 = add_term(a1, s1.x, s1.inv, pr1, G.dom);
-    b1 = add_term(b1, t1.x, t1.inv, pr1, G.dom);
-    a2 = add_term(a2, s2.x, s2.inv, pr2, G.dom);
-    b2 = add_term(b2, t2.x, t2.inv, pr2, G.dom);
+    a1 = add_term<kLayout>(a1, s1.x, s1.inv, pr1, G.dom);
+    b1 = add_term<kLayout>(b1, t1.x, t1.inv, pr1, G.dom);
+    a2 = add_term<kLayout>(a2, s2.x, s2.inv, pr2, G.dom);
+    b2 = add_term<kLayout>(b2, t2.x, t2.inv, pr2, G.dom);
     *U1 = __fsub_rn(a1, b1);
     *U2 = __fsub_rn(a2, b2);
 }
@@ -177,12 +180,13 @@ template <int kLayout, int kShare>
 __device__ __forceinline__ void advance_m(WalkState& w, float* acc, uint32_t m, uint32_t u, const DevGraph& G,
                                           const Probe* pr)
 {
+    resolve<kLayout>(w, G);
     const uint32_t xp = w.x;
     const float ip = w.inv;
     step<kLayout>(w, u, G);
 #pragma unroll
     for (int j = 0; j < kShare; ++j)
-        if ((uint32_t)j < m) acc[j] = add_term(acc[j], xp, ip, pr[j], G.dom);
+        if ((uint32_t)j < m) acc[j] = add_term<kLayout>(acc[j], xp, ip, pr[j], G.dom);
 }
 
 // U_p for each probe of a group; the walks' streams are keyed by kw, the
@@ -224,11 +228,13 @@ __device__ __forceinline__ void walk_pair_m(const DevGraph& G, const Probe* pr, 
             advance_m<kLayout, kShare>(wt, b, m, rt.z, G, pr);
         }
     }
+    resolve<kLayout>(ws, G);
+    resolve<kLayout>(wt, G);
 #pragma unroll
     for (int j = 0; j < kShare; ++j) {
         if ((uint32_t)j < m) {
-            a[j] = add_term(a[j], ws.x, ws.inv, pr[j], G.dom);
-            b[j] = add_term(b[j], wt.x, wt.inv, pr[j], G.dom);
+            a[j] = add_term<kLayout>(a[j], ws.x, ws.inv, pr[j], G.dom);
+            b[j] = add_term<kLayout>(b[j], wt.x, wt.inv, pr[j], G.dom);
         }
         U[j] = __fsub_rn(a[j], b[j]);
     }
@@ -460,6 +466,7 @@ static const void* walk_fn(int layout, int uniform, int share)
 {
     if (layout == kLayoutFat) return walk_fn_l<kLayoutFat>(uniform, share);
     if (layout == kLayoutFatNT) return walk_fn_l<kLayoutFatNT>(uniform, share);
+    if (layout == kLayoutFat8) return walk_fn_l<kLayoutFat8>(uniform, share);
     if (layout == kLayoutCompact) return walk_fn_l<kLayoutCompact>(uniform, share);
     if (layout == kLayoutCompactHub) return walk_fn_l<kLayoutCompactHub>(uniform, share);
     if (layout == kLayoutHub32) return walk_fn_l<kLayoutHub32>(uniform, share);
@@ -498,6 +505,9 @@ hipError_t launch_walk(const WalkArgs& a, int layout, int uniform, int share, ui
     } else if (layout == kLayoutFatNT) {
         if (uniform) launch_l<kLayoutFatNT, 1>(a, share, grid, st);
         else launch_l<kLayoutFatNT, 0>(a, share, grid, st);
+    } else if (layout == kLayoutFat8) {
+        if (uniform) launch_l<kLayoutFat8, 1>(a, share, grid, st);
+        else launch_l<kLayoutFat8, 0>(a, share, grid, st);
     } else if (layout == kLayoutCompact) {
         if (uniform) launch_l<kLayoutCompact, 1>(a, share, grid, st);
         else launch_l<kLayoutCompact, 0>(a, share, grid, st);
@@ -557,21 +567,25 @@ hipError_t launch_zero(void* p, size_t bytes, hipStream_t st)
     return hipGetLastError();
 }
 
-__global__ void fat_kernel(const uint4* node, const uint32_t* col, uint4* adj, uint32_t nnz)
+template <int kLayout>
+__global__ void fat_kernel(const uint4* node, const uint32_t* col, void* adj, uint32_t nnz)
 {
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < nnz; i += gridDim.x * blockDim.x) {
         const uint4 e = node[col[i]];
-        adj[i] = make_uint4(e.w, e.x, e.y, e.z);
+        if constexpr (kLayout == kLayoutFat8) static_cast<uint2*>(adj)[i] = make_uint2(e.w << kFat8Shift | e.y << 3, e.x << 3);
+        else static_cast<uint4*>(adj)[i] = make_uint4(e.w, e.x, e.y, e.z);
     }
 }
 
-hipError_t build_fat_adjacency(const uint4* node, const uint32_t* col, uint4* adj, uint32_t nnz,
+hipError_t build_fat_adjacency(const uint4* node, const uint32_t* col, void* adj, int layout, uint32_t nnz,
                                hipStream_t st)
 {
     if (nnz == 0) return hipSuccess;
     uint32_t blocks = (nnz + 255) / 256;
     if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(fat_kernel, dim3(blocks), dim3(256), 0, st, node, col, adj, nnz);
+    if (layout == kLayoutFat8)
+        hipLaunchKernelGGL(fat_kernel<kLayoutFat8>, dim3(blocks), dim3(256), 0, st, node, col, adj, nnz);
+    else hipLaunchKernelGGL(fat_kernel<kLayoutFat>, dim3(blocks), dim3(256), 0, st, node, col, adj, nnz);
     return hipGetLastError();
 }
 
@@ -585,8 +599,8 @@ __global__ void trace_kernel(GraphTables gt, uint32_t count, const int32_t* star
 {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     DevGraph G = make_graph(gt);
-    if constexpr (runs_layout(kLayout)) {
-        // the run table in LDS, as the walk kernels read it
+    if constexpr (runs_layout(kLayout) || kLayout == kLayoutFat8) {
+        // the run table or the reciprocals in LDS, as the walk kernels read them
         __shared__ __align__(16) uint32_t lds[hub_words(1024, kLayout)];
         stage_hubs<kLayout>(G, lds, hub_nodes(1024, kLayout));
     }
@@ -596,16 +610,17 @@ __global__ void trace_kernel(GraphTables gt, uint32_t count, const int32_t* star
     WalkState w = start_at<kLayout>(G, x0);
     const uint32_t c3 = (uid[i] << 1) | side[i];
     int32_t* tr = trace ? trace + (size_t)i * (L + 1) : nullptr;
-    if (tr) tr[0] = (int32_t)w.x;
+    if (tr) tr[0] = (int32_t)node_id<kLayout>(w);
     float a = 0.0f;
     U4 r = U4{0, 0, 0, 0};
     for (int s = 0; s < L; ++s) {
         if ((s & 3) == 0) r = philox10((uint32_t)(s >> 2), pp[i], kk[i], c3, slo, shi);
         const uint32_t u = (s & 3) == 0 ? r.x : (s & 3) == 1 ? r.y : (s & 3) == 2 ? r.z : r.w;
         a = advance<kLayout>(w, a, u, G, pr);
-        if (tr) tr[s + 1] = (int32_t)w.x;
+        if (tr) tr[s + 1] = (int32_t)node_id<kLayout>(w);
     }
-    a = add_term(a, w.x, w.inv, pr, G.dom);
+    resolve<kLayout>(w, G);
+    a = add_term<kLayout>(a, w.x, w.inv, pr, G.dom);
     if (acc_out) acc_out[i] = a;
 }
 
@@ -619,6 +634,7 @@ hipError_t launch_trace(const GraphTables& g, int layout, uint32_t count, const 
 #define PW_TRACE(Lay) hipLaunchKernelGGL(trace_kernel<Lay>, dim3(blocks), dim3(128), 0, st, g, count, start, uid, k, p, side, L, slo, shi, trace, acc)
     if (layout == kLayoutFat) PW_TRACE(1);
     else if (layout == kLayoutFatNT) PW_TRACE(6);
+    else if (layout == kLayoutFat8) PW_TRACE(10);
     else if (layout == kLayoutCompact) PW_TRACE(2);
     else if (layout == kLayoutCompactHub) PW_TRACE(3);
     else if (layout == kLayoutHub32) PW_TRACE(4);
@@ -693,6 +709,7 @@ __global__ __launch_bounds__(block_threads(kLayout, 1)) void gather_kernel(Graph
             x ^= x >> 17;
             x ^= x << 5;
             rng[c] = x;
+            resolve<kLayout>(w[c], G);
             step<kLayout>(w[c], x, G);
         }
     }
@@ -715,6 +732,7 @@ hipError_t launch_gather(const GraphTables& g, int layout, int chains, uint32_t 
     } while (0)
     if (layout == kLayoutFat) PW_GATHER_C(1);
     else if (layout == kLayoutFatNT) PW_GATHER_C(6);
+    else if (layout == kLayoutFat8) PW_GATHER_C(10);
     else if (layout == kLayoutCompact) PW_GATHER_C(2);
     else if (layout == kLayoutCompactHub) PW_GATHER_C(3);
     else if (layout == kLayoutHub32) PW_GATHER_C(4);
