@@ -42,7 +42,7 @@ HBM_PEAK_GBS = 8000.0
 L2_PEAK_REQ_PER_S = 8 * 16 * 2.4e9   # one request per L2 channel per clock, 16 channels per XCD
 COUNTERS = os.path.join(ROOT, "profiles", "walk_kernel_cl100k_counters.txt")
 FAT_SCALE_COUNTERS = os.path.join(ROOT, "profiles", "walk_kernel_fat_cl40m_counters.txt")
-KERNEL_SOURCES = ["pw_kernels.hip", "pw_device.hpp", "pw_internal.hpp", "pw_runs.hpp"]
+KERNEL_SOURCES = ["pw_kernels.hip", "pw_signs.hip", "pw_chunk.hpp", "pw_device.hpp", "pw_internal.hpp", "pw_runs.hpp"]
 LAYOUT_NAMES = {0: "csr", 1: "fat", 2: "compact", 3: "compact, hubs first", 4: "hubs first, 4-byte ids",
                 5: "hubs first, probe on storage ids"}
 
@@ -655,9 +655,9 @@ def scale_cl40m(B, torch, stream, served_queries=65536, which=("csr", "hubs", "a
         dt_bl = time.perf_counter() - t0
         ref_routines = {
             "lambda": {"iterations": 200, "estimate": lam, "seconds": dt_lam,
-                       "device_bytes": 4 * 8 * g.n + 2 * 1024 * 8 + 16},
+                       "device_bytes": 2 * 8 * g.n + 4 * 512 * 8 + 8},
             "beta_truncated": {"pairs": 8, "L": 1000, "seconds": dt_bl, "beta": [float(x) for x in bl],
-                               "device_bytes_per_pass": 3 * 8 * g.n * 8, "free_device_bytes_before": int(free0)}}
+                               "device_bytes_per_pass": 2 * 8 * g.n * 8, "free_device_bytes_before": int(free0)}}
         dg.free()
     c_B, c_R, how = BUDGETS["cl40m"]
     best = max(layouts.values(), key=lambda x: x["batched_queries_per_s"])

@@ -250,14 +250,18 @@ int bd_plan(const bd_graph* g, int64_t nq, const int32_t* s, const int32_t* t,
 typedef struct {
     uint32_t mode;
     int32_t  chunk_probes;   /* probes per work-group chunk; 0 = from chunk_pairs */
-    int32_t  grid_wgs;       /* persistent grid size (BATCHED); 0 = resident capacity */
+    int32_t  grid_wgs;       /* persistent grid size (BATCHED); 0 = one or two work groups
+                                per compute unit on the 256-thread kernels (locality in
+                                L2), else resident capacity */
     int32_t  use_graph;      /* BATCHED: replay a captured hipGraph of the launch (work buffers
                                 are reused; the graph is rebuilt when the batch shape changes) */
     int32_t  chunk_pairs;    /* (probe, replica) pairs per chunk, also the replica-part size of
                                 a split probe (BATCHED); 0 = one per work-group thread (PLAIN:
                                 256, or 2048 on the hubs-first layouts with two pairs per
-                                thread, but at most the probes that give each compute unit a
-                                chunk) / 4096 (BATCHED) */
+                                thread, or the probes that a work group has sign tables for,
+                                but at most the probes that give each compute unit a chunk)
+                                / a sixth of an even share of the launch, at most 4096
+                                (BATCHED) */
     int32_t  queues;         /* BATCHED: chunk queues of the persistent launch, 1..8. A query's
                                 chunks stay in one queue and a work group takes chunks from the
                                 queue of the XCD it runs on before the others, so they share
@@ -316,8 +320,8 @@ int bd_query_batch(bd_graph* g, int64_t nq, const int32_t* s, const int32_t* t,
  * device memory and creates no events or streams; the caller still passes its
  * inputs and outputs in host memory and the graph stays as loaded.
  *   Arguments, results and errors as bd_query_batch, and additionally:
- *   - BD_E_SCRATCH when the batch's buffers exceed the array (about 650 bytes
- *     per query plus 32 per chunk, and 36 per probe of queries whose probes
+ *   - BD_E_SCRATCH when the batch's buffers exceed the array, also in chunks of
+ *     4,096 pairs, which are taken then (about 650 bytes per query plus 32 per chunk, and 36 per probe of queries whose probes
  *     are split in batched mode); nothing runs then;
  *   - BD_E_INVALID when the current device is not the graph's;
  *   - exec->use_graph is ignored (no hipGraph), and stats->walk_kernel_ms is
@@ -339,9 +343,10 @@ int bd_query_batch_noalloc(bd_graph* g, int64_t nq, const int32_t* s, const int3
  * L sparse products (the paper's PUSH series; a deterministic reference for
  * the estimator, which is unbiased for beta^(L) by Lemma 3.3).
  *   beta_L  host, nq doubles.
- * Up to 64 queries share one pass: three n x Q binary64 blocks (the series
- * term, the next term, the running sum), fewer queries per pass when those
- * would take more than half of the free device memory.
+ * Up to 64 queries share one pass: two n x Q binary64 blocks (h <- v0 + P h,
+ * from one to the other), fewer queries per pass when those would take more
+ * than half of the free device memory. Graphs of up to 2,048 nodes whose
+ * adjacency fits a work group's LDS run whole in one launch.
  */
 int bd_truncated_beta(bd_graph* g, int64_t nq, const int32_t* s, const int32_t* t, int32_t L,
                       void* stream, double* beta_L);
@@ -351,7 +356,7 @@ int bd_truncated_beta(bd_graph* g, int64_t nq, const int32_t* s, const int32_t* 
  * (section 2.1), estimated by `iters` power iterations on D^{-1/2} A D^{-1/2}
  * (same spectrum) with the stationary direction projected out; the estimate
  * is ||N x|| for the unit iterate x, which converges to lambda from below.
- * The iteration runs on the device (four n-vectors of binary64, the start
+ * The iteration runs on the device (two n-vectors of binary64, the start
  * vector a counter-based function of seed); only the estimate is copied back.
  */
 int bd_graph_lambda(bd_graph* g, int32_t iters, uint64_t seed, void* stream, double* lambda);
