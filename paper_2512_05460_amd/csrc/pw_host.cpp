@@ -19,7 +19,6 @@
 
 #include "probewalk.h"
 #include "pw_internal.hpp"
-#include "pw_signtab.hpp"
 
 using namespace pw;
 
@@ -1039,14 +1038,6 @@ int query_shape(const bd_graph* g, const QueryDesc& d)
     return 2 * scored >= positions * (!one_read ? 2 : share == 1 ? 16 : 3) ? best : -1;
 }
 
-// The one shape that a launch over several queries takes: the one that most of
-// their walk steps ask for.
-struct ShapeVote {
-    double steps[kSignShapes] = {};
-    void add(int shape, double work) { steps[shape] += work; }
-    int best() const { return (int)(std::max_element(steps, steps + kSignShapes) - steps); }
-};
-
 // Pairs of one pass over a work group, as chunks are sized by: those that a
 // work group of the general kernel runs at once, or 1,024 on the sign-table
 // kernels where that is more (chunks are never cut finer for it, so that a batch needs
@@ -1556,7 +1547,7 @@ void build_batch(const bd_graph* g, int64_t nq, const int32_t* s, const int32_t*
         const QueryDesc& d = b.qd[q];
         b.shapes.push_back(query_shape(g, d));
         const bool signs = b.shapes[q] >= 0;
-        if (signs) vote.add(b.shapes[q], cost(q));
+        if (signs) vote.add(b.shapes[q], (double)Groups(d).n * d.R * ((double)d.L + 1.0));
         lanes[q] = query_lanes(g, d, signs);
         const bool uniform = (int64_t)d.R >= umin;
         b.part[q] = (uint8_t)(signs ? (uniform ? kSignUniform : kSignAny) : (uniform ? kWalkUniform : kWalkAny));

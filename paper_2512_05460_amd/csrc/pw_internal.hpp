@@ -7,6 +7,7 @@
 #include <mutex>
 
 #include "pw_runs.hpp"
+#include "pw_signtab.hpp"
 
 namespace pw {
 
@@ -77,16 +78,6 @@ struct SignTables {
     uint32_t T;           // sign tables a work group holds
 };
 
-// A launch shape of the sign-table kernels for a graph and sharing class: one
-// to four work groups per CU.
-struct SignShape {
-    int lds = 0;           // 1: the adjacency is staged in LDS
-    uint32_t threads = 0;  // per work group; 0: the tables do not fit
-    uint32_t per_cu = 0;   // work groups a CU holds at once
-    uint32_t bytes = 0;    // dynamic LDS
-    uint32_t T = 0;        // sign tables
-};
-constexpr int kSignShapes = 4;
 // Dynamic LDS a work group can ask for: the CU's 160 KB less the kernels' static part.
 constexpr uint32_t kSignLdsMost = 160u * 1024u - 1280u;
 

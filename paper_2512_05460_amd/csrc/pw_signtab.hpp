@@ -1,5 +1,5 @@
-// Node order and block table of the sign-table kernels (host side, no HIP;
-// the kernels that read them are in pw_signs.hip).
+// Node order, block table and launch shapes of the sign-table kernels (host
+// side, no HIP; the kernels that read them are in pw_signs.hip).
 #pragma once
 
 #include <stddef.h>
@@ -9,6 +9,37 @@
 #include <vector>
 
 namespace pw {
+
+// A launch shape of the sign-table kernels for a graph and sharing class: one
+// to four work groups per CU.
+struct SignShape {
+    int lds = 0;           // 1: the adjacency is staged in LDS
+    uint32_t threads = 0;  // per work group; 0: the tables do not fit
+    uint32_t per_cu = 0;   // work groups a CU holds at once
+    uint32_t bytes = 0;    // dynamic LDS
+    uint32_t T = 0;        // sign tables
+};
+constexpr int kSignShapes = 4;
+
+// The one shape that a launch over several queries takes: the one that most of
+// their scored steps, pairs x (L + 1), ask for, and never one that none of them
+// asks for, which may be empty (threads = 0), not even where every count is 0.
+struct ShapeVote {
+    double steps[kSignShapes] = {};
+    bool asked[kSignShapes] = {};
+    void add(int shape, double work)
+    {
+        steps[shape] += work;
+        asked[shape] = true;
+    }
+    int best() const
+    {
+        int b = 0;
+        for (int i = 1; i < kSignShapes; ++i)
+            if (asked[i] && (!asked[b] || steps[i] > steps[b])) b = i;
+        return b;
+    }
+};
 
 constexpr uint32_t kSignShiftMin = 4, kSignShiftMax = 9;
 
