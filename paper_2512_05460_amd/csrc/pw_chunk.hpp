@@ -28,12 +28,16 @@ __device__ __forceinline__ void lds_add_i128(unsigned long long* p, i128 v)
     atomicAdd(p + 1, hi + carry);
 }
 
-// Waits until the atomics this wave has issued have been performed. What the work
-// groups of a query exchange are atomically updated words alone (block sums,
-// split-probe sums, counters), read back by atomic loads, so this order is all
-// they need; everything else a query leaves is read after the launch. A
-// device-scope fence here instead also writes the XCD's whole L2 back and
-// invalidates it: at L = 1 and R = 100 it made 480 us of what takes 261 us.
+// What the work groups of a query exchange while a launch runs are the words of
+// its block sums, split-probe sums and counters, and each access to them is a
+// read-modify-write at device scope, clearing included: there is one order of
+// them per word, whatever XCD they come from, and each sees the value that the one
+// before it left. Between words the order is the hardware's, not a fence's: a wave
+// waits here until its atomics have been performed, so that they come before
+// whatever another wave does once it has seen a counter that this one adds to
+// next. Everything else a query leaves is read after the launch. (A device-scope
+// fence would also write the XCD's whole L2 back and invalidate it: at L = 1 and
+// R = 100 it made 480 us of what takes 261 us.)
 __device__ __forceinline__ void atomics_performed()
 {
     asm volatile("" ::: "memory");
@@ -41,11 +45,12 @@ __device__ __forceinline__ void atomics_performed()
     asm volatile("" ::: "memory");
 }
 
-// A 128-bit sum as its atomic additions have left it (read by atomics too, so
-// that no cache of this XCD can hold an older value).
-__device__ __forceinline__ i128 read_i128(unsigned long long* p)
+// A 128-bit sum as its atomic additions have left it; its words are zero after
+// that, for the next query of the slot or range. (Adding 0 instead would be a plain
+// load: the compiler makes one of it.)
+__device__ __forceinline__ i128 take_i128(unsigned long long* p)
 {
-    const unsigned long long lo = atomicAdd(p, 0ull), hi = atomicAdd(p + 1, 0ull);
+    const unsigned long long lo = atomicExch(p, 0ull), hi = atomicExch(p + 1, 0ull);
     return (i128)(((u128)hi << 64) | (u128)lo);
 }
 
@@ -58,7 +63,7 @@ __device__ inline void finalize_query(const WalkArgs& A, const QueryDesc& d, dou
     const uint32_t G = d.G, g = threadIdx.x;
     unsigned long long* bs = A.blocksum + (size_t)d.slot * A.gdim * 2;
     if (g < G) {
-        const double y = (i128_to_f64(read_i128(bs + 2 * g)) * 0x1p-64) / (double)d.B;
+        const double y = (i128_to_f64(take_i128(bs + 2 * g)) * 0x1p-64) / (double)d.B;
         ys[g] = y;
         if (A.ybar_debug) A.ybar_debug[g] = y;
     }
@@ -71,14 +76,10 @@ __device__ inline void finalize_query(const WalkArgs& A, const QueryDesc& d, dou
         if (rank == G / 2u) ys[kMaxG + 1] = y;
     }
     __syncthreads();
-    if (A.recycle) {
-        // every chunk of this query has finished: the slot can be cleared for reuse
-        for (uint32_t i = g; i < 2 * A.gdim; i += blockDim.x) bs[i] = 0ull;
-    }
     if (g != 0) return;
     const double med = (G & 1u) ? ys[kMaxG] : 0.5 * (ys[kMaxG] + ys[kMaxG + 1]);
     A.beta[d.slot] = med;
-    if (A.recycle) A.done[(size_t)d.slot * A.done_stride] = 0u;
+    if (A.recycle) atomicExch(A.done + (size_t)d.slot * A.done_stride, 0u);
     if (A.comp_ring) {
         const uint32_t i = atomicAdd(A.comp_count, 1u);
         Completion c;
@@ -116,14 +117,13 @@ __device__ __forceinline__ void finish_parts(const WalkArgs& A, const QueryDesc&
             atomics_performed();
             const uint32_t prev = atomicAdd(A.pcount + pi, pc);
             if (prev + pc == d.R) {
-                const i128 S1 = read_i128(ps);
-                const u128 S2 = (u128)read_i128(ps + 2);
+                // every part of this probe has been added
+                const i128 S1 = take_i128(ps);
+                const u128 S2 = (u128)take_i128(ps + 2);
+                atomicExch(A.pcount + pi, 0u);
                 const double Q = probe_q(S1, S2, d.R);
                 if (A.q_debug) A.q_debug[k] = Q;
                 atomic_add_i128(A.blocksum + ((size_t)d.slot * A.gdim + k / d.B) * 2, f64_to_i128_trunc(Q * 0x1p64));
-                // every part of this probe has been added: clear it for reuse
-                ps[0] = ps[1] = ps[2] = ps[3] = 0ull;
-                A.pcount[pi] = 0u;
                 atomics_performed();
                 const uint32_t old = atomicAdd(A.done + (size_t)d.slot * A.done_stride, 1u);
                 if (old + 1u == d.K()) last = 1;

@@ -2528,7 +2528,8 @@ int process_completions(bd_server* S, const Slice& sl)
 
 // Cancelled requests whose slots no launched slice can touch any more: clear
 // the slots' device state (block sums, probe counter, split-probe
-// accumulators) on the admission stream, which every later slice waits for,
+// accumulators) on the admission stream, which every later slice waits for
+// (stores that write these words' bytes alone: slots in use share their lines),
 // free them, and finish the request with BD_E_CANCELLED for the queries that
 // had not finished. Caller holds mu.
 int reclaim_cancelled(bd_server* S)

@@ -106,7 +106,7 @@ struct WalkArgs {
     uint32_t* comp_count;           // optional (served mode): completions posted so far
     Completion* comp_ring;          // optional: ring of (slot, beta) completions
     uint32_t comp_cap;
-    uint32_t recycle;               // clear a finished query's block sums and counter
+    uint32_t recycle;               // clear a finished query's counter (its sums are cleared as they are read)
     uint32_t persistent;
     // Persistent launches: the chunk table is cut into nqueues segments
     // [qoff[i], qoff[i+1]), each with its own cursor cursor[i]. A work group
