@@ -1619,7 +1619,7 @@ void build_batch(const bd_graph* g, int64_t nq, const int32_t* s, const int32_t*
         // otherwise the kernel that runs any query takes them all
         for (const int part : {kSignUniform, kWalkUniform}) {
             const int i = part == kSignUniform ? 0 : 1;
-            if (!others[i] || uniform_chunks[i] >= (uint64_t)persistent_wgs(g, part, b.share, b.shape, b.pairs_per_query)) continue;
+            if (!others[i] || uniform_chunks[i] >= (uint64_t)resident_wgs(g, part, b.share, b.shape)) continue;
             for (uint8_t& p : b.part)
                 if (p == part) p = (uint8_t)(part + 1);
         }
@@ -2666,7 +2666,7 @@ void fill_slice(bd_server* S, Slice& sl)
     const int share = share_class(policy_share(S->pol));
     for (const int part : {kSignUniform, kWalkUniform}) {
         std::vector<Item>&u = items[part], &any = items[part + 1];
-        if (any.empty() || u.empty() || u.size() >= (size_t)server_wgs(S, part, sl.shape)) continue;
+        if (any.empty() || u.empty() || u.size() >= (size_t)resident_wgs(S->g, part, share, sl.shape)) continue;
         any.insert(any.begin(), u.begin(), u.end());
         u.clear();
     }
