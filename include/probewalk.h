@@ -250,9 +250,10 @@ int bd_plan(const bd_graph* g, int64_t nq, const int32_t* s, const int32_t* t,
 typedef struct {
     uint32_t mode;
     int32_t  chunk_probes;   /* probes per work-group chunk; 0 = from chunk_pairs */
-    int32_t  grid_wgs;       /* persistent grid size (BATCHED); 0 = one or two work groups
-                                per compute unit on the 256-thread kernels (locality in
-                                L2), else resident capacity */
+    int32_t  grid_wgs;       /* persistent grid size (BATCHED); 0 = one, two or four work
+                                groups per compute unit on the 256-thread kernels (by the
+                                walks' mean length: locality in L2), else resident
+                                capacity, or one for long walks of small queries */
     int32_t  use_graph;      /* BATCHED: replay a captured hipGraph of the launch (work buffers
                                 are reused; the graph is rebuilt when the batch shape changes) */
     int32_t  chunk_pairs;    /* (probe, replica) pairs per chunk, also the replica-part size of

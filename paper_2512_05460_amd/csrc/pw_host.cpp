@@ -41,6 +41,9 @@ constexpr int64_t kAutoCompactBytes = int64_t(12) << 20;
 // and -46% with 192 MB (the grid, whose locality lives in the caches).
 constexpr int64_t kFatNontemporalBytes = int64_t(4) << 30;
 constexpr int64_t kAllL2Bytes = int64_t(32) << 20;  // the eight XCDs' L2s
+// Tables beyond which the general kernels' launches count on locality
+// (persistent_wgs).
+constexpr int64_t kLongWalkBytes = int64_t(12) << 20, kWideEntryBytes = int64_t(16) << 20;
 
 #define HIP_TRY(expr)                                  \
     do {                                               \
@@ -423,26 +426,50 @@ uint32_t storage_id(const bd_graph* g, int32_t v)
     return g->internal.empty() ? (uint32_t)v : g->internal[(size_t)v];
 }
 
-// Work groups of a persistent launch of the general kernels, at most the
-// resident ones. Two 256-thread groups per CU already keep enough reads in
-// flight (Chung-Lu-like graphs of 1e5 to 1e7 nodes and the grid run within 2% of
-// the full device's rate or above it), and every further one brings other
-// queries' neighbourhoods into the same L2. Queries with fewer pairs than an XCD
-// then runs at once get one group per CU: 1,024 grid queries of 1,332 pairs took
-// 78.5 ms on all resident groups, 49.7 on two and 33.3 on one with 16-byte
-// entries (with 8 bytes, twice as many queries 165, 112 and 72 ms), and one
-// costs a single large query 2%. The 1,024-thread kernels do the same only where
-// their tables exceed the L2s together (the grid 46.3 ms on two, 35.0 on one):
-// within L2 their two groups hide its latency. Walk sharing, bound by the
-// probes' arithmetic, keeps all.
-int persistent_wgs(const bd_graph* g, int part, int share, int shape, double pairs_per_query)
+// What a launch's queries on the general kernels ask for, on average.
+struct GeneralLoad {
+    double pairs_per_query = 0.0;
+    double steps_per_walk = 0.0;
+};
+
+// Work groups of a persistent launch of the general kernels, at most the resident
+// ones. Every further group brings other queries' neighbourhoods into the same L2,
+// and those grow with the walks' length; what fewer groups lose is reads in
+// flight, which short walks (whose neighbourhoods fit anyhow) need. Kernel ms on
+// one, two and four 256-thread groups per CU, queries of 1,184 pairs:
+//   grid of 2e6 nodes, 8-byte entries: L = 30 0.35, 0.25, 0.24; 100 0.93, 0.72,
+//     0.70; 300 2.6, 2.4, 2.8; 700 12.3, 13.6, 19.6; 1,000 9.7, 11.1, 17.5;
+//   the same on compact ids: L = 100 1.49, 1.08, 0.92; 600 9.3, 8.4, 10.8; 1,000
+//     17.4, 17.1, 25.1; 5,000 50, 58, 88;
+//   grid of 250,000 nodes, compact (8 MB): L = 1,000 15.1, 13.7, 14.6;
+//   Chung-Lu-like, n = 300,000, 16-byte entries: L = 30 1.01, 1.04, 1.10; 1,000
+//     35.7, 37.2, 37.7 (n = 10,000, 3 MB of tables: L = 200 2.31, 2.10, 2.28).
+// So four groups for walks of up to 120 steps, two up to 600, and beyond that one
+// where a query has fewer pairs than an XCD then runs at once and the tables are
+// large; with 16-byte entries and such tables one always, or two for queries of
+// more pairs. Non-temporal entries come from memory at every step and take two:
+// 65,536 queries on 20.7 GB of them 2,855 ms on one, 2,686 on two and on all.
+// The 1,024-thread kernels take one group for such long walks of small queries
+// where their tables exceed the L2s together (the grid, hubs first, L = 1,000 26.0
+// for 29.1 ms; within L2 their two groups hide its latency). On the degree-run
+// table, with one read a step, only from 2,000 steps and a work group's pairs on
+// (L = 3,000 53.5 for 68.5 ms, 1,000 14.3 for 13.2; queries of 222 pairs 54 for 37).
+// Walk sharing, bound by the probes' arithmetic, keeps all.
+int persistent_wgs(const bd_graph* g, int part, int share, int shape, const GeneralLoad& load)
 {
     const int r = resident_wgs(g, part, share, shape);
     if (sign_part(part) || share > 1) return r;
-    const int threads = block_threads(run_kernel(g, share), share), cus = (int)g->cus;
-    const bool small = pairs_per_query <= (double)cus / kMaxQueues * threads;
-    if (threads == kBlockThreads) return std::min(r, small ? cus : 2 * cus);
-    return small && g->device_bytes > kAllL2Bytes ? std::min(r, cus) : r;
+    const int layout = run_kernel(g, share), threads = block_threads(layout, share), cus = (int)g->cus;
+    const bool small = load.pairs_per_query <= (double)cus / kMaxQueues * threads;
+    if (threads != kBlockThreads) {
+        const bool far = runs_layout(layout) ? load.steps_per_walk > 2000.0 && load.pairs_per_query >= (double)threads
+                                             : load.steps_per_walk > 600.0;
+        return small && far && g->device_bytes > kAllL2Bytes ? std::min(r, cus) : r;
+    }
+    if (layout == kLayoutFatNT) return std::min(r, 2 * cus);
+    if (layout == kLayoutFat && g->device_bytes > kWideEntryBytes) return std::min(r, small ? cus : 2 * cus);
+    if (load.steps_per_walk <= 120.0) return std::min(r, 4 * cus);
+    return std::min(r, small && load.steps_per_walk > 600.0 && g->device_bytes > kLongWalkBytes ? cus : 2 * cus);
 }
 
 // Launch shapes of the sign-table kernels for M probes per walk: four to one
@@ -1174,7 +1201,7 @@ struct Batch {
     std::vector<uint8_t> part;          // per valid query, its kernel part
     std::vector<int> shapes;            // per valid query, the sign-table kernels' shape for it (-1: general kernel)
     int shape = 0;                      // the shape of the batched sign-table launches
-    double pairs_per_query = 0.0;       // of the queries on the general kernels
+    GeneralLoad load;                   // of the queries on the general kernels
     // chunk queues of the persistent launches: qoff[part][i] is the first chunk
     // of queue i relative to the part
     uint32_t nqueues = 1;
@@ -1349,7 +1376,7 @@ int run_batch(bd_graph* g, const Batch& b, const bd_exec& ex, hipStream_t user_s
         const uint32_t nch = b.part_begin[part + 1] - b.part_begin[part];
         if (nch == 0) continue;
         uint32_t grid = ex.grid_wgs > 0 ? (uint32_t)ex.grid_wgs
-                                         : (uint32_t)persistent_wgs(g, part, b.share, b.shape, b.pairs_per_query);
+                                         : (uint32_t)persistent_wgs(g, part, b.share, b.shape, b.load);
         grids[part] = std::min<uint32_t>(grid, nch);
     }
     auto launch_persistent = [&](hipStream_t s2) -> int {
@@ -1579,7 +1606,7 @@ void build_batch(const bd_graph* g, int64_t nq, const int32_t* s, const int32_t*
         pairs_of[f] += n;
         general += f;
     }
-    b.pairs_per_query = general ? pairs_of[1] / (double)general : 0.0;
+    if (general) b.load = GeneralLoad{pairs_of[1] / (double)general, total[1] / pairs_of[1] - 1.0};
     if (ex.mode != BD_MODE_PLAIN && spread_chunks && ex.chunk_pairs <= 0 && ex.chunk_probes <= 0) {
         double lane_steps[2] = {0.0, 0.0};  // of every lane of the device
         uint32_t wg[2] = {0, 0};
@@ -1587,7 +1614,7 @@ void build_batch(const bd_graph* g, int64_t nq, const int32_t* s, const int32_t*
             if (total[f] == 0.0) continue;
             wg[f] = f == 0 ? sign_shape(g, b.share, b.shape).threads : (uint32_t)group_pairs(g->kernel_layout, b.share);
             const int part = f == 0 ? kSignUniform : kWalkAny;
-            lane_steps[f] = total[f] / ((double)persistent_wgs(g, part, b.share, b.shape, b.pairs_per_query) * wg[f]);
+            lane_steps[f] = total[f] / ((double)persistent_wgs(g, part, b.share, b.shape, b.load) * wg[f]);
         }
         for (size_t q = 0; q < b.qd.size(); ++q) {
             const QueryDesc& d = b.qd[q];
@@ -2391,7 +2418,7 @@ bd_exec server_exec(const bd_server* S, uint32_t lanes)
 // Work groups of a slice's launch (its chunks come from many requests).
 int server_wgs(const bd_server* S, int part, int shape)
 {
-    return persistent_wgs(S->g, part, share_class(policy_share(S->pol)), shape, 1e18);
+    return persistent_wgs(S->g, part, share_class(policy_share(S->pol)), shape, GeneralLoad{1e18, 1e18});
 }
 
 // Whether the query's replicas are split over chunks (it then needs accumulators).
