@@ -1609,12 +1609,13 @@ void build_batch(const bd_graph* g, int64_t nq, const int32_t* s, const int32_t*
     if (general) b.load = GeneralLoad{pairs_of[1] / (double)general, total[1] / pairs_of[1] - 1.0};
     if (ex.mode != BD_MODE_PLAIN && spread_chunks && ex.chunk_pairs <= 0 && ex.chunk_probes <= 0) {
         double lane_steps[2] = {0.0, 0.0};  // of every lane of the device
-        uint32_t wg[2] = {0, 0};
+        uint32_t wg[2] = {0, 0}, wgs[2] = {0, 0};  // lanes of a work group, work groups
         for (const int f : {0, 1}) {
             if (total[f] == 0.0) continue;
             wg[f] = f == 0 ? sign_shape(g, b.share, b.shape).threads : (uint32_t)group_pairs(g->kernel_layout, b.share);
             const int part = f == 0 ? kSignUniform : kWalkAny;
-            lane_steps[f] = total[f] / ((double)persistent_wgs(g, part, b.share, b.shape, b.load) * wg[f]);
+            wgs[f] = (uint32_t)persistent_wgs(g, part, b.share, b.shape, b.load);
+            lane_steps[f] = total[f] / ((double)wgs[f] * wg[f]);
         }
         for (size_t q = 0; q < b.qd.size(); ++q) {
             const QueryDesc& d = b.qd[q];
@@ -1624,6 +1625,12 @@ void build_batch(const bd_graph* g, int64_t nq, const int32_t* s, const int32_t*
             // (less than a pass where the device has a compute unit for every chunk)
             const double each = std::ceil(pairs_of[f] / (2.0 * g->cus));
             if (each < fit) fit = std::max((uint32_t)each, 64u);
+            // (a query of up to two passes of a 1,024-thread work group stays whole
+            // where every work group gets one: 512 of 1,184 pairs, L = 400, on the
+            // grid took 2.09 ms in chunks of a pass and its rest, 1.46 so; of fewer
+            // queries, 300 are better cut and 200 whole)
+            const double all = (double)Groups(d).n * d.R;
+            if (f == 1 && wg[f] >= 1024u && general >= wgs[f] && all <= 2.0 * wg[f]) fit = std::max(fit, (uint32_t)all);
             const uint32_t whole = std::min<uint32_t>((d.R + 63u) & ~63u, kSplitReplicas);
             pairs[q] = (int32_t)std::max(fit, whole);
         }
