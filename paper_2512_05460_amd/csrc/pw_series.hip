@@ -342,7 +342,8 @@ __global__ __launch_bounds__(1024) void series_small_kernel(const uint4* tab, ui
             if (__ballot(j < have[k])) most[k] = j + 1u;
         }
     }
-    // a 16-lane group's first long row: 1/d (a division each step for further ones)
+    // a 16-lane group's first long row: 1/d (a division each step for further ones; the
+    // same product for both, since which rows come first differs from run to run)
     const uint32_t long0 = threadIdx.x / 16u < nl ? order[ns + threadIdx.x / 16u] : n;
     const double linv = long0 < n ? 1.0 / (double)(rows[long0] >> 16) : 0.0;
     auto at = [&](uint32_t byte) { return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(h) + byte); };
@@ -371,7 +372,7 @@ __global__ __launch_bounds__(1024) void series_small_kernel(const uint4* tab, ui
                 if (j + 48u < e) a3 += at(2u * ids[j + 48u]);
             }
             const double s = row_sum16((a0 + a1) + (a2 + a3));
-            if ((threadIdx.x & 15u) == 0u) next[x] = seeded(x, x == long0 ? s * linv : s / (double)(w >> 16));
+            if ((threadIdx.x & 15u) == 0u) next[x] = seeded(x, s * (x == long0 ? linv : 1.0 / (double)(w >> 16)));
         }
         __syncthreads();
         double* t = h;
