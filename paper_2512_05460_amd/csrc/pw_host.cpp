@@ -1891,7 +1891,8 @@ extern "C" int bd_truncated_beta(bd_graph* g, int64_t nq, const int32_t* s, cons
     DevBuf dh, dy, dpart, dbeta;
     int rc = dh.alloc(matrix(Qmax));
     if (rc == BD_OK) rc = dy.alloc(matrix(Qmax));
-    if (rc == BD_OK) rc = dpart.alloc((size_t)kSeriesParts * 2 * 8 * series_columns(Qmax) * series_slabs(Qmax));
+    if (rc == BD_OK)
+        rc = dpart.alloc((size_t)kSeriesParts * 2 * 8 * series_columns(Qmax) * series_slabs(Qmax) + sizeof(SeriesSeeds));
     if (rc == BD_OK) rc = dbeta.alloc(64 * 8);
     if (rc != BD_OK) return rc;
     for (int64_t q0 = 0; q0 < nq; q0 += Qmax) {

@@ -279,9 +279,10 @@ struct SeriesPair {
 constexpr uint32_t kHubDegree = 64;          // rows above it get a work group of their own
 constexpr uint32_t kSeriesParts = 512;       // partial sums per column
 constexpr uint32_t kSeriesSmallNodes = 2048; // largest graph of the one-work-group form
+constexpr uint32_t kSeriesShortRow = 16;     // rows up to it take a lane there, longer ones 16
 uint32_t series_columns(uint32_t Q);         // columns a slab
 uint32_t series_slabs(uint32_t Q);           // slabs of Q columns
-// H and Y: n x series_columns x series_slabs doubles each; part: 2 kSeriesParts a column.
+// H and Y: n x series_columns x series_slabs doubles each; part: 2 kSeriesParts a column and a SeriesSeeds.
 hipError_t launch_series(const uint32_t* rp, const uint32_t* col, const uint32_t* col24, uint32_t n,
                          const uint32_t* hubs, uint32_t nhub, uint32_t Q, int32_t L, const SeriesSeeds& seeds, double* H,
                          double* Y, double* part, double* beta, hipStream_t st);

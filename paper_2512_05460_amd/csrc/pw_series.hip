@@ -26,7 +26,7 @@ struct RowTables {
     }
 };
 
-// V columns that a lane sums at once: two (a 16-byte load) where a row has them.
+// V columns that a lane sums at once: two are a 16-byte load.
 template <int V>
 struct Cols {
     double v[V];
@@ -126,20 +126,20 @@ __device__ __forceinline__ double block_columns(double v, double* lds)
 // work groups take consecutive slabs, so that every XCD works on few slabs and
 // its 4 MB L2 holds their often-read rows. The step is bound by the gather of
 // nnz x 8 Q bytes, by L2 misses first: a row of 16 columns is one 128-byte line,
-// all of which is used. A lane owns two columns of a row (16-byte loads; P lanes
-// share the neighbours where C is small), and rows of more than kHubDegree
+// all of which is used. A lane owns V columns of a row (two: 16-byte loads; P lanes
+// share the neighbours where C or the graph is small), and rows of more than kHubDegree
 // neighbours, which would keep their wave for long after the others have ended,
 // get a work group each.
 // Chung-Lu-like graph, n = 1e5, 1e6 entries, 64 columns, a step: 417 us as one
 // wave per row over 64-column rows; 63 us so (slabs of 8: 80 us, of 32: 63 us;
 // 8,192 waves looping over the rows instead of a wave a row: 91 us).
 // ---------------------------------------------------------------------------
-template <int C, int P>
+template <int C, int P, int V>
 __global__ __launch_bounds__(256) void series_step_kernel(RowTables g, uint32_t n, const uint32_t* hubs, uint32_t nhub,
-                                                          uint32_t sbits, SeriesSeeds seeds, const double* H, double* Y)
+                                                          uint32_t sbits, const SeriesSeeds* seeds, const double* H,
+                                                          double* Y)
 {
     __shared__ double lds[256];
-    constexpr int V = C > 1 ? 2 : 1;
     constexpr uint32_t kColLanes = C / V, kLanes = kColLanes * P, kRowsAtOnce = 256u / kLanes;
     const uint32_t slab = blockIdx.x & ((1u << sbits) - 1u);
     const uint32_t c = (threadIdx.x & (kColLanes - 1u)) * V, q = slab * C + c;
@@ -147,10 +147,10 @@ __global__ __launch_bounds__(256) void series_step_kernel(RowTables g, uint32_t 
     double vs[V], vt[V];
 #pragma unroll
     for (int i = 0; i < V; ++i) {
-        s[i] = seeds.s[q + i];
-        t[i] = seeds.t[q + i];
-        vs[i] = seeds.vs[q + i];
-        vt[i] = seeds.vt[q + i];
+        s[i] = seeds->s[q + i];
+        t[i] = seeds->t[q + i];
+        vs[i] = seeds->vs[q + i];
+        vt[i] = seeds->vt[q + i];
     }
     H += (size_t)slab * n * C;
     Y += (size_t)slab * n * C;
@@ -184,9 +184,18 @@ __global__ __launch_bounds__(256) void series_step_kernel(RowTables g, uint32_t 
     }
 }
 
+// v_0; and the seeds left in memory for the steps, whose launches are a
+// microsecond each longer with 1.5 KB of arguments.
 template <int C>
-__global__ __launch_bounds__(256) void series_start_kernel(uint32_t n, uint32_t sbits, SeriesSeeds seeds, double* H)
+__global__ __launch_bounds__(256) void series_start_kernel(uint32_t n, uint32_t sbits, SeriesSeeds seeds, double* H,
+                                                           SeriesSeeds* kept)
 {
+    if (blockIdx.x == 0 && threadIdx.x < 64u) {
+        kept->s[threadIdx.x] = seeds.s[threadIdx.x];
+        kept->t[threadIdx.x] = seeds.t[threadIdx.x];
+        kept->vs[threadIdx.x] = seeds.vs[threadIdx.x];
+        kept->vt[threadIdx.x] = seeds.vt[threadIdx.x];
+    }
     const uint32_t slab = blockIdx.x & ((1u << sbits) - 1u), item = blockIdx.x >> sbits;
     const uint32_t c = threadIdx.x & (C - 1u), q = slab * C + c;
     const uint32_t row = item * (256u / C) + threadIdx.x / C;
@@ -231,22 +240,31 @@ __global__ __launch_bounds__(256) void series_finish_kernel(uint32_t n, const do
     if (threadIdx.x == 0) beta[blockIdx.x] = sq - lin * lin / (double)n;
 }
 
-template <int C, int P>
+template <int C, int P, int V>
 static hipError_t series_on(const RowTables& g, uint32_t n, const uint32_t* hubs, uint32_t nhub, uint32_t sbits,
                             uint32_t Q, int32_t L, const SeriesSeeds& seeds, double* H, double* Y, double* part,
                             double* beta, hipStream_t st)
 {
-    const uint32_t per = 256u / ((C > 1 ? C / 2 : C) * P), rows = (n + per - 1) / per, all = (n + 256u / C - 1) / (256u / C);
+    const uint32_t per = 256u / (C / V * P), rows = (n + per - 1) / per, all = (n + 256u / C - 1) / (256u / C);
     const dim3 block(256);
-    hipLaunchKernelGGL((series_start_kernel<C>), dim3(all << sbits), block, 0, st, n, sbits, seeds, H);
+    SeriesSeeds* kept = reinterpret_cast<SeriesSeeds*>(part + ((size_t)C << sbits) * kSeriesParts * 2);
+    hipLaunchKernelGGL((series_start_kernel<C>), dim3(all << sbits), block, 0, st, n, sbits, seeds, H, kept);
     for (int32_t i = 0; i < L; ++i) {
-        hipLaunchKernelGGL((series_step_kernel<C, P>), dim3((rows + nhub) << sbits), block, 0, st, g, n, hubs, nhub, sbits, seeds, H, Y);
+        hipLaunchKernelGGL((series_step_kernel<C, P, V>), dim3((rows + nhub) << sbits), block, 0, st, g, n, hubs, nhub, sbits, kept, H, Y);
         std::swap(H, Y);
     }
     hipLaunchKernelGGL((series_sums_kernel<C>), dim3(kSeriesParts << sbits), block, 0, st, n, sbits, H, part);
     hipLaunchKernelGGL(series_finish_kernel, dim3(Q), block, 0, st, n, part, beta);
     return hipGetLastError();
 }
+
+// Rows (of all slabs) up to which a row's lanes are a wave or half of one: with
+// fewer rows than that, lanes of their own for a row's columns alone leave most of
+// the device idle and a long row's reads one after another. A step (a
+// microsecond of it since saved in the launch) at n = 3,000, 62 neighbours a row,
+// 1, 8 and 16 columns: 5.1, 6.6, 7.0 us so, 6.3, 10.9, 12.3 else; n = 10,000, 10 a
+// row, 48 columns 18.2 so, 15.8 else.
+constexpr uint32_t kSeriesWaveRows = 8000;
 
 uint32_t series_columns(uint32_t Q)
 {
@@ -268,12 +286,16 @@ hipError_t launch_series(const uint32_t* rp, const uint32_t* col, const uint32_t
     const RowTables g{rp, col, col24};
     uint32_t sbits = 0;
     while ((1u << sbits) < series_slabs(Q)) ++sbits;
+    auto on = [&](auto narrow, auto wave) {
+        return (n << sbits) > kSeriesWaveRows ? narrow(g, n, hubs, nhub, sbits, Q, L, seeds, H, Y, part, beta, st)
+                                    : wave(g, n, hubs, nhub, sbits, Q, L, seeds, H, Y, part, beta, st);
+    };
     switch (series_columns(Q)) {
-    case 1: return series_on<1, 4>(g, n, hubs, nhub, sbits, Q, L, seeds, H, Y, part, beta, st);
-    case 2: return series_on<2, 4>(g, n, hubs, nhub, sbits, Q, L, seeds, H, Y, part, beta, st);
-    case 4: return series_on<4, 2>(g, n, hubs, nhub, sbits, Q, L, seeds, H, Y, part, beta, st);
-    case 8: return series_on<8, 1>(g, n, hubs, nhub, sbits, Q, L, seeds, H, Y, part, beta, st);
-    default: return series_on<16, 1>(g, n, hubs, nhub, sbits, Q, L, seeds, H, Y, part, beta, st);
+    case 1: return on(series_on<1, 4, 1>, series_on<1, 64, 1>);
+    case 2: return on(series_on<2, 4, 2>, series_on<2, 32, 1>);
+    case 4: return on(series_on<4, 2, 2>, series_on<4, 16, 1>);
+    case 8: return on(series_on<8, 1, 2>, series_on<8, 16, 2>);
+    default: return on(series_on<16, 1, 2>, series_on<16, 8, 2>);
     }
 }
 
@@ -290,7 +312,7 @@ hipError_t launch_series(const uint32_t* rp, const uint32_t* col, const uint32_t
 // with four lanes a row (more instructions for the sums than for the reads),
 // 212 us so.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kLaneRows = kSeriesSmallNodes / 1024, kShort = 16;
+constexpr uint32_t kLaneRows = kSeriesSmallNodes / 1024, kShort = kSeriesShortRow;
 
 __global__ __launch_bounds__(1024) void series_small_kernel(const uint4* tab, uint32_t nrow, uint32_t idw, uint32_t n,
                                                             int32_t L, const SeriesPair* pairs, double* beta)
