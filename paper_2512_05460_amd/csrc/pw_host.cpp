@@ -207,6 +207,7 @@ struct bd_graph {
     bool runs_shared = false;                          // code 8: the table fits the walk-sharing kernels
     DevBuf hubs;                                       // storage ids of the rows above kHubDegree
     uint32_t nhubs = 0;
+    uint32_t long_rows = 0, long_entries = 0;          // rows above kSeriesShortRow, their entries
     DevBuf sblk, sids, slds, spid;                     // tables of the sign-table kernels (none: empty)
     SignTables signs{}, signs_lds{};                   // the two forms' arguments
     SignShape sign_shape[3][kSignShapes];              // launch shapes for 1, 2 and 4 probes per walk
@@ -828,8 +829,14 @@ extern "C" int graph_load_csr(int64_t n, const int64_t* row_ptr, const int32_t* 
     }
     {
         std::vector<uint32_t> hubs;
-        for (size_t i = 0; i < (size_t)n; ++i)
-            if (rp32[i + 1] - rp32[i] > kHubDegree) hubs.push_back((uint32_t)i);
+        for (size_t i = 0; i < (size_t)n; ++i) {
+            const uint32_t d = rp32[i + 1] - rp32[i];
+            if (d > kHubDegree) hubs.push_back((uint32_t)i);
+            if (d > kSeriesShortRow) {
+                ++g->long_rows;
+                g->long_entries += d;
+            }
+        }
         g->nhubs = (uint32_t)hubs.size();
         const int hrc = g->hubs.alloc(hubs.size() * 4);
         if (hrc != BD_OK) {
@@ -1846,6 +1853,23 @@ const uint32_t* plain_ids(const bd_graph* g)
     return packed_ids(g) ? nullptr : g->col.as<const uint32_t>();
 }
 
+// Whether nq truncated series take the one-work-group form. Its step costs about
+// 0.8 us, half a microsecond for every 64 rows above kSeriesShortRow and 53 ns for
+// every 1,000 entries of those, whatever the pairs up to one a compute unit; the
+// general form's about 3.4 us (a launch) and 50 ns a pair, for every 64 pairs.
+// Measured, a pair and eight, one work group and general form: 1,000 nodes of 7
+// neighbours 0.7 and 0.7 us, 3.3 and 3.6; of 42 neighbours 10.6 and 10.6, 3.3 and
+// 4.2; 250 nodes of 249 neighbours 6.1 and 6.1, 3.4 and 5.0.
+bool small_series(const bd_graph* g, int64_t nq)
+{
+    const SignTables& t = g->signs_lds;
+    if (!t.tabw || g->n > (int64_t)kSeriesSmallNodes || series_small_bytes(t.nblk, t.idw, (uint32_t)g->n) > kSignLdsMost)
+        return false;
+    const double step = 0.8 + 0.5 * (double)((g->long_rows + 63u) / 64u) + 5.3e-5 * (double)g->long_entries;
+    const double general = 3.4 * (double)((nq + 63) / 64) + 0.05 * (double)nq;
+    return step * (double)((nq + 255) / 256) <= general;
+}
+
 }  // namespace
 
 extern "C" int bd_truncated_beta(bd_graph* g, int64_t nq, const int32_t* s, const int32_t* t, int32_t L,
@@ -1860,7 +1884,7 @@ extern "C" int bd_truncated_beta(bd_graph* g, int64_t nq, const int32_t* s, cons
     const uint32_t n = (uint32_t)g->n;
     auto inverse_degree = [&](int32_t v) { return 1.0 / (double)g->deg[(size_t)v]; };
     const SignTables& lt = g->signs_lds;
-    if (lt.tabw && n <= kSeriesSmallNodes && series_small_bytes(lt.nblk, lt.idw, n) <= kSignLdsMost) {
+    if (small_series(g, nq)) {
         // a small graph: one launch, a work group per pair
         for (int64_t q0 = 0; q0 < nq; q0 += 65536) {
             const size_t Q = (size_t)std::min<int64_t>(65536, nq - q0);
