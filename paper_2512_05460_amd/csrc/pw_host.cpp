@@ -1911,14 +1911,20 @@ extern "C" int bd_truncated_beta(bd_graph* g, int64_t nq, const int32_t* s, cons
     HIP_TRY(hipMemGetInfo(&free_b, &total_b));
     uint32_t Qmax = (uint32_t)std::min<int64_t>(64, nq);
     auto matrix = [&](uint32_t Q) { return (size_t)n * series_columns(Q) * series_slabs(Q) * 8; };
-    while (Qmax > 1 && 2 * matrix(Qmax) > free_b / 2) Qmax = Qmax > 16 ? (Qmax - 1) / 16 * 16 : Qmax / 2;
+    auto fewer = [](uint32_t Q) { return Q > 16 ? (Q - 1) / 16 * 16 : Q / 2; };
+    while (Qmax > 1 && 2 * matrix(Qmax) > free_b / 2) Qmax = fewer(Qmax);
     DevBuf dh, dy, dpart, dbeta;
-    int rc = dh.alloc(matrix(Qmax));
-    if (rc == BD_OK) rc = dy.alloc(matrix(Qmax));
+    int rc = dbeta.alloc(64 * 8);
     if (rc == BD_OK)
         rc = dpart.alloc((size_t)kSeriesParts * 2 * 8 * series_columns(Qmax) * series_slabs(Qmax) + sizeof(SeriesSeeds));
-    if (rc == BD_OK) rc = dbeta.alloc(64 * 8);
     if (rc != BD_OK) return rc;
+    for (;; Qmax = fewer(Qmax)) {
+        rc = dh.alloc(matrix(Qmax));
+        if (rc == BD_OK) rc = dy.alloc(matrix(Qmax));
+        if (rc == BD_OK) break;
+        dh.release();
+        if (Qmax == 1) return rc;  // an allocator may hold less than the device has free
+    }
     for (int64_t q0 = 0; q0 < nq; q0 += Qmax) {
         const uint32_t Q = (uint32_t)std::min<int64_t>(Qmax, nq - q0);
         // v_0 = D^{-1} b_st in storage ids

@@ -136,12 +136,13 @@ __device__ __forceinline__ double block_columns(double v, double* lds)
 // ---------------------------------------------------------------------------
 template <int C, int P, int V>
 __global__ __launch_bounds__(256) void series_step_kernel(RowTables g, uint32_t n, const uint32_t* hubs, uint32_t nhub,
-                                                          uint32_t sbits, const SeriesSeeds* seeds, const double* H,
-                                                          double* Y)
+                                                          uint32_t sbits, uint32_t slabs, const SeriesSeeds* seeds,
+                                                          const double* H, double* Y)
 {
     __shared__ double lds[256];
     constexpr uint32_t kColLanes = C / V, kLanes = kColLanes * P, kRowsAtOnce = 256u / kLanes;
     const uint32_t slab = blockIdx.x & ((1u << sbits) - 1u);
+    if (slab >= slabs) return;  // the whole work group (of three slabs)
     const uint32_t c = (threadIdx.x & (kColLanes - 1u)) * V, q = slab * C + c;
     uint32_t s[V], t[V];
     double vs[V], vt[V];
@@ -187,8 +188,8 @@ __global__ __launch_bounds__(256) void series_step_kernel(RowTables g, uint32_t 
 // v_0; and the seeds left in memory for the steps, whose launches are a
 // microsecond each longer with 1.5 KB of arguments.
 template <int C>
-__global__ __launch_bounds__(256) void series_start_kernel(uint32_t n, uint32_t sbits, SeriesSeeds seeds, double* H,
-                                                           SeriesSeeds* kept)
+__global__ __launch_bounds__(256) void series_start_kernel(uint32_t n, uint32_t sbits, uint32_t slabs, SeriesSeeds seeds,
+                                                           double* H, SeriesSeeds* kept)
 {
     if (blockIdx.x == 0 && threadIdx.x < 64u) {
         kept->s[threadIdx.x] = seeds.s[threadIdx.x];
@@ -199,18 +200,20 @@ __global__ __launch_bounds__(256) void series_start_kernel(uint32_t n, uint32_t 
     const uint32_t slab = blockIdx.x & ((1u << sbits) - 1u), item = blockIdx.x >> sbits;
     const uint32_t c = threadIdx.x & (C - 1u), q = slab * C + c;
     const uint32_t row = item * (256u / C) + threadIdx.x / C;
-    if (row >= n) return;
+    if (row >= n || slab >= slabs) return;
     H[((size_t)slab * n + row) * C + c] = row == seeds.s[q] ? seeds.vs[q] : row == seeds.t[q] ? seeds.vt[q] : 0.0;
 }
 
 // ||h||^2 and 1^T h of each column in a fixed order: kSeriesParts row ranges,
 // then (second kernel) one work group a column.
 template <int C>
-__global__ __launch_bounds__(256) void series_sums_kernel(uint32_t n, uint32_t sbits, const double* H, double* part)
+__global__ __launch_bounds__(256) void series_sums_kernel(uint32_t n, uint32_t sbits, uint32_t slabs, const double* H,
+                                                          double* part)
 {
     __shared__ double lds[256];
     const uint32_t slab = blockIdx.x & ((1u << sbits) - 1u), item = blockIdx.x >> sbits;
     const uint32_t c = threadIdx.x & (C - 1u);
+    if (slab >= slabs) return;
     double sq = 0.0, lin = 0.0;
     for (uint32_t row = item * (256u / C) + threadIdx.x / C; row < n; row += kSeriesParts * (256u / C)) {
         const double h = H[((size_t)slab * n + row) * C + c];
@@ -246,14 +249,16 @@ static hipError_t series_on(const RowTables& g, uint32_t n, const uint32_t* hubs
                             double* beta, hipStream_t st)
 {
     const uint32_t per = 256u / (C / V * P), rows = (n + per - 1) / per, all = (n + 256u / C - 1) / (256u / C);
+    const uint32_t slabs = series_slabs(Q);
     const dim3 block(256);
-    SeriesSeeds* kept = reinterpret_cast<SeriesSeeds*>(part + ((size_t)C << sbits) * kSeriesParts * 2);
-    hipLaunchKernelGGL((series_start_kernel<C>), dim3(all << sbits), block, 0, st, n, sbits, seeds, H, kept);
+    SeriesSeeds* kept = reinterpret_cast<SeriesSeeds*>(part + (size_t)C * slabs * kSeriesParts * 2);
+    hipLaunchKernelGGL((series_start_kernel<C>), dim3(all << sbits), block, 0, st, n, sbits, slabs, seeds, H, kept);
     for (int32_t i = 0; i < L; ++i) {
-        hipLaunchKernelGGL((series_step_kernel<C, P, V>), dim3((rows + nhub) << sbits), block, 0, st, g, n, hubs, nhub, sbits, kept, H, Y);
+        hipLaunchKernelGGL((series_step_kernel<C, P, V>), dim3((rows + nhub) << sbits), block, 0, st, g, n, hubs, nhub, sbits,
+                           slabs, kept, H, Y);
         std::swap(H, Y);
     }
-    hipLaunchKernelGGL((series_sums_kernel<C>), dim3(kSeriesParts << sbits), block, 0, st, n, sbits, H, part);
+    hipLaunchKernelGGL((series_sums_kernel<C>), dim3(kSeriesParts << sbits), block, 0, st, n, sbits, slabs, H, part);
     hipLaunchKernelGGL(series_finish_kernel, dim3(Q), block, 0, st, n, part, beta);
     return hipGetLastError();
 }
@@ -273,10 +278,7 @@ uint32_t series_columns(uint32_t Q)
 
 uint32_t series_slabs(uint32_t Q)
 {
-    const uint32_t slabs = (Q + series_columns(Q) - 1) / series_columns(Q);
-    uint32_t p = 1;
-    while (p < slabs) p <<= 1;
-    return p;
+    return (Q + series_columns(Q) - 1) / series_columns(Q);
 }
 
 hipError_t launch_series(const uint32_t* rp, const uint32_t* col, const uint32_t* col24, uint32_t n,
@@ -287,8 +289,8 @@ hipError_t launch_series(const uint32_t* rp, const uint32_t* col, const uint32_t
     uint32_t sbits = 0;
     while ((1u << sbits) < series_slabs(Q)) ++sbits;
     auto on = [&](auto narrow, auto wave) {
-        return (n << sbits) > kSeriesWaveRows ? narrow(g, n, hubs, nhub, sbits, Q, L, seeds, H, Y, part, beta, st)
-                                    : wave(g, n, hubs, nhub, sbits, Q, L, seeds, H, Y, part, beta, st);
+        return ((uint64_t)n << sbits) > kSeriesWaveRows ? narrow(g, n, hubs, nhub, sbits, Q, L, seeds, H, Y, part, beta, st)
+                                                           : wave(g, n, hubs, nhub, sbits, Q, L, seeds, H, Y, part, beta, st);
     };
     switch (series_columns(Q)) {
     case 1: return on(series_on<1, 4, 1>, series_on<1, 64, 1>);
