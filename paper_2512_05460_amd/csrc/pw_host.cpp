@@ -319,6 +319,13 @@ int fetch_device_offsets(int64_t n, const int64_t* row_ptr, const int32_t* col_i
     return BD_OK;
 }
 
+// Waits for the stream when its scope is left, before buffers declared ahead of it
+// go: an allocator may hand them out again while copies into them are under way.
+struct AwaitOnExit {
+    hipStream_t st;
+    ~AwaitOnExit() { (void)hipStreamSynchronize(st); }
+};
+
 template <class T>
 int upload(DevBuf& b, const std::vector<T>& v, hipStream_t st)
 {
@@ -523,17 +530,22 @@ uint32_t sign_waves(const SignShape& s, uint32_t share, uint32_t R)
 }
 
 // Tables of the sign-table kernels, for graphs whose block table and one sign
-// table fit a CU's LDS. `order`: storage id -> caller id (empty: the tables are
-// stored in the caller's order, and the descending-degree one is made here).
-int load_sign_tables(bd_graph* g, const std::vector<uint32_t>& order_in, const LoadCsr& csr, const int64_t* row_ptr,
-                     const int32_t* col_host, hipStream_t st)
+// table fit a CU's LDS. order_in: storage id -> caller id, its row offsets in
+// rp_in; empty: the tables are stored in the caller's order, and the
+// descending-degree one is made here.
+int load_sign_tables(bd_graph* g, const std::vector<uint32_t>& order_in, const std::vector<uint32_t>& rp_in,
+                     const LoadCsr& csr, const int64_t* row_ptr, const int32_t* col_host, hipStream_t st)
 {
     const size_t n = (size_t)g->n, nnz = (size_t)g->nnz;
     if (n > (size_t(1) << 22) || nnz == 0 || 3 * nnz + 8 > UINT32_MAX) return BD_OK;
-    const std::vector<uint32_t> order = order_in.empty() ? degree_order(g->deg, g->d_max) : order_in;
-    std::vector<uint32_t> rp(n + 1);
-    rp[0] = 0;
-    for (size_t i = 0; i < n; ++i) rp[i + 1] = rp[i] + (uint32_t)g->deg[order[i]];
+    std::vector<uint32_t> order_made, rp_made;
+    if (order_in.empty()) {
+        order_made = degree_order(g->deg, g->d_max);
+        rp_made.resize(n + 1);
+        rp_made[0] = 0;
+        for (size_t i = 0; i < n; ++i) rp_made[i + 1] = rp_made[i] + (uint32_t)g->deg[order_made[i]];
+    }
+    const std::vector<uint32_t>&order = order_in.empty() ? order_made : order_in, &rp = order_in.empty() ? rp_made : rp_in;
     SignOrder so;
     SignTables mem{}, lds{};
     if (g->d_max < (1 << 20) && plan_sign_order(rp, &so)) {
@@ -586,51 +598,41 @@ int load_sign_tables(bd_graph* g, const std::vector<uint32_t>& order_in, const L
         for (size_t v = 0; v < n; ++v) g->sid4[storage_id(g, (int32_t)v)] = 4u * (ranked ? rank[v] : (uint32_t)v);
     }
     if (use[0]) {
-        std::vector<uint32_t> pos, blk;
-        build_sign_order(rp, so, &pos, &blk);
-        std::vector<uint32_t> entry(2 * (size_t)mem.nblk, 0u);
-        for (uint32_t b = 0; b < so.nblk; ++b) {
-            entry[2 * b] = blk[4 * (size_t)b];
-            entry[2 * b + 1] = blk[4 * (size_t)b + 2];
-        }
-        // positions by caller id; the groups of 32 that hold nodes, and the ids that
-        // their probe values are evaluated on (padding repeats the id before it)
-        std::vector<uint32_t> at(n), word, pid;
-        for (size_t i = 0; i < n; ++i) {
-            const uint32_t id = g->layout == 5 ? (uint32_t)i : order[i], x = pos[i];
-            at[order[i]] = x;
-            if (word.empty() || word.back() != x / 32) word.push_back(x / 32);
-            pid.resize(32 * word.size() - 32 + x % 32, pid.empty() ? 0u : pid.back());
-            pid.push_back(id);
-        }
-        pid.resize(32 * word.size(), pid.back());
-        // as the kernel reads them: of 64 groups, each one's first four ids, then the next four, ...
-        const size_t segs = (word.size() + 63) / 64;
-        std::vector<uint32_t> ids_by_lane(segs * 2048, 0u);
-        for (size_t w = 0; w < word.size(); ++w)
-            for (size_t i = 0; i < 32; ++i)
-                ids_by_lane[(w / 64) * 2048 + (i / 4) * 256 + (w % 64) * 4 + i % 4] = pid[32 * w + i];
-        pid.swap(ids_by_lane);
+        std::vector<uint32_t> blk, word;
+        build_sign_order(rp, so, nullptr, &blk);
+        const std::vector<uint32_t> entry = pack_sign_blocks(blk);
+        const std::vector<SignRun> runs = sign_runs(so, &word);
         mem.words = (uint32_t)word.size();
-        pid.insert(pid.end(), word.begin(), word.end());
-        DevBuf d_order, d_at, d_rp;
+        const size_t segs = (word.size() + 63) / 64;
+        const bool relabelled = !g->internal.empty();
+        DevBuf d_order, d_at, d_rank, d_rp, d_runs;
+        const AwaitOnExit await{st};
         rc = upload(g->sblk, entry, st);
-        if (rc == BD_OK) rc = upload(g->spid, pid, st);
+        if (rc == BD_OK) rc = g->spid.alloc((segs * 2048 + word.size()) * 4);
         if (rc == BD_OK) rc = upload(d_order, order, st);
-        if (rc == BD_OK) rc = upload(d_at, at, st);
         if (rc == BD_OK) rc = upload(d_rp, rp, st);
+        if (rc == BD_OK) rc = upload(d_runs, runs, st);
+        if (rc == BD_OK) rc = d_at.alloc(n * 4);
+        if (rc == BD_OK && relabelled) rc = d_rank.alloc(n * 4);
         if (rc == BD_OK) rc = g->sids.alloc(3 * nnz + 8);
         if (rc != BD_OK) return rc;
+        uint32_t* pid = g->spid.as<uint32_t>();
+        HIP_TRY(launch_zero(pid, segs * 2048 * 4, st));
+        HIP_TRY(hipMemcpyAsync(pid + segs * 2048, word.data(), word.size() * 4, hipMemcpyHostToDevice, st));
+        HIP_TRY(launch_sign_positions((uint32_t)n, d_order.as<const uint32_t>(), d_runs.as<const SignRun>(),
+                                      (uint32_t)runs.size() - 1u, g->layout == 5 ? 1 : 0, d_at.as<uint32_t>(),
+                                      d_rank.as<uint32_t>(), pid, st));
         HIP_TRY(zero_pad24(g->sids, (size_t)nnz, st));
         HIP_TRY(launch_rename(csr.view, (uint32_t)nnz, d_order.as<const uint32_t>(), d_at.as<const uint32_t>(),
                               d_rp.as<const uint32_t>(), nullptr, g->sids.as<uint8_t>(), st));
+        // positions by storage id, for the endpoints of queries
+        g->spos.resize(n);
+        HIP_TRY(hipMemcpyAsync(g->spos.data(), relabelled ? d_rank.p : d_at.p, n * 4, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
         mem.blk = g->sblk.as<const uint4>();
-        mem.pid = g->spid.as<const uint32_t>();
+        mem.pid = pid;
         mem.ids = g->sids.as<const uint32_t>();
         g->signs = mem;
-        g->spos.resize(n);
-        for (size_t v = 0; v < n; ++v) g->spos[storage_id(g, (int32_t)v)] = at[v];
     }
     return BD_OK;
 }
@@ -851,7 +853,7 @@ extern "C" int graph_load_csr(int64_t n, const int64_t* row_ptr, const int32_t* 
         }
     }
     if (!(flags & (BD_NARROW_HUBS | BD_DIRECT_HUBS | BD_WIDE_HUBS))) {
-        const int src = load_sign_tables(g, order, csr, row_ptr, on_device ? nullptr : col_idx, st);
+        const int src = load_sign_tables(g, order, rp32, csr, row_ptr, on_device ? nullptr : col_idx, st);
         if (src != BD_OK) {
             delete g;
             return src;

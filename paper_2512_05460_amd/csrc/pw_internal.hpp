@@ -260,6 +260,8 @@ hipError_t launch_components(const CsrView& g, int64_t nnz, uint32_t* parent, ui
 hipError_t launch_rename(const CsrView& g, uint32_t nnz, const uint32_t* order, const uint32_t* map, const uint32_t* rp,
                          uint32_t* ids, uint8_t* ids24, hipStream_t st);
 hipError_t launch_nodes(uint32_t n, const uint32_t* order, const uint32_t* rp, uint4* node, uint2* node8, hipStream_t st);
+hipError_t launch_sign_positions(uint32_t n, const uint32_t* order, const SignRun* runs, uint32_t nruns, int ranked,
+                                 uint32_t* at, uint32_t* rank, uint32_t* pid, hipStream_t st);
 hipError_t build_fat_adjacency(const uint4* node, const uint32_t* col, void* adj, int layout, uint32_t nnz,
                                hipStream_t st);
 // Gather-roofline microbenchmark: `chains` in {1, 2, 4, 8} chains per lane.

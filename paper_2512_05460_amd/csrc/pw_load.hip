@@ -242,4 +242,41 @@ hipError_t launch_nodes(uint32_t n, const uint32_t* order, const uint32_t* rp, u
     return hipGetLastError();
 }
 
+// Positions and probe ids of the sign-table kernels (SignTables::pid), from the runs
+// of equal degree: node i of the descending order has position pos + (i - first) of
+// its run. at: by caller id; rank: by i, or null. pid: of each word of 32 positions
+// the ids that probes are evaluated on, of 64 words 4 ids at a time; positions of a
+// word behind a run's last node repeat its id. (Four loops over the nodes on the
+// host, and two more copies up, took 5 of a load's 11.5 ms at n = 1e6.)
+__global__ __launch_bounds__(256) void sign_positions_kernel(uint32_t n, const uint32_t* order, const SignRun* runs,
+                                                             uint32_t nruns, int ranked, uint32_t* at, uint32_t* rank,
+                                                             uint32_t* pid)
+{
+    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < n; i += gridDim.x * 256u) {
+        uint32_t lo = 0, hi = nruns;
+        while (hi - lo > 1u) {
+            const uint32_t mid = lo + (hi - lo) / 2u;
+            if (runs[mid].first <= i) lo = mid;
+            else hi = mid;
+        }
+        const SignRun r = runs[lo], next = runs[lo + 1];
+        const uint32_t v = order[i], id = ranked ? i : v, x = r.pos + (i - r.first);
+        at[v] = x;
+        if (rank) rank[i] = x;
+        const uint32_t w = r.word + (x / 32u - r.pos / 32u);
+        auto put = [&](uint32_t y) { pid[(w / 64u) * 2048u + (y / 4u) * 256u + (w % 64u) * 4u + y % 4u] = id; };
+        put(x % 32u);
+        if (i + 1u == next.first)
+            for (uint32_t y = x + 1u; y % 32u != 0u && y < next.pos; ++y) put(y % 32u);
+    }
+}
+
+hipError_t launch_sign_positions(uint32_t n, const uint32_t* order, const SignRun* runs, uint32_t nruns, int ranked,
+                                 uint32_t* at, uint32_t* rank, uint32_t* pid, hipStream_t st)
+{
+    hipLaunchKernelGGL(sign_positions_kernel, dim3(std::min((n + 255u) / 256u, 16384u)), dim3(256), 0, st, n, order, runs,
+                       nruns, ranked, at, rank, pid);
+    return hipGetLastError();
+}
+
 }  // namespace pw

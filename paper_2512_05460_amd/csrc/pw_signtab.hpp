@@ -79,17 +79,41 @@ inline bool plan_sign_order(const std::vector<uint32_t>& rp, SignOrder* o)
     return best != ~uint64_t(0);
 }
 
-// pos[storage id] and the block entries {base, d, bits of 1.0f/d, 0}: position
-// x of a block has row offset base + x d (32-bit arithmetic, base may wrap).
+// Where each run lies: its first storage id, first position, and first word of 32
+// positions among those that hold nodes; then {n, ~0, the number of words}.
+struct SignRun {
+    uint32_t first, pos, word;
+};
+
+inline std::vector<SignRun> sign_runs(const SignOrder& o, std::vector<uint32_t>* words)
+{
+    std::vector<SignRun> runs;
+    words->clear();
+    uint32_t x0 = 0;
+    for (size_t r = 0; r + 1 < o.run.size(); ++r) {
+        const uint32_t len = o.run[r + 1] - o.run[r];
+        uint32_t w = x0 / 32;
+        if (!words->empty() && words->back() == w) ++w;  // begins in the last one's second half
+        runs.push_back(SignRun{o.run[r], x0, (uint32_t)words->size() - (w - x0 / 32)});
+        for (; w <= (x0 + len - 1) / 32; ++w) words->push_back(w);
+        x0 += ((len + (1u << o.shift) - 1) >> o.shift) << o.shift;
+    }
+    runs.push_back(SignRun{o.run.back(), ~0u, (uint32_t)words->size()});
+    return runs;
+}
+
+// pos[storage id] (unless null) and the block entries {base, d, bits of 1.0f/d, 0}:
+// position x of a block has row offset base + x d (32-bit arithmetic, base may wrap).
 inline void build_sign_order(const std::vector<uint32_t>& rp, const SignOrder& o, std::vector<uint32_t>* pos,
                              std::vector<uint32_t>* blk)
 {
-    pos->resize(rp.size() - 1);
+    if (pos) pos->resize(rp.size() - 1);
     blk->assign((size_t)o.nblk * 4, 0u);
     uint32_t at = 0;  // next block
     for (size_t r = 0; r + 1 < o.run.size(); ++r) {
         const uint32_t f = o.run[r], e = o.run[r + 1], d = rp[f + 1] - rp[f], x0 = at << o.shift;
-        for (uint32_t i = f; i < e; ++i) (*pos)[i] = x0 + (i - f);
+        if (pos)
+            for (uint32_t i = f; i < e; ++i) (*pos)[i] = x0 + (i - f);
         const float inv = 1.0f / (float)d;
         const uint32_t nb = (e - f + (1u << o.shift) - 1) >> o.shift, base = rp[f] - x0 * d;
         for (uint32_t b = 0; b < nb; ++b) {
@@ -100,6 +124,19 @@ inline void build_sign_order(const std::vector<uint32_t>& rp, const SignOrder& o
         }
         at += nb;
     }
+}
+
+// The entries as the kernels read them, {base, bits of 1.0f/d}, an even number.
+// They take d as the whole number next to the reciprocal of 1.0f/d, which holds
+// below 2^20.
+inline std::vector<uint32_t> pack_sign_blocks(const std::vector<uint32_t>& blk)
+{
+    std::vector<uint32_t> entry((blk.size() / 4 + 1) / 2 * 4, 0u);
+    for (size_t b = 0; b < blk.size() / 4; ++b) {
+        entry[2 * b] = blk[4 * b];
+        entry[2 * b + 1] = blk[4 * b + 2];
+    }
+    return entry;
 }
 
 }  // namespace pw
