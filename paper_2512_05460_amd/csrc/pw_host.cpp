@@ -858,11 +858,6 @@ extern "C" int graph_load_csr(int64_t n, const int64_t* row_ptr, const int32_t* 
             delete g;
             return src;
         }
-        // (the first question also allows the kernels their LDS)
-        for (const int share : {1, 2, 4})
-            for (const int part : {kSignUniform, kSignAny})
-                for (int i = 0; i < kSignShapes; ++i)
-                    if (sign_shape(g, share, i).threads) resident_wgs(g, part, share, i);
     }
     g->device_bytes = (int64_t)(g->node.bytes + g->col.bytes + g->adj.bytes + g->rp32.bytes + g->col24.bytes +
                                 g->node8.bytes + g->runtab.bytes + g->sblk.bytes + g->sids.bytes + g->slds.bytes +
@@ -1021,6 +1016,7 @@ hipError_t launch_kernel(const bd_graph* g, WalkArgs& a, int part, int share, in
 {
     const int uniform = part == kSignUniform || part == kWalkUniform;
     if (!sign_part(part)) return launch_walk(a, run_kernel(g, share), uniform, share, grid, st);
+    (void)resident_wgs(g, part, share, shape);  // (the first question also allows the kernel its LDS)
     a.signs = sign_tables(g, share, shape);
     return launch_signs(a, sign_shape(g, share, shape), uniform, share, grid, st);
 }
@@ -1384,6 +1380,7 @@ int run_batch(bd_graph* g, const Batch& b, const bd_exec& ex, hipStream_t user_s
     for (int part = 0; part < kKernelParts; ++part) {
         const uint32_t nch = b.part_begin[part + 1] - b.part_begin[part];
         if (nch == 0) continue;
+        (void)resident_wgs(g, part, b.share, b.shape);  // asked here, not while a launch is captured
         uint32_t grid = ex.grid_wgs > 0 ? (uint32_t)ex.grid_wgs
                                          : (uint32_t)persistent_wgs(g, part, b.share, b.shape, b.load);
         grids[part] = std::min<uint32_t>(grid, nch);
