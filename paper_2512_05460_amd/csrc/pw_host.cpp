@@ -2901,6 +2901,11 @@ extern "C" int bd_server_create(bd_graph* g, const bd_server_cfg* cfg, bd_server
     }
     S->resident[0] = server_wgs(S, kWalkAny, 0);
     S->resident[1] = server_wgs(S, kWalkUniform, 0);
+    // (the scheduler thread launches later: the sign-table kernels' questions are asked on this one)
+    const int share = share_class(policy_share(S->pol));
+    for (int i = 0; i < kSignShapes; ++i)
+        if (sign_shape(g, share, i).threads)
+            for (const int part : {kSignUniform, kSignAny}) (void)resident_wgs(g, part, share, i);
     int rc = S->d_qd.alloc((size_t)S->slots * sizeof(QueryDesc));
     if (rc == BD_OK) rc = S->d_bs.alloc((size_t)S->slots * S->gdim * 16);
     if (rc == BD_OK) rc = S->d_done.alloc((size_t)S->slots * 4);
