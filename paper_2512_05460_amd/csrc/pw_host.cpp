@@ -1438,16 +1438,24 @@ int run_batch(bd_graph* g, const Batch& b, const bd_exec& ex, hipStream_t user_s
     };
     if (ex.mode == BD_MODE_PLAIN) {
         status = zero_all(st);
-        // one query per launch, one work group per chunk
+        // one query per launch, one work group per chunk; as many launches as the
+        // 2^32 work items of one ask for
         auto launch_query = [&](size_t q) -> int {
-            const uint32_t c0 = b.chunk_begin[q];
             const uint32_t c1 = q + 1 < nv ? b.chunk_begin[q + 1] : (uint32_t)b.chunks.size();
-            WalkArgs aq = a;
-            aq.chunks = static_cast<const Chunk*>(w.chunks) + c0;
-            aq.nchunks = c1 - c0;
-            aq.persistent = 0;
-            ++launches;
-            return launch_part(aq, b.part[q], b.shapes[q], c1 - c0, st);
+            const uint32_t threads = sign_part(b.part[q]) ? sign_shape(g, b.share, b.shapes[q]).threads
+                                                          : (uint32_t)block_threads(run_kernel(g, b.share), b.share);
+            const uint32_t most = 0xFFFFFFFFu / threads;
+            int rc = BD_OK;
+            for (uint32_t c = b.chunk_begin[q]; c < c1 && rc == BD_OK;) {
+                WalkArgs aq = a;
+                aq.chunks = static_cast<const Chunk*>(w.chunks) + c;
+                aq.nchunks = std::min(most, c1 - c);
+                aq.persistent = 0;
+                ++launches;
+                rc = launch_part(aq, b.part[q], b.shapes[q], aq.nchunks, st);
+                c += aq.nchunks;
+            }
+            return rc;
         };
         if (watch) {
             for (size_t q = 0; q < nv && status == BD_OK; ++q) {
