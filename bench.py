@@ -895,7 +895,8 @@ def main():
         best = max((B.bd_gather_roofline(dg, c, 1000) for c in (2, 4, 8)), key=lambda r: r["steps_per_s"])
         roof = {"steps_per_s": best["steps_per_s"], "chains_per_lane": best["chains_per_lane"],
                 "frac": kernel_sps / best["steps_per_s"],
-                "what": "same dependent loads on the same tables, no Philox or probe arithmetic"}
+                "what": ("the general walk kernel's dependent loads on this layout's tables, no Philox or probe "
+                         "arithmetic; sign_kernel reads one 3-byte position a step from tables of its own")}
     if args.copy_calib:
         n = args.copy_calib * (1 << 20) // 4
         x = torch.empty(n, dtype=torch.float32, device="cuda")
@@ -957,7 +958,8 @@ def main():
             "traffic": None if traffic_per_step is None else traffic_per_step * steps_per_launch / 1e9,
             "traffic_unit": "GB per launch",
             "traffic_note": traffic_note,
-            "kernel": "walk_kernel",
+            "kernel": ("sign_kernel; walk_kernel for queries that score a probe less often than its table "
+                       "would be evaluated"),
             "avg_launch_ms": kms_all / max(1, launches_all),
             "walk_steps_per_launch": steps_per_launch,
             "kernel_walk_steps_per_s": kernel_sps,

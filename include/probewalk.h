@@ -77,7 +77,10 @@ typedef struct bd_graph bd_graph;
 #define BD_LAYOUT_CSR       0u  /* node table {offset, degree, 1/degree} + neighbour ids:
                                    two dependent gathers per walk step */
 #define BD_LAYOUT_FAT       1u  /* adds 16-byte adjacency entries {neighbour, its offset,
-                                   its degree, its 1/degree}: one gather per walk step */
+                                   its degree, its 1/degree}: one gather per walk step. Of 8
+                                   bytes {neighbour and its degree, its offset} up to 2^22
+                                   nodes, 2^29 - 1 entries and degrees of 127, except with
+                                   non-temporal loads */
 #define BD_SKIP_VALIDATION  2u  /* trust the caller: skip the symmetry, sortedness and
                                    connectivity checks (ranges are still checked) */
 #define BD_RELABEL_DEGREE   4u  /* store nodes in descending-degree order (locality of the
@@ -322,8 +325,9 @@ int bd_query_batch(bd_graph* g, int64_t nq, const int32_t* s, const int32_t* t,
  * inputs and outputs in host memory and the graph stays as loaded.
  *   Arguments, results and errors as bd_query_batch, and additionally:
  *   - BD_E_SCRATCH when the batch's buffers exceed the array, also in chunks of
- *     4,096 pairs, which are taken then (about 650 bytes per query plus 32 per chunk, and 36 per probe of queries whose probes
- *     are split in batched mode); nothing runs then;
+ *     4,096 pairs, which are taken then (about 650 bytes per query plus 32 per
+ *     chunk, and 36 per probe of queries whose probes are split in batched
+ *     mode); nothing runs then;
  *   - BD_E_INVALID when the current device is not the graph's;
  *   - exec->use_graph is ignored (no hipGraph), and stats->walk_kernel_ms is
  *     0 (no timing events); the other stats are filled.
@@ -391,7 +395,8 @@ int bd_query_stabilized(bd_graph* g, int64_t nq, const int32_t* s, const int32_t
  * Autotuner: runs the (small, representative) sample batch once per candidate
  * execution configuration and returns the fastest by walk-kernel time in *best:
  * chunk_pairs in {128, 256, ..., 16384} with 8 chunk queues, then (BATCHED)
- * the best of those with 1 queue. times_ms (host, may be NULL) receives the
+ * the best of those with 1 queue. The automatic sizes (chunk_pairs = 0), which
+ * differ from query to query, are not among them: time them beside *best. times_ms (host, may be NULL) receives the
  * kernel time of each of the n_candidates (<= 16) candidates in that order;
  * *n_candidates is set to the count.
  */

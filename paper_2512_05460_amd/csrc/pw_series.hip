@@ -310,9 +310,9 @@ hipError_t launch_series(const uint32_t* rp, const uint32_t* col, const uint32_t
 // in every step), in descending order of their length so that a wave's rows
 // need equally many reads; longer rows take 16 lanes that read the ids from LDS
 // and add up by DPP.
-// n = 1,000, 6,000 entries, 3 pairs, L = 200: 815 us as 200 launches, 333 us
-// with four lanes a row (more instructions for the sums than for the reads),
-// 212 us so.
+// n = 1,000, 6,000 entries, 3 pairs, L = 200: 815 us as 200 launches, the kernel 333
+// us with four lanes a row (more instructions for the sums than for the reads), 212
+// us of a call's 245 so.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kLaneRows = kSeriesSmallNodes / 1024, kShort = kSeriesShortRow;
 

@@ -3,15 +3,16 @@
 // A probe's sign z^(k)(x) is a fixed function of the node. A chunk scores each
 // of its probes 2 R (L + 1) times, and where that is more often than the graph
 // has nodes it is cheaper to evaluate the Feistel permutation and the hash once
-// per node into a table in LDS and let the walks look the sign up: 23
-// instructions per walk step instead of 118. The tables are indexed by the
+// per node into a table in LDS and let the walks look the sign up: 29
+// vector instructions per walk step, the tables' building included, instead of
+// 118. The tables are indexed by the
 // node's position in the kernels' own tables, so the walks need neither the
 // caller's id nor a row table from memory whatever layout the graph was loaded
 // in. Two forms:
 //
 //   * Small graphs (kLds): row offset and degree of every node (4 bytes) and the
 //     whole adjacency (2 bytes an entry) are staged in LDS, and a table holds
-//     z / d as binary32. A step is three LDS reads and 14 instructions.
+//     z / d as binary32. A step is three LDS reads.
 //   * Larger ones: nodes are stored in descending degree, each run of equal
 //     degree padded to whole blocks of 2^shift positions, so a block has one
 //     degree d and a node x of it has row offset base + x d. One LDS read of
