@@ -455,8 +455,9 @@ struct GeneralLoad {
 // So four groups for walks of up to 120 steps, two up to 600, and beyond that one
 // where a query has fewer pairs than an XCD then runs at once and the tables are
 // large; with 16-byte entries and such tables one always, or two for queries of
-// more pairs. Non-temporal entries come from memory at every step and take two:
-// 65,536 queries on 20.7 GB of them 2,855 ms on one, 2,686 on two and on all.
+// more pairs. Tables of which nearly every step's read comes from memory (the
+// non-temporal ones) take two: 65,536 queries on 20.7 GB 2,855 ms on one, 2,686 on
+// two and on all; with ordinary loads 3,071, 2,946 and 2,947.
 // The 1,024-thread kernels take one group for such long walks of small queries
 // where their tables exceed the L2s together (the grid, hubs first, L = 1,000 26.0
 // for 29.1 ms; within L2 their two groups hide its latency). On the degree-run
@@ -474,7 +475,7 @@ int persistent_wgs(const bd_graph* g, int part, int share, int shape, const Gene
                                              : load.steps_per_walk > 600.0;
         return small && far && g->device_bytes > kAllL2Bytes ? std::min(r, cus) : r;
     }
-    if (layout == kLayoutFatNT) return std::min(r, 2 * cus);
+    if (layout == kLayoutFatNT || g->device_bytes >= kFatNontemporalBytes) return std::min(r, 2 * cus);
     if (layout == kLayoutFat && g->device_bytes > kWideEntryBytes) return std::min(r, small ? cus : 2 * cus);
     if (load.steps_per_walk <= 120.0) return std::min(r, 4 * cus);
     return std::min(r, small && load.steps_per_walk > 600.0 && g->device_bytes > kLongWalkBytes ? cus : 2 * cus);
