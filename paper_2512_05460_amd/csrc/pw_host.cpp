@@ -638,6 +638,16 @@ int load_sign_tables(bd_graph* g, const std::vector<uint32_t>& order_in, const s
     return BD_OK;
 }
 
+void drop_sign_tables(bd_graph* g)
+{
+    for (DevBuf* b : {&g->sblk, &g->sids, &g->slds, &g->spid}) b->release();
+    g->signs = g->signs_lds = SignTables{};
+    for (auto& shapes : g->sign_shape)
+        for (SignShape& s : shapes) s = SignShape{};
+    g->spos.clear();
+    g->sid4.clear();
+}
+
 }  // namespace
 
 extern "C" int bd_set_allocator(const bd_allocator* a)
@@ -854,7 +864,11 @@ extern "C" int graph_load_csr(int64_t n, const int64_t* row_ptr, const int32_t* 
         }
     }
     if (!(flags & (BD_NARROW_HUBS | BD_DIRECT_HUBS | BD_WIDE_HUBS))) {
-        const int src = load_sign_tables(g, order, rp32, csr, row_ptr, on_device ? nullptr : col_idx, st);
+        int src = load_sign_tables(g, order, rp32, csr, row_ptr, on_device ? nullptr : col_idx, st);
+        if (src == BD_E_NOMEM) {  // the general kernels run every query without them
+            drop_sign_tables(g);
+            src = BD_OK;
+        }
         if (src != BD_OK) {
             delete g;
             return src;
